@@ -46,7 +46,7 @@ static int device_cus() {
     return n;
 }
 
-bool make_layout(const sc_gemm_desc &d, int cus, Layout *lay) {
+static bool layout_with(const sc_gemm_desc &d, int cus, bool plans, Layout *lay) {
     Layout l{};
     l.cus = cus > 0 ? cus : DEFAULT_CUS;
     l.KQP = (int)round_up((d.K + 3) / 4, 4);
@@ -77,15 +77,35 @@ bool make_layout(const sc_gemm_desc &d, int cus, Layout *lay) {
     // the status word is always the first word of the workspace
     size_t off = 0;
     l.off_status = off;
-    off = align256(off + 4 * 4);
+    off = align256(off + 8 * 4);
+    // (the int8-chunk GEMM's sequences are in its plans' slots)
     l.off_rA = off;
-    off = align256(off + (size_t)l.LBS * 4);
+    if (!l.rgen) off = align256(off + (size_t)l.LBS * 4);
     l.off_rB = off;
-    off = align256(off + (size_t)l.LBS * 4);
+    if (!l.rgen) off = align256(off + (size_t)l.LBS * 4);
     l.off_CA = off;
     if (cbsg) off = align256(off + (size_t)(d.L_max + 1) * CA_COLS * 2);
+    // Slot plans: while a tile's products sum to less than 2^24 in magnitude whatever slots hold
+    // them (K x L_max; so every part is exact), and more than one group of 32 cycles exists.
+    // At most 32 plans past the first, and at most PLAN_GROUPS tables.  Short tiles with varying
+    // lengths (attention heads: K = 64) go without: their pairs hold rows from 94 to 453 cycles,
+    // so the prefixes are short against the longest row, and the wait for a tile's plan costs
+    // each of them more (ViT-L/14 Q.K^T 411 us without plans, 416 with).
+    const double Lmean = d.L_hint > 0 ? d.L_hint : d.L_max;
+    const bool one_length = Lmean >= d.L_max, long_tiles = (int64_t)l.KC * ((int64_t)(Lmean + 31) / 32) >= 16;
+    l.nplans = 1;
+    l.pstep = LCH;
+    if (plans && l.rgen && (one_length || long_tiles) && l.LBS > 32 && (int64_t)l.KC * 32 * l.LBS < MFMA_EXACT) {
+        const int n = PLAN_GROUPS / (l.LBS / 32) < 32 ? PLAN_GROUPS / (l.LBS / 32) : 32;
+        l.pstep = (int)round_up((d.L_max + n - 1) / n, 8);
+        l.nplans = 1 + (d.L_max + l.pstep - 1) / l.pstep;
+    }
+    l.off_plan = off;
+    if (l.rgen) off = align256(off + (size_t)l.nplans * 16);
+    l.off_pslots = off;
+    if (l.rgen) off = align256(off + (size_t)l.nplans * l.LBS * 8);
     l.off_rtab = off;
-    if (l.rgen) off = align256(off + (size_t)(l.LBS / 32) * 512 * 16);
+    if (l.rgen) off = align256(off + (size_t)l.nplans * (l.LBS / 32) * 512 * 16);
 
     // one A block per batch entry
     const size_t rowsA = (size_t)l.MT * BM;
@@ -95,9 +115,11 @@ bool make_layout(const sc_gemm_desc &d, int cus, Layout *lay) {
     l.off_Ls = a;
     a = align256(a + rowsA * 4);
     l.off_tileL = a;
-    a = align256(a + (size_t)l.MT * 4);
+    if (!l.rgen) a = align256(a + (size_t)l.MT * 4);
     l.off_tileOff = a;
-    a = align256(a + (size_t)l.MT * 8);
+    if (!l.rgen) a = align256(a + (size_t)l.MT * 8);
+    l.off_pair = a;
+    if (l.rgen) a = align256(a + (size_t)(l.MT / 2 + 1) * 16);
     l.off_Ap = a;
     // largest planes of one batch entry: every tile at L_max rounded up to an octet
     if (!mul_ok((size_t)l.MT * (size_t)l.words_per_L, (size_t)round_up(d.L_max, MSTEP) * 4, &sz))
@@ -147,7 +169,6 @@ bool make_layout(const sc_gemm_desc &d, int cus, Layout *lay) {
     const int smax = kunits > l.Smin ? kunits : l.Smin;
     // partial-sum bytes of one part (256-row blocks of N <= 64 compute 64 columns)
     const double tile_bytes = (double)l.mbm * (l.narrow ? 64 : l.mbn) * 4.0;
-    const double Lmean = d.L_hint > 0 ? d.L_hint : d.L_max;
     l.S = l.Smin;
     l.F = 0;
     if (quad && tiles > 0) {
@@ -165,7 +186,7 @@ bool make_layout(const sc_gemm_desc &d, int cus, Layout *lay) {
         l.q_slots = l.narrow ? 2 * l.cus : l.cus;
         l.q_Lmean = Lmean;
         l.q_pbytes = tile_bytes;
-        l.q_one = Lmean >= d.L_max;
+        l.q_one = one_length;
         const double avgT = l.q_perL * Lmean, maxT = l.q_perL * d.L_max;
         double best = 0.0;
         for (int s = l.Smin; s <= MAX_SPLIT && s <= smax; s *= 2) {
@@ -218,19 +239,18 @@ bool make_layout(const sc_gemm_desc &d, int cus, Layout *lay) {
     // Int8-chunk GEMM with varying lengths: the work of a tile follows its rows' lengths
     // (Sec. 4.1: the cost follows the sum of the l_i), known only on the device.  There the
     // tiles' chunk steps are laid end to end and cut into sk_slots equal ranges, one per GEMM
-    // block (k_units): a tile inside a range runs whole, one that a cut crosses runs in
+    // block (k_rprep): a tile inside a range runs whole, one that a cut crosses runs in
     // pieces that the split-sum pass adds.  A range holds at most RSTEP_EXACT steps, so every
     // whole tile and piece sums exactly.
     // (Short tiles, a few chunk steps each, keep the division below: their pieces' partial sums
     // and their in-GEMM decodes would cost as much as the steps; ViT-L/14 Q.K^T heads with
     // K = 64 took 0.61 ms cut into ranges against 0.41 ms split alike.)
     l.pcols = l.narrow ? 64 : l.mbn;
-    l.vsplit = quad && l.rgen && tiles > 0 && !l.q_one &&
-               (int64_t)l.KC * ((int64_t)(Lmean + 31) / 32) >= 16;
+    l.vsplit = quad && l.rgen && tiles > 0 && !l.q_one && long_tiles;
     l.off_units = off;
     int64_t pieces = quad ? (tiles - l.F) * (int64_t)l.S : tiles * (int64_t)l.S;
     if (l.vsplit) {
-        // (k_units weighs a step at most w1 and at least w2 and adds at most 7 w1 per tile for
+        // (k_rprep weighs a step at most w1 and at least w2 and adds at most 7 w1 per tile for
         // its decode and a minimum step: W <= w1 wmax.  A range of cost T = ceil(W / sl) <=
         // w1 wmax / sl + 1 holds at most T / w2 + 1 steps, which must stay below RSTEP_EXACT;
         // the 256 x 64 blocks' ranges hold up to twice T.)
@@ -273,10 +293,21 @@ bool make_layout(const sc_gemm_desc &d, int cus, Layout *lay) {
     l.off_Ls += baseA;
     l.off_tileL += baseA;
     l.off_tileOff += baseA;
+    l.off_pair += baseA;
     l.off_Ap += baseA;
     l.off_Bp += baseB;
     l.total = off;
     *lay = l;
+    return true;
+}
+
+bool make_layout(const sc_gemm_desc &d, int cus, Layout *lay) {
+    if (!layout_with(d, cus, true, lay)) return false;
+    // a call that fits sc_gemm_noalloc's array without the tables of the slot plans keeps fitting it
+    Layout one;
+    if (lay->nplans > 1 && lay->total > SC_NOALLOC_WORKSPACE_BYTES && layout_with(d, cus, false, &one) &&
+        one.total <= SC_NOALLOC_WORKSPACE_BYTES)
+        *lay = one;
     return true;
 }
 
@@ -329,9 +360,10 @@ static int enqueue(const sc_gemm_desc &d, const Layout &lay, const int8_t *A, co
                    hipStream_t st) {
     uint32_t *rA = reinterpret_cast<uint32_t *>(ws + lay.off_rA);
     // one batch entry with LFSR sequences: the scheduler's single block also clears the
-    // status and makes the sequences (one launch fewer); otherwise k_draws does, first
+    // status and makes the sequences (one launch fewer); otherwise k_draws does, first.  The
+    // int8-chunk GEMM's scheduler and k_rprep write all that k_draws would
     const bool empty = d.batch == 0 || d.M == 0 || d.N == 0;
-    const bool fuse = !empty && d.batch == 1 && d.rng == SC_RNG_LFSR32;
+    const bool fuse = !empty && (lay.rgen || (d.batch == 1 && d.rng == SC_RNG_LFSR32));
     hipError_t e = hipSuccess;
     if (!fuse) {
         e = launch_draws(d.seed, d.rng, lay.LBS, rA, reinterpret_cast<uint32_t *>(ws + lay.off_rB), nullptr, -1,
@@ -344,9 +376,8 @@ static int enqueue(const sc_gemm_desc &d, const Layout &lay, const int8_t *A, co
         launch_cbsg_table(rA, d.L_max, reinterpret_cast<uint16_t *>(ws + lay.off_CA), st) != hipSuccess)
         return SC_ERR_HIP;
     if ((e = launch_schedule(d, lay, L_per_row, ws, fuse, st)) != hipSuccess) return SC_ERR_HIP;
-    if (lay.vsplit && (e = launch_units(d, lay, ws, st)) != hipSuccess) return SC_ERR_HIP;
     if (lay.rgen) {
-        if ((e = launch_rchunks(d, lay, A, B, ws, st)) != hipSuccess) return SC_ERR_HIP;
+        if ((e = launch_rprep(d, lay, A, B, ws, st)) != hipSuccess) return SC_ERR_HIP;
     } else if (!lay.fused) {
         if ((e = launch_mplanes(d, lay, A, B, ws, st)) != hipSuccess) return SC_ERR_HIP;
     }

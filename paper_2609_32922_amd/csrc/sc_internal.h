@@ -4,25 +4,33 @@
 //
 //   status     one uint32 (bit 0: some L_i out of range), then one uint32: the longest
 //              tile-pair cycle count of the call (256-row GEMM), then one uint32: nonzero
-//              when some 256-row pair holds more distinct lengths that are not multiples of
-//              32 than the int8-chunk GEMM has masked tables (rslots; it then masks its
-//              fragments); all cleared by k_draws (or k_schedule); then one uint32: the
-//              work units of the 256-row GEMM when their division follows the tile lengths
-//              (written by k_units)
-//   draws      rA[LBS], rB[LBS]                   uint32, comparator sequences
+//              when some 256-row pair holds more row lengths that end inside a slot group
+//              than the int8-chunk GEMM has masked tables (rslots; it then masks its
+//              fragments).  Cleared by k_draws (or k_schedule), or, int8-chunk GEMM, written
+//              by k_rprep
+//   draws      rA[LBS], rB[LBS]                   uint32, comparator sequences (not with rgen)
 //   CA         C-BSG only: CA[L][beta] = #{l < L : rA_l < beta}, uint16 [L_max+1][257]
-//   rtab       int8-chunk GEMM only: for each 32-cycle group G, the fp4 slot row of every
-//              int8 byte for A and for B: uint4 [LBS/32][2][256] (built once per call)
+//   plan       int8-chunk GEMM only: slot plans (see below), int4 {prefix, merged slots,
+//              slots in all, 0} each, and their slots, uint2 [plan][LBS]
+//   rtab       int8-chunk GEMM only: for each plan and 32-slot group G, the fp4 slot row of
+//              every int8 byte for A and for B: uint4 [plan][LBS/32][2][256] (built once per
+//              call, for the plans that some pair takes)
 //   per batch entry b of A (batch entries):
 //     perm[MT*BM]      sorted position -> original row (or -1 for padding)
 //     Ls[MT*BM]        stream length at each sorted position
 //     tileL[MT]        cycles the GEMM runs for row tile t: the longest L of the tile (of
 //                      the tile pair with 256-row blocks), rounded up to 8
 //     tileOff[MT]      word offset of tile t's planes inside Ap
+//     pair[MT/2]       int8-chunk GEMM, in place of tileL and tileOff: int4 {longest, shortest
+//                      length, distinct lengths, those not multiples of 32} of each 256-row
+//                      pair (k_schedule), which k_rprep replaces with {32-slot groups, plan,
+//                      slots the plan saves, slots of a row of L_max cycles}; then the batch
+//                      entry's record {bad length, longest length rounded up to 8, bits of the
+//                      plans its pairs take (two words)}
 //     Ap               fp4 planes of A (or int8 chunks, below)
 //   part       partial counts when GEMM tiles are split along the inner (element, cycle) range
-//   units      vsplit only (k_units): the 256-row GEMM's work units {tile, first chunk step,
-//              end chunk step, partial index or -1} (int4), per tile {pieces, partial index
+//   units      vsplit only (k_rprep): the 256-row GEMM's work units {tile, first chunk step,
+//              end chunk step, UNIT_PLAN * plan + partial index + 1 (0: none)} (int4), per tile {pieces, partial index
 //              of piece 0} (int2), and per GEMM block the first of its units (uint32,
 //              sk_slots + 1 of them)
 //   per batch entry of B (1 if B is broadcast, else batch entries):
@@ -84,6 +92,26 @@ __host__ __device__ inline double quad_split_time(int64_t tiles, int s, double p
     const double red = s > 1 ? (double)tiles * (2 * s) * part_bytes / PART_BW + 5e-6 : 0.0;
     return (load > maxT / s ? load : maxT / s) + red;
 }
+// Slot plans of the int8-chunk GEMM.  The count of an element pair is a sum over cycles of
+// zA_l zB_l, and cycle l's A bit is a function of the element's value alone: z = [n >= c],
+// with n = q + 127 (bipolar) or |q| (unipolar) and c = the class of the draw r_l, the least n
+// whose boundary lies above r_l.  There are only 254 (bipolar) or 127 (unipolar) classes, so
+// cycles whose A draws share a class have the same A bit for every element, and their B bits
+// can be added first: sum_l a b_l = a sum_l b_l.  The same holds with A and B swapped.  A slot
+// is such a set of cycles; it holds +-1 (or 0) on one side and a sum of up to SLOT_CYCLES bits
+// on the other, an integer of magnitude <= 4, which fp4 e2m1 represents exactly.  The cycles
+// are edges between A classes and B classes, a slot takes the edges of one class, so the
+// fewest slots are a minimum vertex cover: 88 of 128 cycles for bipolar streams, 140 of 256,
+// 212 of 512, and 58 of 96, 90 of 192 for unipolar ones (means over seeds).  The sum over a
+// slot's cycles is only right for rows that run all of them, so plan k covers the cycles
+// below its prefix p_k, and cycle p_k + j keeps a slot of its own, S_k + j: a 256-row pair
+// takes the plan with the largest prefix no longer than its shortest row, and a row of L >=
+// p_k cycles ends after S_k + L - p_k slots.  Prefixes: multiples of pstep, and L_max.
+constexpr int SLOT_CYCLES = 4;
+constexpr int MAX_PLANS = 40;    // plans of a call (bits of the status words)
+constexpr int PLAN_GROUPS = 512; // most (plan, group) tables of a call, 8 KiB each
+constexpr int UNIT_PLAN = 1 << 24;   // a unit's partial index (below 2^22) and plan in one word
+
 constexpr int OCH = 8;           // octets per block of the nibble-plane generator
 constexpr int RSLOTS = 4;        // int8-chunk GEMM: tables masked to a row length, per cycle group
 constexpr int64_t MFMA_EXACT = 1ll << 24;   // products one fp32 accumulator sums exactly
@@ -118,6 +146,45 @@ __device__ __forceinline__ int beta_unipolar(int q) {
 
 __device__ __forceinline__ int wave_uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
+// classes of a draw r in [0, 255]: the least n = q + 127 (bipolar) or n = |q| (unipolar) whose
+// boundary floor((256 n + 127) / 254) (floor((256 n + 63) / 127)) lies above r, so that
+// [r < beta] = [n >= class]
+__host__ __device__ inline int class_bipolar(int r) { return (254 * r + 127 + 255) >> 8; }
+__host__ __device__ inline int class_unipolar(int r) { return (127 * r + 64 + 255) >> 8; }
+
+// Inclusive scan across a 64-lane wave.
+template <typename T>
+__device__ __forceinline__ T wave_incl_scan(T v, int lane) {
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const T t = __shfl_up(v, o, 64);
+        if (lane >= o) v += t;
+    }
+    return v;
+}
+
+// Exclusive scan over a block of NT threads; returns the block total in *total.
+template <int NT, typename T>
+__device__ T block_excl_scan(T v, T *total) {
+    constexpr int NW = NT / 64;
+    __shared__ T wsum[NW];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const T inc = wave_incl_scan(v, lane);
+    if (lane == 63) wsum[w] = inc;
+    __syncthreads();
+    // (every thread adds up the waves before its own: NW <= 16 broadcast reads, no second scan)
+    T base = 0, all = 0;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) {
+        const T x = wsum[k];
+        if (k < w) base += x;
+        all += x;
+    }
+    *total = all;
+    __syncthreads();
+    return base + inc - v;
+}
+
 template <typename T>
 __device__ __forceinline__ T *ws_ptr(uint8_t *ws, size_t off) {
     return reinterpret_cast<T *>(ws + off);
@@ -141,8 +208,9 @@ struct Layout {
     int KC;            // 32-element chunks per row, ceil(K/32)
     int cus;           // compute units of the device the call runs on
     int64_t words_per_L;   // plane words of one 128-row tile per cycle of its length
-    size_t off_rA, off_rB, off_status, off_CA, off_rtab;
-    size_t off_perm, off_Ls, off_tileL, off_tileOff, off_Ap;
+    int nplans, pstep;     // rgen: slot plans (1: every cycle has its own slot) and their spacing
+    size_t off_rA, off_rB, off_status, off_CA, off_plan, off_pslots, off_rtab;
+    size_t off_perm, off_Ls, off_tileL, off_tileOff, off_pair, off_Ap;
     size_t stride_batchA;          // bytes per A batch entry block
     size_t off_Bp;
     size_t stride_batchB;          // bytes per B batch entry block
@@ -159,7 +227,7 @@ struct Layout {
     int p16;           // int8-chunk GEMM split into parts of at most P16_STEPS chunk steps: the
                        // partial counts are int16 ([pieces][256 rows][pcols columns])
     int vsplit;        // int8-chunk GEMM with varying lengths: the tiles' chunk steps, end to
-                       // end, are cut into sk_slots equal ranges, one per GEMM block (k_units)
+                       // end, are cut into sk_slots equal ranges, one per GEMM block (k_rprep)
     int sk_slots;      // vsplit: GEMM blocks, each running one range of the work
     size_t off_units, off_tinfo, off_slot;
     size_t total;
@@ -173,11 +241,10 @@ bool make_layout(const sc_gemm_desc &d, int cus, Layout *lay);
 hipError_t launch_draws(uint64_t seed, int rng, int n, uint32_t *rA, uint32_t *rB,
                         uint8_t *bytes_out, int op_only, uint32_t *status, hipStream_t st);
 hipError_t launch_cbsg_table(const uint32_t *rA, int L_max, uint16_t *CA, hipStream_t st);
-// draws: also clear the status words and make the comparator sequences (one batch entry only)
+// draws: also clear the status words and make the comparator sequences (one batch entry only);
+// with rgen also the slot plans
 hipError_t launch_schedule(const sc_gemm_desc &d, const Layout &lay, const int32_t *L,
                            uint8_t *ws, bool draws, hipStream_t st);
-// the 256-row GEMM's work units from the scheduled tile lengths (Layout::vsplit)
-hipError_t launch_units(const sc_gemm_desc &d, const Layout &lay, uint8_t *ws, hipStream_t st);
 
 // counting GEMM (sc_mfma.hip)
 // Profiling events of the next launch_mgemm / launch_fgemm on this host thread (sc_gemm's
@@ -194,12 +261,26 @@ hipError_t launch_mgemm(const sc_gemm_desc &d, const Layout &lay, const float *s
 hipError_t launch_fgemm(const sc_gemm_desc &d, const Layout &lay, const int8_t *A, const int8_t *B,
                         const float *sA, const float *sB, float *out, int32_t *counts, uint8_t *ws,
                         hipStream_t st);
-hipError_t launch_rchunks(const sc_gemm_desc &d, const Layout &lay, const int8_t *A, const int8_t *B,
+hipError_t launch_rprep(const sc_gemm_desc &d, const Layout &lay, const int8_t *A, const int8_t *B,
                           uint8_t *ws, hipStream_t st);
 
 // bytes of one batch entry of an operand from its first byte: (rows - 1) * ld + K
 __host__ __device__ inline int64_t fused_extent(int rows, int64_t ld, int K) {
     return rows > 0 && K > 0 ? (int64_t)(rows - 1) * ld + K : 0;
+}
+
+// cycles below which slot plan k merges (k < nplans), and the plan of a pair whose shortest row
+// has L cycles
+__host__ __device__ inline int plan_prefix(int k, int nplans, int pstep, int L_max) {
+    return k == 0 ? 0 : k == nplans - 1 ? L_max : k * pstep;
+}
+__host__ __device__ inline int plan_of(int L, int nplans, int pstep, int L_max) {
+    return nplans == 1 ? 0 : L >= L_max ? nplans - 1 : L / pstep;
+}
+// slots of a row of L cycles in a pair whose plan saves `save` slots and gives L_max `top` slots
+// (top counts whole groups: the slots past the last cycle are zero)
+__device__ __forceinline__ int slot_length(int L, int save, int top, int L_max) {
+    return L <= 0 ? 0 : L >= L_max ? top : L - save;
 }
 
 // thresholds and ladder of the per-row length policy, passed by value to the kernel

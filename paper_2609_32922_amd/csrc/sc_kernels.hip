@@ -3,12 +3,14 @@
 //   k_draws      comparator sequences r^A, r^B (Sec. 3.1 "Bitstream generation",
 //                LFSR or scrambled Sobol-8 of Sec. A.1) -- one lane per cycle, the LFSR
 //                through jump-ahead; it also clears the status words.  With one batch
-//                entry and LFSR sequences k_schedule does both instead (one launch fewer)
+//                entry and LFSR sequences k_schedule does both instead (one launch fewer),
+//                and the int8-chunk GEMM needs neither
 //   k_cbsg_table C-BSG only: CA[L][beta] = ones of A's stream in its first L cycles
 //   k_schedule   per-row length scheduler: validates L_i, counting-sorts rows by L
 //                (descending) so that a 128-row tile runs for the longest length it
 //                holds (Sec. 4.2: row i stops after its own l_i cycles; Sec. 4.1: the
 //                cost grows with the sum of the l_i)
+//   k_schedule_plans  the same for the int8-chunk GEMM, with its slot plans beside it
 #include "sc_internal.h"
 
 namespace scg {
@@ -105,7 +107,7 @@ __global__ __launch_bounds__(256) void k_draws(uint64_t seed, int rng, int n, ui
     if (status != nullptr && l == 0 && blockIdx.y == 0) {
         status[0] = 0u;
         status[1] = 0u;   // longest tile pair of the call
-        status[2] = 0u;   // some row pair holds more lengths inside a cycle group than tables
+        status[2] = 0u;   // (int8-chunk GEMM only; k_rprep writes it)
     }
     if (l >= n) return;
     const uint32_t v = draw_value(seed, rng, op, l);
@@ -117,7 +119,7 @@ __global__ __launch_bounds__(256) void k_draws(uint64_t seed, int rng, int n, ui
 
 hipError_t launch_draws(uint64_t seed, int rng, int n, uint32_t *rA, uint32_t *rB,
                         uint8_t *bytes_out, int op_only, uint32_t *status, hipStream_t st) {
-    dim3 grid((unsigned)((n + 255) / 256), op_only >= 0 ? 1u : 2u);
+    dim3 grid((unsigned)((n > 0 ? n : 1) + 255) / 256, op_only >= 0 ? 1u : 2u);
     hipLaunchKernelGGL(k_draws, grid, dim3(256), 0, st, seed, rng, n, rA, rB, bytes_out, op_only,
                        status);
     return hipGetLastError();
@@ -146,40 +148,6 @@ hipError_t launch_cbsg_table(const uint32_t *rA, int L_max, uint16_t *CA, hipStr
 }
 
 // ----------------------------------------------------------------------------
-// helpers
-// ----------------------------------------------------------------------------
-
-// Inclusive scan across a 64-lane wave.
-__device__ __forceinline__ int64_t wave_incl_scan(int64_t v, int lane) {
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int64_t t = __shfl_up(v, o, 64);
-        if (lane >= o) v += t;
-    }
-    return v;
-}
-
-// Exclusive scan over a 1024-thread block; returns the block total in *total.
-__device__ int64_t block_excl_scan_1024(int64_t v, int64_t *total) {
-    __shared__ int64_t wsum[16];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int64_t inc = wave_incl_scan(v, lane);
-    if (lane == 63) wsum[w] = inc;
-    __syncthreads();
-    if (w == 0) {
-        int64_t x = lane < 16 ? wsum[lane] : 0;
-        x = wave_incl_scan(x, lane);
-        if (lane < 16) wsum[lane] = x;
-    }
-    __syncthreads();
-    const int64_t base = w > 0 ? wsum[w - 1] : 0;
-    *total = wsum[15];
-    __syncthreads();
-    return base + inc - v;
-}
-
-
-// ----------------------------------------------------------------------------
 // per-row length scheduler (one 1024-thread block per batch entry)
 // ----------------------------------------------------------------------------
 // Adds 1 to hist[l] for every active lane and returns the lane's old value (its place
@@ -201,20 +169,27 @@ __device__ int wave_bucket_add(int *hist, int l, bool active) {
     return active ? atomicAdd(&hist[l], 1) : 0;
 }
 
-__global__ __launch_bounds__(1024) void k_schedule(const int32_t *__restrict__ L, int64_t strideL,
-                                                   int M, int L_max, Layout lay, uint8_t *ws, uint64_t seed,
-                                                   int rng, int ndraws) {
-    __shared__ int hist[SC_L_MAX_LIMIT + 1];
-    __shared__ int hstart[SC_L_MAX_LIMIT + 1];
-    __shared__ int dpair[2048 + 1];
-    __shared__ int lmin, lmax;
+struct SchedLds {
+    int hist[SC_L_MAX_LIMIT + 1], hstart[SC_L_MAX_LIMIT + 1], dpair[2048 + 1];
+    int lmin, lmax;
+    uint32_t bad, used[2];
+};
+// RGEN: of the int8-chunk GEMM.  There the block leaves what it found in its batch entry's record
+// (bad length, longest row, plans taken) instead of adding to the status words, which k_rprep
+// writes from all records: no launch has to clear them first.
+template <bool RGEN>
+__device__ __forceinline__ void schedule_block(const int32_t *__restrict__ L, int64_t strideL, int M, int L_max,
+                                               const Layout &lay, uint8_t *ws, uint64_t seed, int rng, int ndraws,
+                                               SchedLds &sh) {
+    int *hist = sh.hist, *hstart = sh.hstart, *dpair = sh.dpair;
+    int &lmin = sh.lmin, &lmax = sh.lmax;
     const int b = blockIdx.x, tid = threadIdx.x;
     uint8_t *wsb = ws + (size_t)b * lay.stride_batchA;
     int32_t *perm = ws_ptr<int32_t>(wsb, lay.off_perm);
     int32_t *Ls = ws_ptr<int32_t>(wsb, lay.off_Ls);
     int32_t *tileL = ws_ptr<int32_t>(wsb, lay.off_tileL);
     int64_t *tileOff = ws_ptr<int64_t>(wsb, lay.off_tileOff);
-    uint32_t *status = ws_ptr<uint32_t>(ws, lay.off_status);
+    uint32_t *status = RGEN ? &sh.bad : ws_ptr<uint32_t>(ws, lay.off_status);
     const int32_t *Lb = L + (size_t)b * strideL;
 
     // Up to SREG * 1024 rows the lengths are loaded once, all loads in flight together (issued
@@ -230,7 +205,7 @@ __global__ __launch_bounds__(1024) void k_schedule(const int32_t *__restrict__ L
             lv[k] = i < M ? Lb[i] : 0;
         }
     }
-    if (ndraws > 0) {
+    if (!RGEN && ndraws > 0) {
         // one batch entry: this block also clears the status words and makes the comparator
         // sequences (the work of k_draws), before any of its own status updates
         if (tid == 0) {
@@ -248,6 +223,7 @@ __global__ __launch_bounds__(1024) void k_schedule(const int32_t *__restrict__ L
     if (tid == 0) {
         lmin = INT_MAX;
         lmax = INT_MIN;
+        sh.bad = sh.used[0] = sh.used[1] = 0u;
     }
     __syncthreads();
     // the lengths held in registers: validated, and their range over the batch entry
@@ -294,8 +270,6 @@ __global__ __launch_bounds__(1024) void k_schedule(const int32_t *__restrict__ L
                 Ls[i] = l;
             }
         }
-        // every pair meets one length; it is not a multiple of 32 only when l is not
-        if (tid == 0 && lay.rgen && l % 32 != 0 && lay.rslots < 1) atomicOr(status + 2, 1u);
     } else if (cached) {
 #pragma unroll
         for (int k = 0; k < SREG; ++k)
@@ -314,17 +288,17 @@ __global__ __launch_bounds__(1024) void k_schedule(const int32_t *__restrict__ L
     __syncthreads();
     // start position of each length bucket, longest lengths first (also kept in hstart: the
     // scatter below moves hist[l] on to the end of l's run)
-    int64_t carry = 0;
+    int rcarry = 0;
     for (int c = 0; !one && c <= L_max; c += 1024) {
         const int idx = L_max - (c + tid);
-        const int64_t v = idx >= 0 ? hist[idx] : 0;
-        int64_t tot;
-        const int64_t ex = block_excl_scan_1024(v, &tot);
+        const int v = idx >= 0 ? hist[idx] : 0;
+        int tot;
+        const int ex = block_excl_scan<1024>(v, &tot);
         if (idx >= 0) {
-            hist[idx] = (int)(carry + ex);
-            hstart[idx] = (int)(carry + ex);
+            hist[idx] = rcarry + ex;
+            hstart[idx] = rcarry + ex;
         }
-        carry += tot;
+        rcarry += tot;
         __syncthreads();
     }
     if (one) {
@@ -356,40 +330,6 @@ __global__ __launch_bounds__(1024) void k_schedule(const int32_t *__restrict__ L
         perm[p] = -1;
         Ls[p] = 0;
     }
-    // The int8-chunk GEMM keeps, per cycle group, a table of A masked to each row length
-    // that ends inside the group: rslots of them.  Rows are sorted, so the distinct lengths of
-    // a pair are the runs of equal length that meet it; a pair that more lengths which are not
-    // multiples of 32 meet than there are tables makes the GEMM mask its fragments instead.
-    // Each such length adds one to every pair its run [hstart[l], end) meets (a difference
-    // array over pairs, then a scan); end = hstart[l - 1] (runs in order of decreasing
-    // length), or M.  (Up to 2048 pairs per pass; the first pass runs beside the scatter.)
-    const int npairs = lay.rgen && !one ? lay.MT / 2 : 0;
-    for (int q0 = 0; q0 < npairs; q0 += 2048) {
-        const int nq = min(npairs - q0, 2048);
-        if (q0 > 0) __syncthreads();
-        for (int q = tid; q <= nq; q += 1024) dpair[q] = 0;
-        __syncthreads();
-        for (int l = tid; l <= L_max; l += 1024) {
-            const int start = hstart[l], end = l == 0 ? M : hstart[l - 1];
-            if (l % 32 == 0 || end <= start) continue;
-            const int qa = max(start >> 8, q0), qb = min((end - 1) >> 8, q0 + nq - 1);
-            if (qa > qb) continue;
-            atomicAdd(&dpair[qa - q0], 1);
-            atomicAdd(&dpair[qb + 1 - q0], -1);
-        }
-        __syncthreads();
-        int64_t pc = 0;
-        bool over = false;
-        for (int c = 0; c < nq; c += 1024) {
-            const int q = c + tid;
-            int64_t tot;
-            const int64_t v = q < nq ? dpair[q] : 0;
-            const int64_t ex = block_excl_scan_1024(v, &tot);
-            over = over || (q < nq && pc + ex + v > lay.rslots);
-            pc += tot;
-        }
-        if (__syncthreads_or(over) && tid == 0) atomicOr(status + 2, 1u);
-    }
     __syncthreads();
     // After the scatter hist[l] is the end of length l's run of sorted positions (runs in
     // order of decreasing length, ends non-increasing in l): the length at sorted position
@@ -404,147 +344,246 @@ __global__ __launch_bounds__(1024) void k_schedule(const int32_t *__restrict__ L
         }
         return lo;
     };
-    // tile lengths (first sorted row of a tile holds its longest length; a pair of tiles
-    // that one 256-row block takes runs at the pair's longest length) and, for the GEMMs that
-    // read planes, the tiles' plane offsets
-    carry = 0;
-    for (int c = 0; c < lay.MT; c += 1024) {
-        const int t = c + tid;
-        int tl = 0;
-        if (t < lay.MT) {
-            const int t0 = lay.mbm == 2 * BM ? (t & ~1) : t;
-            tl = (int)round_up(length_at(t0 * BM), MSTEP);
-            tileL[t] = tl;
+    if (RGEN) {
+        // Int8-chunk GEMM: each pair's longest and shortest length, which choose its slot plan,
+        // and how many distinct lengths it meets (the GEMM keeps a table of A masked to each
+        // row length that ends inside a group, rslots of them).  Rows are sorted, so a length is a
+        // run [hstart[l], end) and adds one to every pair that the run meets (a difference array
+        // over pairs, then a scan; lengths that are not multiples of 32 in the upper half);
+        // end = hstart[l - 1] (runs in order of decreasing length).  Up to 2048 pairs per pass.
+        int4 *pair = ws_ptr<int4>(wsb, lay.off_pair);
+        const int npairs = lay.MT / 2;
+        for (int q0 = 0; q0 < npairs; q0 += 2048) {
+            const int nq = min(npairs - q0, 2048);
+            if (!one) {
+                __syncthreads();
+                for (int q = tid; q <= nq; q += 1024) dpair[q] = 0;
+                __syncthreads();
+                for (int l = 1 + tid; l <= L_max; l += 1024) {
+                    const int start = hstart[l], end = hstart[l - 1];
+                    if (end <= start) continue;
+                    const int qa = max(start >> 8, q0), qb = min((end - 1) >> 8, q0 + nq - 1);
+                    if (qa > qb) continue;
+                    const int add = l % 32 != 0 ? 0x10001 : 1;
+                    atomicAdd(&dpair[qa - q0], add);
+                    atomicAdd(&dpair[qb + 1 - q0], -add);
+                }
+                __syncthreads();
+            }
+            int pc = 0;
+            for (int c = 0; c < nq; c += 1024) {
+                const int q = c + tid;
+                int nd = lmin > 0 ? (lmin % 32 != 0 ? 0x10001 : 1) : 0;
+                if (!one) {
+                    int tot;
+                    const int v = q < nq ? dpair[q] : 0;
+                    nd = pc + block_excl_scan<1024>(v, &tot) + v;
+                    pc += tot;
+                }
+                if (q >= nq) continue;
+                const int p = (q0 + q) * 256;
+                const int hi = one ? lmin : length_at(p), lo = one ? lmin : length_at(min(p + 255, M - 1));
+                pair[q0 + q] = make_int4(hi, lo, nd & 0xFFFF, nd >> 16);
+                const int k = plan_of(lo, lay.nplans, lay.pstep, L_max);
+                atomicOr(&sh.used[k >> 5], 1u << (k & 31));
+            }
         }
-        if (!lay.rgen) {
+        __syncthreads();
+        if (tid == 0)
+            pair[npairs] = make_int4((int)sh.bad, (int)round_up(one ? lmin : length_at(0), MSTEP), (int)sh.used[0],
+                                     (int)sh.used[1]);
+    } else {
+        // tile lengths (first sorted row of a tile holds its longest length; a pair of tiles
+        // that one 256-row block takes runs at the pair's longest length) and the tiles' plane
+        // offsets
+        int64_t carry = 0;
+        for (int c = 0; c < lay.MT; c += 1024) {
+            const int t = c + tid;
+            int tl = 0;
+            if (t < lay.MT) {
+                const int t0 = lay.mbm == 2 * BM ? (t & ~1) : t;
+                tl = (int)round_up(length_at(t0 * BM), MSTEP);
+                tileL[t] = tl;
+            }
             int64_t tot;
-            const int64_t ex = block_excl_scan_1024((int64_t)tl * lay.words_per_L, &tot);
+            const int64_t ex = block_excl_scan<1024>((int64_t)tl * lay.words_per_L, &tot);
             if (t < lay.MT) tileOff[t] = carry + ex;
             carry += tot;
         }
     }
     // the first tile pair holds the batch entry's longest rows
-    if (tid == 0 && lay.mbm == 2 * BM) atomicMax(status + 1, (uint32_t)round_up(length_at(0), MSTEP));
+    if (!RGEN && tid == 0 && lay.mbm == 2 * BM) atomicMax(status + 1, (uint32_t)round_up(length_at(0), MSTEP));
 }
 
-// Work division of the int8-chunk GEMM when row lengths vary (Layout::vsplit).  Tile t (pair
-// tp of batch entry b x B pair tw, in the GEMM's tile order: longest pairs first) runs
-// ceil(tileL / 32) x KC chunk steps (32-cycle groups x 32-element chunks) and then decodes.
-// Its cost, in units of the time of one step: W1 per step while every row block of the
-// block runs, W2 per step once the 256 x 64 blocks run only the first half of each wave's
-// row blocks (from the group where sorted row 128 of the pair has ended: rows are sorted by
-// length, and the blocks {2, 3} and {6, 7} of the waves' row halves hold rows 128 .. 255),
-// W3 once they run only row block 0 (from the group where sorted row 32 has ended),
-// at least 1 (a tile of rows of length 0 still writes its zeros), plus E for its decode and
-// prologue (measured: 13.6 + 3.7 us against 3.6 us per step for 256 x 256 blocks; 13.4 us
-// against 1.65 us per step for 256 x 64 blocks, whose best E measured 5 steps of 3, 5 and 8).
-// The tiles' costs are laid end to end and the total cut into sk_slots ranges of about
-// T = ceil(W / sk_slots) (see cut() below), range s for GEMM block s: every block
-// gets the same share of the MFMA work, which follows the sum of the row lengths (Sec. 4.1),
-// and of the decodes.  A tile inside one range runs whole and is decoded by its block; a
-// tile that c cuts cross through its steps runs as c + 1 pieces (a cut maps to the first
-// step whose cost ends after it), whose partial sums the split-sum pass adds (a cut through
-// the decode's share leaves the steps to one piece).  Written: units {tile, first step, end
-// step, partial index or -1} in tile order, which is range order; slot[s] = the first unit
-// of range s (slot[sk_slots] = the unit count); tinfo[t] = {pieces, partial index of piece
-// 0}.  One block.
-__global__ __launch_bounds__(1024) void k_units(Layout lay, int batch, uint8_t *ws) {
+// ----------------------------------------------------------------------------
+// slot plans of the int8-chunk GEMM (one 1024-thread block per plan)
+// ----------------------------------------------------------------------------
+// The cycles l < p of plan k are edges between the class of A's draw and the class of B's; the
+// block covers them with few classes by leaf removal: while some class holds one live cycle,
+// the class at that cycle's other end takes all of its own live cycles (all such classes at
+// once; optimal as long as such classes are found, which is nearly always up to L = 256 bipolar
+// or 192 unipolar: 2 to 5 rounds); when there is none, or after PLAN_ROUNDS rounds, A's classes
+// take what is left (more rounds, or the fullest classes first, saved at most one slot of 212
+// and none past L = 512).  A class with more than SLOT_CYCLES cycles takes several slots.  The
+// order in which cycles take places in a class's slots does not matter: every sum is an exact
+// integer.  (Latency: 16 waves around two barriers per round.)
+struct PlanLds {
+    int deg[512];                       // live cycles of each class: A's, then B's
+    int mark[512];                      // the round in which the class was taken
+    int cnt[512], base[512];            // cycles, and first slot, of each class
+    uint32_t own[SC_L_MAX_LIMIT];       // slot: class | side << 8 | cycles << 9
+    uint32_t part[SC_L_MAX_LIMIT];      // slot: its cycles' classes on the other side, a byte each
+    int wg[SC_L_MAX_LIMIT / 32];        // cycles of each group
+    int leaf[8], left[8];               // per round: a class of one live cycle exists; cycles are left
+    int wmax;
+};
+constexpr int PLAN_ROUNDS = 6;
+
+__device__ __forceinline__ void plan_block(int k, const Layout &lay, int L_max, uint8_t *ws, uint64_t seed, bool bip,
+                                           PlanLds &sh) {
+    constexpr int EPT = SC_L_MAX_LIMIT / 1024;    // cycles per thread
     const int tid = threadIdx.x;
-    const int NTW = lay.NT / 2, npairs = lay.MT / 2, slots = lay.sk_slots;
-    const int tiles = batch * npairs * NTW;
-    const int64_t W1 = lay.narrow ? RW1_NARROW : 1, W2 = lay.narrow ? RW2_NARROW : 1;
-    const int64_t W3 = lay.narrow ? RW3_NARROW : 1;
-    const int64_t E = 5 * W1;
-    // tile t's steps at weight W1, W2 and W3 (the 256 x 64 blocks: from the group after which
-    // sorted row 128, then row 32, of the pair has ended)
-    auto steps = [&](int t) -> int4 {
-        const int tb = t / NTW, b = tb % batch, tp = tb / batch;
-        uint8_t *wsb = ws + (size_t)b * lay.stride_batchA;
-        const int g0 = (ws_ptr<int32_t>(wsb, lay.off_tileL)[2 * tp] + 31) / 32;
-        int g1 = g0, g2 = g0;
-        if (lay.narrow) {
-            auto ends = [&](int r) {
-                const int L1 = ws_ptr<int32_t>(wsb, lay.off_perm)[r] >= 0 ? ws_ptr<int32_t>(wsb, lay.off_Ls)[r] : 0;
-                return min((L1 + 31) / 32, g0);
-            };
-            g1 = ends(tp * 256 + 128);
-            g2 = max(ends(tp * 256 + 32), g1);
-        }
-        return make_int4(g1 * lay.KC, (g2 - g1) * lay.KC, (g0 - g2) * lay.KC, 0);
-    };
-    auto cost = [&](int4 n) -> int64_t {
-        const int64_t c = (int64_t)n.x * W1 + (int64_t)n.y * W2 + (int64_t)n.z * W3;
-        return c > 0 ? c : 1;
-    };
-    // the steps whose cost ends at or before c (0 <= c <= cost(n); c = cost(n): every step)
-    auto step_at = [&](int4 n, int64_t c) -> int64_t {
-        const int64_t c1 = (int64_t)n.x * W1, c2 = c1 + (int64_t)n.y * W2;
-        return c < c1 ? c / W1 : c < c2 ? n.x + (c - c1) / W2 : n.x + n.y + (c - c2) / W3;
-    };
-    int64_t W = 0;
-    for (int c = 0; c < tiles; c += 1024) {
-        int64_t tot;
-        block_excl_scan_1024(c + tid < tiles ? cost(steps(c + tid)) + E : 0, &tot);
-        W += tot;
+    const int p = plan_prefix(k, lay.nplans, lay.pstep, L_max);
+    int ca[EPT], cb[EPT], rank[EPT];
+    uint32_t live = 0u, onB = 0u;
+    if (tid < 512) {
+        sh.deg[tid] = 0;
+        sh.mark[tid] = 0;
+        sh.cnt[tid] = 0;
     }
-    const int64_t T = (W + slots - 1) / slots;
-    // Range s covers the costs [cut(s), cut(s + 1)).  The 256 x 64 blocks take the ranges in
-    // pairs, 2p for the first block of a CU and 2p + 1 for the second, the first
-    // (16 + RLEAD_NARROW) / 16 T long (cut(slots) = slots T >= W either way).
-    const bool lead = lay.narrow && slots % 2 == 0;
-    const int64_t TL = lead ? T + T * RLEAD_NARROW / 16 : T;
-    auto cut = [&](int64_t s) -> int64_t { return lead ? (s >> 1) * 2 * T + (s & 1) * TL : s * T; };
-    auto range_of = [&](int64_t c) -> int64_t {
-        if (!lead) return c / T;
-        const int64_t p = c / (2 * T);
-        return 2 * p + (c - p * 2 * T >= TL ? 1 : 0);
-    };
-    int4 *units = ws_ptr<int4>(ws, lay.off_units);
-    int2 *tinfo = ws_ptr<int2>(ws, lay.off_tinfo);
-    uint32_t *slot = ws_ptr<uint32_t>(ws, lay.off_slot);
-    int64_t ccarry = 0, ucarry = 0, pcarry = 0;
-    for (int c = 0; c < tiles; c += 1024) {
-        const int t = c + tid;
-        const int4 n = t < tiles ? steps(t) : make_int4(0, 0, 0, 0);
-        const int64_t w = t < tiles ? cost(n) : 0, cw = t < tiles ? w + E : 0;
-        int64_t ctot, utot, ptot;
-        const int64_t C = ccarry + block_excl_scan_1024(cw, &ctot);
-        // ranges meeting the tile's cost; the last one starts inside the decode's share when
-        // the last cut lies past the steps: it gets no piece
-        const int nr = t < tiles ? (int)(range_of(C + cw - 1) - range_of(C) + 1) : 0;
-        const int np = nr > 1 && cut(range_of(C + cw - 1)) >= C + w ? nr - 1 : nr;
-        const int64_t U = ucarry + block_excl_scan_1024(np, &utot);
-        const int64_t P = pcarry + block_excl_scan_1024(np > 1 ? np : 0, &ptot);
-        if (t < tiles) {
-            tinfo[t] = make_int2(np, np > 1 ? (int)P : -1);
-            for (int p = 0; p < nr; ++p) {
-                const int64_t s0 = range_of(C) + p;
-                const int64_t a = p == 0 ? C : cut(s0), e = p == np - 1 ? C + w : cut(s0 + 1);
-                if (p < np)
-                    units[U + p] = make_int4(t, (int)step_at(n, a - C), (int)step_at(n, e - C),
-                                             np > 1 ? (int)(P + p) : -1);
-                // (a range starting inside the decode's share starts with the next tile's first unit)
-                if (cut(s0) == a) slot[s0] = (uint32_t)(U + p);
+    if (tid < SC_L_MAX_LIMIT / 32) sh.wg[tid] = 0;
+    if (tid < 8) sh.leaf[tid] = sh.left[tid] = 0;
+    for (int i = tid; i < p; i += 1024) sh.part[i] = 0xFFFFFFFFu;
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) {
+        const int l = i * 1024 + tid;
+        ca[i] = cb[i] = rank[i] = 0;
+        if (l >= L_max) continue;
+        const int ra = (int)draw_value(seed, SC_RNG_LFSR32, 0, l), rb = (int)draw_value(seed, SC_RNG_LFSR32, 1, l);
+        ca[i] = bip ? class_bipolar(ra) : class_unipolar(ra);
+        cb[i] = 256 + (bip ? class_bipolar(rb) : class_unipolar(rb));
+        if (l < p) live |= 1u << i;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < EPT; ++i)
+        if ((live >> i) & 1u) {
+            atomicAdd(&sh.deg[ca[i]], 1);
+            atomicAdd(&sh.deg[cb[i]], 1);
+        }
+    __syncthreads();
+    static_assert(PLAN_ROUNDS <= 8, "a flag per round");
+    for (int round = 0; round < PLAN_ROUNDS; ++round) {
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) {
+            if (!((live >> i) & 1u)) continue;
+            const bool la = sh.deg[ca[i]] == 1, lb = sh.deg[cb[i]] == 1;
+            if (la) sh.mark[cb[i]] = round + 1;
+            else if (lb) sh.mark[ca[i]] = round + 1;
+            if (la || lb) sh.leaf[round] = 1;
+        }
+        __syncthreads();
+        const bool all = round == PLAN_ROUNDS - 1 || sh.leaf[round] == 0;
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) {
+            if (!((live >> i) & 1u)) continue;
+            const bool b = !all && sh.mark[cb[i]] == round + 1;
+            if (!all && !b && sh.mark[ca[i]] != round + 1) {
+                sh.left[round] = 1;
+                continue;
             }
+            live &= ~(1u << i);
+            if (b) onB |= 1u << i;
+            atomicSub(&sh.deg[ca[i]], 1);
+            atomicSub(&sh.deg[cb[i]], 1);
         }
-        ccarry += ctot;
-        ucarry += utot;
-        pcarry += ptot;
+        __syncthreads();
+        if (sh.left[round] == 0) break;
     }
-    // ranges past the end of the work hold no unit
-    for (int64_t s = (W > 0 ? range_of(W - 1) + 1 : 0) + tid; s <= slots; s += 1024) slot[s] = (uint32_t)ucarry;
+#pragma unroll
+    for (int i = 0; i < EPT; ++i)
+        if (i * 1024 + tid < p) rank[i] = atomicAdd(&sh.cnt[(onB >> i) & 1u ? cb[i] : ca[i]], 1);
+    __syncthreads();
+    int S;
+    const int ex = block_excl_scan<1024>(tid < 512 ? (sh.cnt[tid] + SLOT_CYCLES - 1) / SLOT_CYCLES : 0, &S);
+    if (tid < 512) sh.base[tid] = ex;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) {
+        if (i * 1024 + tid >= p) continue;
+        const bool b = (onB >> i) & 1u;
+        const int v = b ? cb[i] : ca[i], o = b ? ca[i] : cb[i];
+        const int slot = sh.base[v] + rank[i] / SLOT_CYCLES, j = rank[i] % SLOT_CYCLES;
+        reinterpret_cast<uint8_t *>(&sh.part[slot])[j] = (uint8_t)(o & 255);
+        if (j == 0) {
+            const int n = min(SLOT_CYCLES, sh.cnt[v] - (rank[i] - j));
+            sh.own[slot] = (uint32_t)(v & 255) | (b ? 0x100u : 0u) | ((uint32_t)n << 9);
+            if (lay.p16) atomicAdd(&sh.wg[slot / 32], n);
+        }
+    }
+    __syncthreads();
+    // int16 partial counts (Layout::p16): a part of n chunk steps holds counts of at most 32 n x
+    // the heaviest group's cycles; where that could pass int16 the plan merges nothing
+    if (lay.p16) {
+        if (tid < 64) {
+            int m = 32;      // (a group of cycles p.., one a slot; one shared with merged slots adds < 32)
+#pragma unroll
+            for (int i = 0; i < SC_L_MAX_LIMIT / 32 / 64; ++i) {
+                const int G = i * 64 + tid, alone = S < p && G == S / 32 ? 32 - S % 32 : 0;
+                m = max(m, sh.wg[G] + alone);
+            }
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
+            if (tid == 0) sh.wmax = m;
+        }
+        __syncthreads();
+        const int64_t smin = lay.F > 0 ? lay.S : lay.Smin;
+        const int64_t steps = ((int64_t)lay.KC * ((S + L_max - p + 31) / 32) + smin - 1) / smin;
+        if (steps * 32 * sh.wmax > 32767) S = p;
+    }
+    const bool merged = S < p;
+    uint2 *slots = ws_ptr<uint2>(ws, lay.off_pslots) + (size_t)k * lay.LBS;
+    for (int i = tid; merged && i < S; i += 1024) slots[i] = make_uint2(sh.own[i], sh.part[i]);
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) {
+        const int l = i * 1024 + tid;
+        if (l < L_max && (l >= p || !merged))
+            slots[S + l - p] = make_uint2((uint32_t)ca[i] | (1u << 9), (uint32_t)(cb[i] - 256) | 0xFFFFFF00u);
+    }
+    const int T = S + L_max - p;
+    if (tid < 32 && T + tid < (int)round_up(T, 32)) slots[T + tid] = make_uint2(0u, 0xFFFFFFFFu);
+    if (tid == 0) ws_ptr<int4>(ws, lay.off_plan)[k] = make_int4(p, S, T, 0);
 }
 
-hipError_t launch_units(const sc_gemm_desc &d, const Layout &lay, uint8_t *ws, hipStream_t st) {
-    hipLaunchKernelGGL(k_units, dim3(1), dim3(1024), 0, st, lay, d.batch, ws);
-    return hipGetLastError();
+__global__ __launch_bounds__(1024) void k_schedule(const int32_t *__restrict__ L, int64_t strideL, int M, int L_max,
+                                                   Layout lay, uint8_t *ws, uint64_t seed, int rng, int ndraws) {
+    __shared__ SchedLds sh;
+    schedule_block<false>(L, strideL, M, L_max, lay, ws, seed, rng, ndraws, sh);
+}
+
+// Int8-chunk GEMM: blocks 0 .. batch-1 schedule a batch entry each, the rest make a slot plan each
+union SchedPlanLds {
+    SchedLds s;
+    PlanLds p;
+};
+__global__ __launch_bounds__(1024) void k_schedule_plans(const int32_t *__restrict__ L, int64_t strideL, int batch,
+                                                         int M, int L_max, Layout lay, uint8_t *ws, uint64_t seed,
+                                                         int polarity) {
+    __shared__ SchedPlanLds sh;
+    if ((int)blockIdx.x < batch) schedule_block<true>(L, strideL, M, L_max, lay, ws, seed, SC_RNG_LFSR32, 0, sh.s);
+    else plan_block((int)blockIdx.x - batch, lay, L_max, ws, seed, polarity == SC_BIPOLAR_XNOR, sh.p);
 }
 
 hipError_t launch_schedule(const sc_gemm_desc &d, const Layout &lay, const int32_t *L, uint8_t *ws,
                            bool draws, hipStream_t st) {
+    if (lay.rgen) {
+        hipLaunchKernelGGL(k_schedule_plans, dim3((unsigned)(d.batch + lay.nplans)), dim3(1024), 0, st, L, d.strideL,
+                           d.batch, d.M, d.L_max, lay, ws, d.seed, d.polarity);
+        return hipGetLastError();
+    }
     if (draws && d.batch != 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_schedule, dim3((unsigned)d.batch), dim3(1024), 0, st, L, d.strideL, d.M,
-                       d.L_max, lay, ws, d.seed, d.rng, draws ? lay.LBS : 0);
+    hipLaunchKernelGGL(k_schedule, dim3((unsigned)d.batch), dim3(1024), 0, st, L, d.strideL, d.M, d.L_max, lay, ws,
+                       d.seed, d.rng, draws ? lay.LBS : 0);
     return hipGetLastError();
 }
 

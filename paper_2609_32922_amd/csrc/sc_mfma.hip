@@ -372,7 +372,7 @@ hipError_t launch_mplanes(const sc_gemm_desc &d, const Layout &lay, const int8_t
 // MFMA GEMM
 // ----------------------------------------------------------------------------
 struct MGemmArgs {
-    int M, N, K, KQP, LBS, nbB, batch, S, F, KC;
+    int M, N, K, KQP, LBS, nbB, batch, S, F, KC, L_max;
     const float *sA, *sB;
     int64_t strideSA, strideSB, strideO, ldo;
     float *out;
@@ -1603,25 +1603,38 @@ __device__ __forceinline__ uint32_t r_clamp4(uint32_t x) {
     return x | ((~nz & 0x80808080u) >> 7);
 }
 
-// Entry (byte, operand) of the table of cycle group G: the 32 nibbles of cycles 32G .. 32G+31
-// (cycle 32G + k at bits 4 (k % 8) of dword k / 8), sign folded in (unipolar), zero for the
-// padding byte; r points at the operand's draw of cycle 32G.  The tables of every group are
-// built once per call (k_rchunks) into the workspace, [G][operand][byte].
+// Dword w of entry (byte, side) of the table of one slot group: the nibbles of its slots 8 w ..
+// 8 w + 7 (slot 8 w + j at bits 4 j), sign folded in (unipolar), zero for the padding byte.  A
+// slot holds one bit on the side of its own class (+-1 bipolar, 0 / 1 unipolar) and the sum of its
+// cycles' bits on the other, magnitude at most SLOT_CYCLES (its unused classes are 255: a 0 bit).
+// The tables are built once per call (k_rprep) into the workspace, [plan][G][side][byte].
+static_assert(SLOT_CYCLES == 4, "a slot's classes fill one dword; fp4 holds every integer up to 4");
 template <bool BIP>
-__device__ __forceinline__ u4 r_entry(const uint32_t *r, int byte) {
-    u4 x = u4{0u, 0u, 0u, 0u};
-    if (byte == RPAD) return x;
-    const uint32_t zero_nib = BIP ? NIB_NEG : 0u;
+__device__ __forceinline__ uint32_t r_entry(const uint2 (&slots)[8], int side, int byte) {
+    if (byte == RPAD) return 0u;
     const int q = (int)(int8_t)(uint8_t)byte;
-    const uint32_t beta = (uint32_t)(BIP ? beta_bipolar(q) : beta_unipolar(q));
+    const int n = BIP ? q + 127 : abs(q);
+    uint32_t v = 0;
 #pragma unroll
-    for (int dw = 0; dw < 4; ++dw) {
-        uint32_t w = 0;
+    for (int j = 0; j < 8; ++j) {
+        const uint2 t = slots[j];
+        const int cycles = (int)(t.x >> 9);
+        int sum;
+        if ((int)((t.x >> 8) & 1u) == side) {
+            sum = n >= (int)(t.x & 255u) ? 1 : 0;
+            if (BIP) sum = 2 * sum - 1;
+            if (cycles == 0) sum = 0;
+        } else {
+            sum = 0;
 #pragma unroll
-        for (int c = 0; c < 8; ++c) w |= (r[8 * dw + c] < beta ? NIB_POS : zero_nib) << (4 * c);
-        x[dw] = (!BIP && q < 0) ? negate_nibbles(w) : w;
+            for (int c = 0; c < 4; ++c) sum += n >= (int)((t.y >> (8 * c)) & 255u) ? 1 : 0;
+            if (BIP) sum = 2 * sum - cycles;
+        }
+        // e2m1 codes of 0, 1, 2, 3, 4
+        const uint32_t code = (0x65420u >> (4 * abs(sum))) & 15u;
+        v |= ((sum < 0) != (!BIP && q < 0) && sum != 0 ? code | 8u : code) << (4 * j);
     }
-    return x;
+    return v;
 }
 
 struct RChunkArgs {
@@ -1632,8 +1645,10 @@ struct RChunkArgs {
     size_t off_perm;      // side 0 (A) takes its rows in the scheduler's order
     int K, KC;
     int vec[2];           // 16-byte loads are aligned (base and row stride multiples of 16)
-    int groups, bip;      // tables: 32-cycle groups, polarity
-    size_t off_r[2], off_rtab;
+    int bip;
+    int nt, na, gx[2], gy;   // grid: the prep block, nt table blocks, na chunk blocks of A, B's; the
+                             // chunk blocks of a batch entry are gx (64 rows each) x gy (8 chunks)
+    int L_max, batch;
 };
 
 // One 16-byte half of a chunk: bytes d0 .. d0 + 15 of row xrow (K bytes; null: a padding
@@ -1675,29 +1690,250 @@ __device__ __forceinline__ u4 r_half(const int8_t *xrow, int d0, int K, bool vec
     return v;
 }
 
+constexpr int UNIT_PAIRS = 1024;   // pairs whose steps the division keeps in LDS
+// Chunk steps of a pair's tiles at weight W1, W2 and W3 (below), and its plan, from its slots ps
+__device__ __forceinline__ int4 pair_steps(int4 ps, int b, int tp, const RChunkArgs &a, const Layout &lay, uint8_t *ws) {
+    uint8_t *wsb = ws + (size_t)b * lay.stride_batchA;
+    const int g0 = ps.x;
+    int g1 = g0, g2 = g0;
+    if (lay.narrow) {
+        // (padding rows have length 0 in the layout)
+        const int32_t *Ls = ws_ptr<int32_t>(wsb, lay.off_Ls) + tp * 256;
+        const int l1 = Ls[128], l2 = Ls[32];
+        g1 = min((slot_length(l1, ps.z, ps.w, a.L_max) + 31) / 32, g0);
+        g2 = max(min((slot_length(l2, ps.z, ps.w, a.L_max) + 31) / 32, g0), g1);
+    }
+    return make_int4(g1 * lay.KC, (g2 - g1) * lay.KC, (g0 - g2) * lay.KC, ps.y);
+}
+__device__ __forceinline__ int4 unit_steps(int t, const RChunkArgs &a, const Layout &lay, uint8_t *ws,
+                                           const int4 *spair) {
+    const int tb = t / (lay.NT / 2), b = tb % a.batch, tp = tb / a.batch;
+    const int i = b * (lay.MT / 2) + tp;
+    if (i < UNIT_PAIRS) return spair[i];
+    return pair_steps(ws_ptr<int4>(ws + (size_t)b * lay.stride_batchA, lay.off_pair)[tp], b, tp, a, lay, ws);
+}
+
+// Work division of the int8-chunk GEMM when row lengths vary (Layout::vsplit).  Tile t (pair
+// tp of batch entry b x B pair tw, in the GEMM's tile order: longest pairs first) runs
+// groups x KC chunk steps (32-slot groups x 32-element chunks) and then decodes.
+// Its cost, in units of the time of one step: W1 per step while every row block of the
+// block runs, W2 per step once the 256 x 64 blocks run only the first half of each wave's
+// row blocks (from the group where sorted row 128 of the pair has ended: rows are sorted by
+// length, and the blocks {2, 3} and {6, 7} of the waves' row halves hold rows 128 .. 255),
+// W3 once they run only row block 0 (from the group where sorted row 32 has ended),
+// at least 1 (a tile of rows of length 0 still writes its zeros), plus E for its decode and
+// prologue (measured: 13.6 + 3.7 us against 3.6 us per step for 256 x 256 blocks; 13.4 us
+// against 1.65 us per step for 256 x 64 blocks, whose best E measured 5 steps of 3, 5 and 8).
+// The tiles' costs are laid end to end and the total cut into sk_slots ranges of about
+// T = ceil(W / sk_slots) (see cut() below), range s for GEMM block s: every block
+// gets the same share of the MFMA work, which follows the sum of the row lengths (Sec. 4.1),
+// and of the decodes.  A tile inside one range runs whole and is decoded by its block; a
+// tile that c cuts cross through its steps runs as c + 1 pieces (a cut maps to the first
+// step whose cost ends after it), whose partial sums the split-sum pass adds (a cut through
+// the decode's share leaves the steps to one piece).  Written: units {tile, first step, end
+// step, UNIT_PLAN * plan + partial index + 1 (0: none)} in tile order, which is range order;
+// slot[s] = the first unit of range s (slot[sk_slots] = the unit count); tinfo[t] = {pieces,
+// partial index of piece 0}.  One block of 256 threads, beside the layout of the chunks.
+//
+// Thread i takes the i-th run of tiles, so that the whole division needs two block scans; a
+// tile's steps come from LDS (UNIT_PAIRS pairs; calls with more read the rest from memory), and
+// a total W that allows it keeps the divisions in 32 bits (I).
+template <typename I>
+__device__ void units_division(const RChunkArgs &a, const Layout &lay, uint8_t *ws, const int4 *spair, I W) {
+    const int tid = threadIdx.x;
+    const int NTW = lay.NT / 2, npairs = lay.MT / 2, slots = lay.sk_slots;
+    const int tiles = a.batch * npairs * NTW;
+    const int per = (tiles + 255) / 256, t0 = min(tid * per, tiles), t1 = min(t0 + per, tiles);
+    const I W1 = lay.narrow ? RW1_NARROW : 1, W2 = lay.narrow ? RW2_NARROW : 1, W3 = lay.narrow ? RW3_NARROW : 1;
+    const I E = 5 * W1;
+    auto cost = [&](int4 n) -> I {
+        const I c = n.x * W1 + n.y * W2 + n.z * W3;
+        return c > 0 ? c : 1;
+    };
+    // the steps whose cost ends at or before c (0 <= c <= cost(n); c = cost(n): every step)
+    auto step_at = [&](int4 n, I c) -> I {
+        const I c1 = n.x * W1, c2 = c1 + n.y * W2;
+        return c < c1 ? c / W1 : c < c2 ? n.x + (c - c1) / W2 : n.x + n.y + (c - c2) / W3;
+    };
+    const I T = (W + slots - 1) / slots;
+    // Range s covers the costs [cut(s), cut(s + 1)).  The 256 x 64 blocks take the ranges in
+    // pairs, 2p for the first block of a CU and 2p + 1 for the second, the first
+    // (16 + RLEAD_NARROW) / 16 T long (cut(slots) = slots T >= W either way).
+    const bool lead = lay.narrow && slots % 2 == 0;
+    const I TL = lead ? T + T * (I)RLEAD_NARROW / 16 : T;
+    auto cut = [&](I s) -> I { return lead ? (s >> 1) * 2 * T + (s & 1) * TL : s * T; };
+    auto range_of = [&](I c) -> I {
+        if (!lead) return c / T;
+        const I p = c / (2 * T);
+        return 2 * p + (c - p * 2 * T >= TL ? 1 : 0);
+    };
+    int4 *units = ws_ptr<int4>(ws, lay.off_units);
+    int2 *tinfo = ws_ptr<int2>(ws, lay.off_tinfo);
+    uint32_t *slot = ws_ptr<uint32_t>(ws, lay.off_slot);
+    // the cost of a run of tiles, then its units and split-tile pieces (both below 2^32)
+    I c = 0, ctot;
+    for (int t = t0; t < t1; ++t) c += cost(unit_steps(t, a, lay, ws, spair)) + E;
+    const I C0 = block_excl_scan<256>(c, &ctot);
+    // ranges meeting a tile's cost; the last one starts inside the decode's share when
+    // the last cut lies past the steps: it gets no piece
+    auto pieces = [&](I C, I w, int &nr, int &np) {
+        const I r0 = range_of(C), r1 = range_of(C + w + E - 1);
+        nr = (int)(r1 - r0 + 1);
+        np = nr > 1 && cut(r1) >= C + w ? nr - 1 : nr;
+        return r0;
+    };
+    int64_t up = 0, uptot;
+    I C = C0;
+    for (int t = t0; t < t1; ++t) {
+        const I w = cost(unit_steps(t, a, lay, ws, spair));
+        int nr, np;
+        pieces(C, w, nr, np);
+        up += (int64_t)np << 32 | (np > 1 ? np : 0);
+        C += w + E;
+    }
+    const int64_t UP = block_excl_scan<256>(up, &uptot);
+    int64_t U = UP >> 32, P = UP & 0xFFFFFFFFll;
+    C = C0;
+    for (int t = t0; t < t1; ++t) {
+        const int4 n = unit_steps(t, a, lay, ws, spair);
+        const I w = cost(n);
+        int nr, np;
+        const I r0 = pieces(C, w, nr, np);
+        tinfo[t] = make_int2(np, np > 1 ? (int)P : -1);
+        for (int p = 0; p < nr; ++p) {
+            const I s0 = r0 + p;
+            const I b = p == 0 ? C : cut(s0), e = p == np - 1 ? C + w : cut(s0 + 1);
+            if (p < np)
+                units[U + p] = make_int4(t, (int)step_at(n, b - C), (int)step_at(n, e - C),
+                                         n.w * UNIT_PLAN + (np > 1 ? (int)(P + p) + 1 : 0));
+            // (a range starting inside the decode's share starts with the next tile's first unit)
+            if (cut(s0) == b) slot[s0] = (uint32_t)(U + p);
+        }
+        U += np;
+        if (np > 1) P += np;
+        C += w + E;
+    }
+    // ranges past the end of the work hold no unit
+    for (I s = (W > 0 ? range_of(W - 1) + 1 : 0) + tid; s <= slots; s += 256) slot[s] = (uint32_t)(uptot >> 32);
+}
+
+// The prep block: each pair's slot plan (the one with the largest prefix no longer than its
+// shortest row) and 32-slot groups, the flag of a call with more row lengths ending inside a
+// group than masked tables, and the work division
+__device__ void prep_block(const RChunkArgs &a, const Layout &lay, uint8_t *ws, int4 *spair) {
+    const int npairs = lay.MT / 2, NTW = lay.NT / 2, L_max = a.L_max, tid = threadIdx.x;
+    const int64_t W1 = lay.narrow ? RW1_NARROW : 1, W2 = lay.narrow ? RW2_NARROW : 1, W3 = lay.narrow ? RW3_NARROW : 1;
+    // the status words from the batch entries' records
+    int bad = 0, longest = 0;
+    for (int b = tid; b < a.batch; b += 256) {
+        const int4 r = ws_ptr<int4>(ws + (size_t)b * lay.stride_batchA, lay.off_pair)[npairs];
+        bad |= r.x;
+        longest = max(longest, r.y);
+    }
+    if (tid == 0) spair[0] = make_int4(0, 0, 0, 0);
+    __syncthreads();
+    if (bad != 0) atomicOr(&spair[0].x, bad);
+    if (longest > 0) atomicMax(&spair[0].y, longest);
+    __syncthreads();
+    if (tid == 0) {
+        uint32_t *status = ws_ptr<uint32_t>(ws, lay.off_status);
+        status[0] = (uint32_t)spair[0].x;
+        status[1] = (uint32_t)spair[0].y;
+    }
+    __syncthreads();
+    bool over = false;
+    int64_t w = 0, W;
+    for (int i = tid; i < a.batch * npairs; i += 256) {
+        const int b = i / npairs, tp = i % npairs;
+        int4 *pair = ws_ptr<int4>(ws + (size_t)b * lay.stride_batchA, lay.off_pair) + tp;
+        const int4 pi = *pair;      // {longest, shortest, distinct lengths, not multiples of 32}
+        const int k = plan_of(pi.y, lay.nplans, lay.pstep, L_max);
+        const int4 h = ws_ptr<int4>(ws, lay.off_plan)[k];
+        const int save = h.x - h.y, top = (int)round_up(h.z, 32);
+        // lengths that end inside a group (rows of L_max cycles end with the last group, whose
+        // slots past theirs are zero)
+        int nd = save % 32 != 0 ? pi.z : pi.w;
+        if (pi.x >= L_max && (save % 32 != 0 || L_max % 32 != 0)) --nd;
+        over = over || nd > lay.rslots;
+        const int4 ps = make_int4((slot_length(pi.x, save, top, L_max) + 31) / 32, k, save, top);
+        *pair = ps;
+        if (lay.vsplit) {
+            const int4 n = pair_steps(ps, b, tp, a, lay, ws);
+            const int64_t c = n.x * W1 + n.y * W2 + n.z * W3;
+            w += ((c > 0 ? c : 1) + 5 * W1) * NTW;
+            if (i < UNIT_PAIRS) spair[i] = n;
+        }
+    }
+    over = __syncthreads_or(over);
+    if (tid == 0) ws_ptr<uint32_t>(ws, lay.off_status)[2] = over ? 1u : 0u;
+    if (!lay.vsplit) return;
+    block_excl_scan<256>(w, &W);
+    // (2 T slots, the largest intermediate, is below 2 (W + slots))
+    if (W + lay.sk_slots < (1ll << 29)) units_division<int32_t>(a, lay, ws, spair, (int32_t)W);
+    else units_division<int64_t>(a, lay, ws, spair, W);
+}
+
+// Table blocks: the nt blocks share out the tables of the plans that some pair takes (which the
+// batch entries' records tell), an eighth of a table each time (one side's dword w of every byte):
+// a whole table of one side per block took 3 to 4 us each, behind a chain of three loads.
+__device__ void table_block(int u, const RChunkArgs &a, const Layout &lay, uint8_t *ws, uint32_t *sused) {
+    const int groups = lay.LBS / 32, tid = threadIdx.x;
+    uint64_t used;
+    if (a.batch == 1) {
+        const int4 r = ws_ptr<int4>(ws, lay.off_pair)[lay.MT / 2];
+        used = (uint64_t)(uint32_t)r.w << 32 | (uint32_t)r.z;
+    } else {
+        if (tid < 2) sused[tid] = 0u;
+        __syncthreads();
+        uint32_t lo = 0u, hi = 0u;
+        for (int b = tid; b < a.batch; b += 256) {
+            const int4 r = ws_ptr<int4>(ws + (size_t)b * lay.stride_batchA, lay.off_pair)[lay.MT / 2];
+            lo |= (uint32_t)r.z;
+            hi |= (uint32_t)r.w;
+        }
+        if (lo != 0u) atomicOr(&sused[0], lo);
+        if (hi != 0u) atomicOr(&sused[1], hi);
+        __syncthreads();
+        used = (uint64_t)sused[1] << 32 | sused[0];
+    }
+    const int per = groups * 8, jobs = __popcll(used) * per;
+    for (int job = u; job < jobs; job += a.nt) {
+        uint64_t m = used;
+        for (int i = job / per; i > 0; --i) m &= m - 1;
+        const int k = __ffsll((unsigned long long)m) - 1, e = job % per, G = e >> 3, side = (e >> 2) & 1, w = e & 3;
+        if (32 * G >= ws_ptr<int4>(ws, lay.off_plan)[k].z) continue;
+        const uint2 *src = ws_ptr<uint2>(ws, lay.off_pslots) + (size_t)k * lay.LBS + 32 * G + 8 * w;
+        uint2 slots[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) slots[j] = src[j];
+        ws_ptr<uint32_t>(ws, lay.off_rtab)[(((size_t)(k * groups + G) * 2 + side) * 256 + tid) * 4 + w] =
+            a.bip ? r_entry<true>(slots, side, tid) : r_entry<false>(slots, side, tid);
+    }
+}
+
 // Chunks of both operands, through LDS: a block takes 64 rows (of the tile order) x 8 chunks
 // (256 bytes of each row).  It reads them row by row, 16 lanes per row (coalesced along the
 // row), into LDS as [chunk][row][half], then writes each chunk's 64 rows x 32 bytes, which are
-// contiguous in the chunk layout.  Side and batch entry from blockIdx.z.
+// contiguous in the chunk layout.  The same launch holds the prep block and the tables.
 constexpr int RC_ROWS = 64, RC_CH = 8;
 constexpr int RC_CSTRIDE = RC_ROWS * 2 + 1;      // u4 per chunk in LDS (+1: banks shift by chunk)
-__global__ __launch_bounds__(256) void k_rchunks(RChunkArgs a, uint8_t *ws) {
-    if (blockIdx.z == (unsigned)(a.nb[0] + a.nb[1])) {
-        // the last slice of the grid builds the tables of every cycle group
-        u4 *tab = ws_ptr<u4>(ws, a.off_rtab);
-        const int nblk = gridDim.x * gridDim.y;
-        for (int e = (blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x; e < a.groups * 512; e += nblk * 256) {
-            const int G = e >> 9, side = (e >> 8) & 1, byte = e & 255;
-            const uint32_t *r = ws_ptr<uint32_t>(ws, a.off_r[side]) + RCH * G;
-            tab[e] = a.bip ? r_entry<true>(r, byte) : r_entry<false>(r, byte);
-        }
+__global__ __launch_bounds__(256) void k_rprep(RChunkArgs a, Layout lay, uint8_t *ws) {
+    __shared__ u4 sm[RC_CH * RC_CSTRIDE];     // (one region for the three kinds of block)
+    static_assert(UNIT_PAIRS * sizeof(int4) <= sizeof(sm), "the prep block's pairs fit");
+    if (blockIdx.x == 0) {
+        prep_block(a, lay, ws, reinterpret_cast<int4 *>(sm));
         return;
     }
-    __shared__ u4 sm[RC_CH * RC_CSTRIDE];
-    const int side = blockIdx.z >= (unsigned)a.nb[0];
-    const int b = side ? blockIdx.z - a.nb[0] : blockIdx.z;
-    const int r0 = blockIdx.x * RC_ROWS, c0 = blockIdx.y * RC_CH;
-    if (r0 >= a.rows_pad[side]) return;                 // (uniform over the block)
+    if ((int)blockIdx.x <= a.nt) {
+        table_block((int)blockIdx.x - 1, a, lay, ws, reinterpret_cast<uint32_t *>(sm));
+        return;
+    }
+    int u = (int)blockIdx.x - 1 - a.nt;
+    const int side = u >= a.na ? 1 : 0;
+    if (side) u -= a.na;
+    const int b = u / (a.gx[side] * a.gy);
+    u -= b * a.gx[side] * a.gy;
+    const int r0 = (u % a.gx[side]) * RC_ROWS, c0 = (u / a.gx[side]) * RC_CH;
     const int nc = min(RC_CH, a.KC - c0);
     uint8_t *wsb = ws + (size_t)b * a.stride_batch[side];
     const int tid = threadIdx.x, hl = tid & 15;         // hl = 2 * chunk + half
@@ -1718,9 +1954,8 @@ __global__ __launch_bounds__(256) void k_rchunks(RChunkArgs a, uint8_t *ws) {
     }
 }
 
-hipError_t launch_rchunks(const sc_gemm_desc &d, const Layout &lay, const int8_t *A, const int8_t *B,
-                          uint8_t *ws, hipStream_t st) {
-    if (lay.KC == 0) return hipSuccess;       // no chunk and no table is read
+hipError_t launch_rprep(const sc_gemm_desc &d, const Layout &lay, const int8_t *A, const int8_t *B,
+                        uint8_t *ws, hipStream_t st) {
     RChunkArgs a{};
     a.X[0] = A;
     a.X[1] = B;
@@ -1730,9 +1965,6 @@ hipError_t launch_rchunks(const sc_gemm_desc &d, const Layout &lay, const int8_t
     a.strideX[1] = d.strideB;
     a.rows[0] = d.M;
     a.rows[1] = d.N;
-    a.rows_pad[0] = lay.MT * BM;
-    // the 256 x 64 blocks read the first 64 rows of B's pair only
-    a.rows_pad[1] = lay.narrow ? 64 : lay.NT * BN;
     a.nb[0] = d.batch;
     a.nb[1] = lay.nbB;
     a.stride_batch[0] = lay.stride_batchA;
@@ -1744,15 +1976,21 @@ hipError_t launch_rchunks(const sc_gemm_desc &d, const Layout &lay, const int8_t
     a.KC = lay.KC;
     a.vec[0] = (reinterpret_cast<uintptr_t>(A) % 16 == 0) && d.lda % 16 == 0 && d.strideA % 16 == 0;
     a.vec[1] = (reinterpret_cast<uintptr_t>(B) % 16 == 0) && d.ldb % 16 == 0 && d.strideB % 16 == 0;
-    a.groups = lay.LBS / RCH;
     a.bip = d.polarity == SC_BIPOLAR_XNOR;
-    a.off_r[0] = lay.off_rA;
-    a.off_r[1] = lay.off_rB;
-    a.off_rtab = lay.off_rtab;
-    const int rows = a.rows_pad[0] > a.rows_pad[1] ? a.rows_pad[0] : a.rows_pad[1];
-    hipLaunchKernelGGL(k_rchunks, dim3((unsigned)((rows + RC_ROWS - 1) / RC_ROWS), (unsigned)((lay.KC + RC_CH - 1) / RC_CH),
-                                       (unsigned)(d.batch + lay.nbB + 1)),
-                       dim3(256), 0, st, a, ws);
+    a.L_max = d.L_max;
+    a.batch = d.batch;
+    // with K = 0 no chunk and no table is read
+    // (a table block for each eighth of two plans' tables, or of every plan's first)
+    const int groups = lay.LBS / RCH;
+    a.nt = lay.KC > 0 ? 8 * groups * (lay.nplans < 2 ? lay.nplans : 2) + 8 * lay.nplans : 0;
+    a.gx[0] = lay.MT * BM / RC_ROWS;
+    // the 256 x 64 blocks read the first 64 rows of B's pair only
+    a.gx[1] = (lay.narrow ? 64 : lay.NT * BN) / RC_ROWS;
+    a.gy = (lay.KC + RC_CH - 1) / RC_CH;
+    const int64_t na = (int64_t)d.batch * a.gx[0] * a.gy, nb = (int64_t)lay.nbB * a.gx[1] * a.gy;
+    if (1 + a.nt + na + nb > INT_MAX) return hipErrorInvalidValue;
+    a.na = (int)na;
+    hipLaunchKernelGGL(k_rprep, dim3((unsigned)(1 + a.nt + na + nb)), dim3(256), 0, st, a, lay, ws);
     return hipGetLastError();
 }
 
@@ -2160,7 +2398,7 @@ __device__ __forceinline__ void rgemm_body(const MGemmArgs &g, const Layout &lay
     for (int u = ub; u < ue; ++u) {
     // (the previous unit's epilogue is done with the LDS)
     if (u != ub) __syncthreads();
-    int tile, s = 0, S = 1, v = -1;
+    int tile, s = 0, S = 1, v = -1, plan = 0;
     int64_t ux0 = 0, ux1 = 0;
     bool split;
     if (lay.vsplit) {
@@ -2168,7 +2406,8 @@ __device__ __forceinline__ void rgemm_body(const MGemmArgs &g, const Layout &lay
         tile = e.x;
         ux0 = e.y;
         ux1 = e.z;
-        v = e.w;
+        v = e.w % UNIT_PLAN - 1;
+        plan = e.w / UNIT_PLAN;
         split = v >= 0;
     } else if (!q_unit(g, lay, ws, u, tile, s, S, v, split)) {
         return;
@@ -2215,7 +2454,9 @@ __device__ __forceinline__ void rgemm_body(const MGemmArgs &g, const Layout &lay
     // chunk data at once, so that their latency overlaps the loads of the length and the rows
     // below.  (A tile of rows of length 0 runs no step; its early loads read data that exist
     // and go unused.  The 256 x 64 blocks measured slower with it: compensator +1.5 %.)
-    const u4 *rtab = ws_ptr<u4>(ws, lay.off_rtab);
+    const int4 ps = ws_ptr<int4>(wsa, lay.off_pair)[tp];   // {groups, plan, slots saved, slots of L_max}
+    if (!lay.vsplit && lay.nplans > 1) plan = ps.y;   // (one plan: no wait for ps)
+    const u4 *rtab = ws_ptr<u4>(ws, lay.off_rtab) + (size_t)plan * (g.LBS / RCH) * 512;
     const int64_t xs = NARROW ? -1 : lay.vsplit ? ux0 : (S == 1 ? 0 : -1);
     u4 ent[512 / NT];
     RData<NB> cur, nxt;
@@ -2223,7 +2464,8 @@ __device__ __forceinline__ void rgemm_body(const MGemmArgs &g, const Layout &lay
         r_load_ent<NT>(ent, rtab + (size_t)(xs / q.KC) * 512, tid);
         r_load(q, (int)(xs % q.KC), cur);
     }
-    const int ngroups = (int)(round_up(ws_ptr<int32_t>(wsa, lay.off_tileL)[2 * tp], RCH) / RCH);
+    const int ngroups = ps.x;
+    auto slen = [&](int L) { return slot_length(L, ps.z, ps.w, g.L_max); };
 
     const int64_t nch = (int64_t)ngroups * g.KC;
     // the unit's chunk steps (a tile of rows of length 0 has none)
@@ -2243,7 +2485,7 @@ __device__ __forceinline__ void rgemm_body(const MGemmArgs &g, const Layout &lay
         if (tid < ngroups) rems[tid] = 0u;
         __syncthreads();
         const int pt = perm[tid], lt = Ls[tid];
-        const int Lt = pt >= 0 ? lt : 0;
+        const int Lt = pt >= 0 ? slen(lt) : 0;
         if (Lt % RCH != 0) atomicOr(&rems[Lt / RCH], 1u << (Lt % RCH));
         __syncthreads();
     }
@@ -2254,12 +2496,12 @@ __device__ __forceinline__ void rgemm_body(const MGemmArgs &g, const Layout &lay
     for (int i = 0; i < 4; ++i) {
         const int row = r_row0<SKIP>(rh, i) + i32;
         const int pr = perm[row], lr = Ls[row];
-        Lr[i] = pr >= 0 ? lr : INT_MAX;
+        Lr[i] = pr >= 0 ? slen(lr) : INT_MAX;
     }
     const int h0 = r_row0<SKIP>(rh, 0), h1 = r_row0<SKIP>(rh, 2), h01 = r_row0<SKIP>(rh, 1);
     const int p0 = perm[h0], l0 = Ls[h0], p1 = perm[h1], l1 = Ls[h1], p01 = perm[h01], l01 = Ls[h01];
-    const int Lh0 = wave_uniform(p0 >= 0 ? l0 : 0), Lh1 = wave_uniform(p1 >= 0 ? l1 : 0);
-    const int Lh01 = wave_uniform(p01 >= 0 ? l01 : 0);
+    const int Lh0 = wave_uniform(p0 >= 0 ? slen(l0) : 0), Lh1 = wave_uniform(p1 >= 0 ? slen(l1) : 0);
+    const int Lh01 = wave_uniform(p01 >= 0 ? slen(l01) : 0);
 
     const uint32_t lrep = 16u * (uint32_t)(lane & (RREP - 1));
     q.loB = lrep + 16u * RREP;
@@ -2469,6 +2711,7 @@ static MGemmArgs make_gemm_args(const sc_gemm_desc &d, const Layout &lay, const 
     g.S = lay.S;
     g.F = lay.F;
     g.KC = lay.KC;
+    g.L_max = d.L_max;
     g.sA = sA;
     g.sB = sB;
     g.strideSA = d.strideSA;

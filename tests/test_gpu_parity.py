@@ -692,3 +692,46 @@ def test_exact_past_the_bound(dev, oracle_mod, case, polarity):
     _compare(g, 0, rows, cols, out, cnt, oracle_mod, "past bound %s pol%d" % (case, polarity), rng=rng_kind)
     if polarity == 0:
         assert cnt[0, 0, 0] == K * L_max           # every XNOR is 1 (cycles and elements)
+
+
+# Slot plans of the int8-chunk GEMM: cycles below a prefix share slots, later cycles keep their
+# own, and a 256-row pair takes the plan of its shortest row.  Lengths at, one below and one
+# above the prefixes (multiples of 8 up to L_max = 256, of 16 at 512, of 1024 at 4096, and
+# L_max itself), pairs whose shortest row is 0, every int8 value on both sides (each class of
+# both sequences), L_max that is no multiple of 32, and classes with more cycles than a slot
+# holds (512 and 4096 cycles over 254 or 127 classes).
+PLANS = [
+    # M, N, L_max, lengths, polarity, seed
+    (520, 270, 128, "one", 0, 601),
+    (520, 270, 129, "one", 1, 602),
+    (300, 300, 256, "edges8", 0, 603),
+    (600, 48, 256, "edges8", 1, 604),       # 256 x 64 blocks
+    (600, 260, 250, "edges8", 1, 605),
+    (600, 260, 512, "edges16", 0, 606),
+    (600, 40, 512, "edges16", 1, 607),
+    (300, 260, 4096, "edges1024", 1, 608),
+    (300, 260, 33, "one", 0, 609),          # the shortest L_max with plans
+    (300, 40, 64, "below", 0, 610),         # every row one length short of L_max
+]
+
+
+@pytest.mark.parametrize("case", PLANS, ids=[str(c) for c in PLANS])
+def test_slot_plans(dev, oracle_mod, case):
+    M, N, L_max, kind, pol, seed = case
+    rng = np.random.default_rng(seed)
+    K = 256
+    g = W.random_gemm(rng, 1, M, N, K, L_max, pol, seed)
+    g.A[0] = np.stack([rng.permutation(256) for _ in range(M)]).astype(np.uint8).view(np.int8)
+    g.B[0] = np.stack([rng.permutation(256) for _ in range(N)]).astype(np.uint8).view(np.int8)
+    if kind in ("one", "below"):
+        g.L[:] = L_max - (kind == "below")
+    else:
+        step = int(kind[5:])
+        near = rng.integers(0, L_max // step + 2, M) * step + rng.integers(-1, 2, M)
+        g.L[0] = np.clip(near, 0, L_max)
+        g.L[0, :3] = (L_max, L_max - 1, 0)
+    _note("slot plans %s" % (case,))
+    hint = int(g.L.mean()) or 1
+    for h in {0, hint}:
+        out, cnt = _run(g, dev, L_hint=h)
+        _compare(g, 0, np.arange(M), np.arange(N), out, cnt, oracle_mod, "plans%s hint %d" % (case, h))
