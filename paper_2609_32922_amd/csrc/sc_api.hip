@@ -12,6 +12,67 @@ namespace scg {
 
 namespace {
 
+// Slots that L cycles merge into (means over 40 seeds, rows all of length L; see the slot plans)
+double mean_slots(double L, bool bipolar) {
+    static const double at[] = {0, 32, 64, 96, 128, 192, 256, 384, 512, 1024, 4096};
+    static const double bip[] = {0, 29, 52, 72, 88, 116, 140, 179, 212, 342, 1120};
+    static const double uni[] = {0, 26, 44, 58, 70, 90, 106, 138, 172, 304, 1072};
+    int k = 1;
+    while (k < 10 && L > at[k]) ++k;
+    const double *v = bipolar ? bip : uni, f = (L - at[k - 1]) / (at[k] - at[k - 1]);
+    return v[k - 1] + f * (v[k] - v[k - 1]);
+}
+
+// What a layout is chosen by: estimated times (us) of the int8-chunk GEMM.  A chunk step of a 256 x
+// 256 block (one per CU) takes 3.5, its first loads and decode 23 (10 for a part); one of a 64 x
+// 128 C block 1.55, 2.15, 4.05, 5.5 for C = 1, 2, 4, 5 while two run on the CU and 1.4, 1.55, 2.7,
+// 3.3 alone, its other costs 5 + 0.36 C and 1.7 a slot group; partial sums move at 5e6 bytes a us,
+// and the launch that adds them up takes 4.3.  (Fitted to 75 shapes, 14 divisions each: over them
+// the chosen division takes 1.005 times the best one's whole-call time on average, 1.18 at most.)
+struct WorkShape {
+    double batch, KC, gmean, gmax;   // 32-element chunks; 32-slot groups of the mean and the longest row
+    int M, N, cus, Smin;
+    bool one;                        // one row length
+};
+double est_parts(double pieces, double bytes) { return pieces * bytes * 2.0 / 5e6 + 4.3; }
+double est_wide(const WorkShape &w) {
+    const double tiles = w.batch * ((w.M + 255) / 256) * ((w.N + 255) / 256), n = w.KC * w.gmean, part = 256.0 * 256 * 4;
+    if (!w.one) return tiles * (23 + 3.5 * n) / w.cus + 13 + est_parts(2.0 * w.cus, part) * (tiles > w.cus ? 0.5 : 1.0);
+    double best = 1e30;
+    for (int S = w.Smin; S <= MAX_SPLIT && (S == w.Smin || n / S >= 2); S *= 2) {
+        const double t = S == 1 ? ceil(tiles / w.cus) * (23 + 3.5 * n)
+                                : ceil(tiles * S / w.cus) * (10 + 3.5 * n / S) + est_parts(tiles * S, part);
+        best = t < best ? t : best;
+    }
+    const double rest = fmod(tiles, w.cus);
+    if (w.Smin == 1 && tiles > w.cus && rest > 0) {
+        const double S = fmin(floor(w.cus / rest), MAX_SPLIT);
+        best = fmin(best, floor(tiles / w.cus) * (23 + 3.5 * n) + 10 + 3.5 * n / S + (S > 1 ? est_parts(rest * S, part / 2) : 7));
+    }
+    return best;
+}
+double est_tall(const WorkShape &w, int C, int S) {
+    const double step2 = C == 1 ? 1.55 : C == 2 ? 2.15 : C == 4 ? 4.05 : 5.5;
+    const double step1 = C == 1 ? 1.4 : C == 2 ? 1.55 : C == 4 ? 2.7 : 3.3;
+    const double units = w.batch * ((w.M + 63) / 64) * ((w.N + 128 * C - 1) / (128 * C)) * S;
+    const double n = w.KC * w.gmean / S, fixed = 5 + 0.36 * C + 1.7 * ceil(w.gmean / S), slots = 2.0 * w.cus;
+    const double two = fixed + n * step2, alone = fixed + n * step1;
+    double t;
+    if (w.one) {
+        const double rest = fmod(units, slots);
+        t = floor(units / slots) * two + (rest == 0 ? 0 : rest <= w.cus ? alone : two);
+    } else {
+        // (units go out longest first)
+        t = units <= w.cus ? 0 : units / slots * two + 0.58 * two;
+        t = fmax(t, fixed + w.KC * w.gmax / S * (units <= w.cus ? step1 : step2));
+    }
+    if (S > 1) t += est_parts(units, 64.0 * 128 * C * (w.KC * w.gmax / S <= P16_STEPS ? 2 : 4));
+    return t;
+}
+
+// fewest chunk steps of a part of a 64-row tile
+constexpr int TPART = 4;
+
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
 // checked size arithmetic: returns false on overflow of size_t
@@ -46,28 +107,80 @@ static int device_cus() {
     return n;
 }
 
-static bool layout_with(const sc_gemm_desc &d, int cus, bool plans, Layout *lay) {
+// How much of the workspace a layout may spend: everything; no slot plans; int8 chunks only where
+// the 128-row kernels could not take their operands as they are
+enum { LAY_FULL, LAY_ONE_PLAN, LAY_LEAST };
+
+static bool layout_with(const sc_gemm_desc &d, int cus, int spend, Layout *lay) {
     Layout l{};
     l.cus = cus > 0 ? cus : DEFAULT_CUS;
     l.KQP = (int)round_up((d.K + 3) / 4, 4);
     l.words_per_L = (int64_t)l.KQP * 64;
     l.MT = (d.M + BM - 1) / BM;
     l.NT = (d.N + BN - 1) / BN;
+    const bool lfsr = d.rng == SC_RNG_LFSR32;
+    const double Lmean = d.L_hint > 0 ? d.L_hint : d.L_max;
+    const int KC = (d.K + 31) / 32;
+    const bool one_length = Lmean >= d.L_max, long_tiles = (int64_t)KC * ((int64_t)(Lmean + 31) / 32) >= 16;
     // N <= 64 with comparator streams and M > 128: the int8-chunk GEMM in blocks of
     // 256 rows x 64 columns (the B side still laid out as one 256-row pair)
-    l.narrow = d.rng == SC_RNG_LFSR32 && d.N <= 64 && d.M > BM;
-    l.mbn = (l.NT > 1 || l.narrow) ? 2 * BN : BN;
-    l.NT = (int)round_up(l.NT, l.mbn / BN);
-    // N <= 128 (one B tile): every A plane would be used once, so the GEMM generates the
-    // fragments itself (comparator streams; operand offsets must fit 31 bits)
-    l.fused = l.mbn == BN && d.rng == SC_RNG_LFSR32 && fused_extent(d.M, d.lda, d.K) < INT_MAX - 4 &&
+    l.narrow = lfsr && d.N <= 64 && d.M > BM;
+    // comparator streams with few rows or columns, or short tiles with varying lengths
+    // (attention heads): the int8-chunk GEMM in blocks of 64 rows
+    const bool few = lfsr && !l.narrow && (d.M <= BM || d.N <= BN);
+    // few columns and no room for chunks of a long A: k_fgemm takes the operands as they are
+    // (operand offsets must fit 31 bits)
+    l.fused = few && spend == LAY_LEAST && d.N <= BN && fused_extent(d.M, d.lda, d.K) < INT_MAX - 4 &&
               fused_extent(d.N, d.ldb, d.K) < INT_MAX - 4;
-    l.mbm = (l.MT > 1 && l.mbn == 2 * BN) ? 2 * BM : BM;
+    // Blocks of 64 rows x 128 C columns in S parts where that is estimated to take the least time:
+    // few rows or columns, short tiles with varying lengths (attention heads), and shapes that
+    // 256 x 256 blocks pad or fill the chip unevenly with.  Measured (us, 256-row blocks against
+    // these): 48 x 768 x 3072 135 (128-row kernels, since gone) and 32; 197 x 768 x 3072 75 and 51;
+    // 400 x 768 x 768 67 and 38; 128 heads of 577 x 64 x 577 412 and 199; and 6304 x 768 x 3072 375
+    // and 429, 18464 x 1024 x 4096 2150 and 2280, where the 256-row blocks stay.
+    WorkShape w{};
+    w.batch = d.batch > 0 ? d.batch : 0;
+    w.KC = KC;
+    w.M = d.M;
+    w.N = d.N;
+    w.cus = l.cus;
+    w.one = one_length;
+    const bool bip = d.polarity == SC_BIPOLAR_XNOR;
+    w.gmean = ceil(mean_slots(Lmean, bip) / 32.0);
+    w.gmax = one_length ? w.gmean : (d.L_max + 31) / 32;
+    const int64_t rsteps = (int64_t)KC * ((d.L_max + 31) / 32);
+    w.Smin = 1;
+    while (rsteps > RSTEP_EXACT * w.Smin) w.Smin *= 2;
+    // (few rows or columns: any number of parts, for every K x L_max of at most 2^27 products in
+    // whole octets of cycles and 16-element steps)
+    if (few) w.Smin = (int)((rsteps + RSTEP_EXACT - 1) / RSTEP_EXACT);
+    if (few && round_up(d.L_max, MSTEP) * l.KQP * 4 > SC_KL_LIMIT) return false;
+    if (w.Smin < 1) w.Smin = 1;
+    int tallC = 0, tallS = 1;
+    if (lfsr && !l.narrow && !l.fused && (few || spend != LAY_LEAST)) {
+        double best = few ? 1e30 : est_wide(w);
+        for (int c : {1, 2, 4, 5})
+            for (int S = w.Smin; S <= (c == 5 ? 1 : w.Smin > MAX_SPLIT ? w.Smin : MAX_SPLIT); ++S) {
+                if (S > w.Smin && w.KC * w.gmean / S < TPART) break;
+                const double t = est_tall(w, c, S);
+                if (t < best) {
+                    best = t;
+                    tallC = c;
+                    tallS = S;
+                }
+            }
+    }
+    const bool tall = tallC > 0;
+    l.mbn = (l.NT > 1 || l.narrow || tall) && !l.fused ? 2 * BN : BN;
+    l.NT = (int)round_up(l.NT, l.mbn / BN);
+    l.mbm = ((l.MT > 1 && l.mbn == 2 * BN) || tall) ? 2 * BM : BM;
     if (l.mbm == 2 * BM) l.MT = (int)round_up(l.MT, 2);
-    // 256 x 256 blocks with comparator streams: fragments from int8 chunks and a table of
-    // each 32-cycle group, so the operands are read as bytes instead of fp4 planes
-    l.rgen = l.mbm == 2 * BM && d.rng == SC_RNG_LFSR32;
-    l.rslots = l.narrow ? 0 : RSLOTS;
+    // comparator streams: fragments from int8 chunks and a table of each slot group, so the
+    // operands are read as bytes instead of as fp4 planes
+    l.rgen = l.mbm == 2 * BM && lfsr;
+    l.tshift = tall ? 6 : 8;
+    l.rtiles = tall ? (d.M + TROWS - 1) / TROWS : l.MT / 2;
+    l.rslots = l.narrow || tall ? 0 : RSLOTS;
     l.KC = (d.K + 31) / 32;
     l.LBS = (int)round_up(d.L_max, LCH);
     l.nbB = (d.strideB == 0) ? 1 : d.batch;
@@ -87,15 +200,10 @@ static bool layout_with(const sc_gemm_desc &d, int cus, bool plans, Layout *lay)
     if (cbsg) off = align256(off + (size_t)(d.L_max + 1) * CA_COLS * 2);
     // Slot plans: while a tile's products sum to less than 2^24 in magnitude whatever slots hold
     // them (K x L_max; so every part is exact), and more than one group of 32 cycles exists.
-    // At most 32 plans past the first, and at most PLAN_GROUPS tables.  Short tiles with varying
-    // lengths (attention heads: K = 64) go without: their pairs hold rows from 94 to 453 cycles,
-    // so the prefixes are short against the longest row, and the wait for a tile's plan costs
-    // each of them more (ViT-L/14 Q.K^T 411 us without plans, 416 with).
-    const double Lmean = d.L_hint > 0 ? d.L_hint : d.L_max;
-    const bool one_length = Lmean >= d.L_max, long_tiles = (int64_t)l.KC * ((int64_t)(Lmean + 31) / 32) >= 16;
+    // At most 32 plans past the first, and at most PLAN_GROUPS tables.
     l.nplans = 1;
     l.pstep = LCH;
-    if (plans && l.rgen && (one_length || long_tiles) && l.LBS > 32 && (int64_t)l.KC * 32 * l.LBS < MFMA_EXACT) {
+    if (spend == LAY_FULL && l.rgen && l.LBS > 32 && (int64_t)l.KC * 32 * l.LBS < MFMA_EXACT) {
         const int n = PLAN_GROUPS / (l.LBS / 32) < 32 ? PLAN_GROUPS / (l.LBS / 32) : 32;
         l.pstep = (int)round_up((d.L_max + n - 1) / n, 8);
         l.nplans = 1 + (d.L_max + l.pstep - 1) / l.pstep;
@@ -119,7 +227,7 @@ static bool layout_with(const sc_gemm_desc &d, int cus, bool plans, Layout *lay)
     l.off_tileOff = a;
     if (!l.rgen) a = align256(a + (size_t)l.MT * 8);
     l.off_pair = a;
-    if (l.rgen) a = align256(a + (size_t)(l.MT / 2 + 1) * 16);
+    if (l.rgen) a = align256(a + (size_t)(l.rtiles + 1) * 16);
     l.off_Ap = a;
     // largest planes of one batch entry: every tile at L_max rounded up to an octet
     if (!mul_ok((size_t)l.MT * (size_t)l.words_per_L, (size_t)round_up(d.L_max, MSTEP) * 4, &sz))
@@ -159,11 +267,18 @@ static bool layout_with(const sc_gemm_desc &d, int cus, bool plans, Layout *lay)
     const int64_t per_unit = l.rgen ? 32 * 32 : l.fused ? 128 : 64;
     l.Smin = 1;
     while (l.Smin <= MAX_SPLIT && (units + l.Smin - 1) / l.Smin * per_unit > MFMA_EXACT) l.Smin *= 2;
-    if (l.Smin > MAX_SPLIT) return false;
+    if (few && tallC > 0) l.Smin = w.Smin;
+    else if (l.Smin > MAX_SPLIT) return false;
+
+    int64_t tiles = (int64_t)(d.batch > 0 ? d.batch : 0) * (l.MT / (l.mbm / BM)) * (l.NT / (l.mbn / BN));
+    l.tall = tallC;
+    if (tall) {
+        tiles = (int64_t)(d.batch > 0 ? d.batch : 0) * l.rtiles * (((int64_t)d.N + 128 * tallC - 1) / (128 * tallC));
+        if (tiles * MAX_SPLIT > INT_MAX) return false;
+    }
 
     // Division of the GEMM tiles into work units.
-    const bool quad = l.mbm == 2 * BM;
-    const int64_t tiles = (int64_t)(d.batch > 0 ? d.batch : 0) * (l.MT / (l.mbm / BM)) * (l.NT / (l.mbn / BN));
+    const bool quad = l.mbm == 2 * BM && !tall;
     // indivisible steps along the inner range per cycle (chunks of every 32-cycle group with rgen)
     const int kunits = l.rgen ? l.KC * (l.LBS / 32) : l.KQP / 2;
     const int smax = kunits > l.Smin ? kunits : l.Smin;
@@ -171,7 +286,9 @@ static bool layout_with(const sc_gemm_desc &d, int cus, bool plans, Layout *lay)
     const double tile_bytes = (double)l.mbm * (l.narrow ? 64 : l.mbn) * 4.0;
     l.S = l.Smin;
     l.F = 0;
-    if (quad && tiles > 0) {
+    if (tall) {
+        l.S = tallS;
+    } else if (quad && tiles > 0) {
         // 256 x 256 tiles, one block per CU, taking whole tiles or parts of tiles
         // (quad_split_time).  Candidates: every tile split s ways (F = 0), or whole tiles in
         // full rounds with the tiles of a last partial round split to fill one round.  Split
@@ -245,7 +362,7 @@ static bool layout_with(const sc_gemm_desc &d, int cus, bool plans, Layout *lay)
     // (Short tiles, a few chunk steps each, keep the division below: their pieces' partial sums
     // and their in-GEMM decodes would cost as much as the steps; ViT-L/14 Q.K^T heads with
     // K = 64 took 0.61 ms cut into ranges against 0.41 ms split alike.)
-    l.pcols = l.narrow ? 64 : l.mbn;
+    l.pcols = tall ? 128 * l.tall : l.narrow ? 64 : l.mbn;
     l.vsplit = quad && l.rgen && tiles > 0 && !l.q_one && long_tiles;
     l.off_units = off;
     int64_t pieces = quad ? (tiles - l.F) * (int64_t)l.S : tiles * (int64_t)l.S;
@@ -275,8 +392,9 @@ static bool layout_with(const sc_gemm_desc &d, int cus, bool plans, Layout *lay)
     // Parts of the int8-chunk GEMM's split tiles of at most P16_STEPS chunk steps store int16
     // partial counts (half the partial-sum traffic).  A part of S has at most ceil(steps / S)
     // of a tile's steps; with F = 0 the GEMM may lower S to Smin.
+    l.Sleast = tall || l.F > 0 ? l.S : l.Smin;
     if (l.rgen && !l.vsplit && l.S > 1) {
-        const int64_t smin = l.F > 0 ? l.S : l.Smin;
+        const int64_t smin = l.Sleast;
         const int64_t steps = (int64_t)l.KC * (l.LBS / 32);
         l.p16 = (steps + smin - 1) / smin <= P16_STEPS;
     }
@@ -284,7 +402,7 @@ static bool layout_with(const sc_gemm_desc &d, int cus, bool plans, Layout *lay)
     if (pieces > 0 && (l.S > 1 || l.vsplit)) {
         size_t partb;
         // every piece is [mbm rows][pcols columns] of int32 (int16 with p16)
-        if (!mul_ok((size_t)pieces, (size_t)l.mbm * (size_t)l.pcols * (l.p16 ? 2 : 4), &partb)) return false;
+        if (!mul_ok((size_t)pieces, (size_t)(tall ? TROWS : l.mbm) * (size_t)l.pcols * (l.p16 ? 2 : 4), &partb)) return false;
         off = align256(off + partb);
     }
 
@@ -302,12 +420,13 @@ static bool layout_with(const sc_gemm_desc &d, int cus, bool plans, Layout *lay)
 }
 
 bool make_layout(const sc_gemm_desc &d, int cus, Layout *lay) {
-    if (!layout_with(d, cus, true, lay)) return false;
-    // a call that fits sc_gemm_noalloc's array without the tables of the slot plans keeps fitting it
-    Layout one;
-    if (lay->nplans > 1 && lay->total > SC_NOALLOC_WORKSPACE_BYTES && layout_with(d, cus, false, &one) &&
-        one.total <= SC_NOALLOC_WORKSPACE_BYTES)
-        *lay = one;
+    if (!layout_with(d, cus, LAY_FULL, lay)) return false;
+    // a call that fits sc_gemm_noalloc's array without the tables of the slot plans, or without
+    // chunks of its operands, keeps fitting it
+    for (int spend = LAY_ONE_PLAN; lay->total > SC_NOALLOC_WORKSPACE_BYTES && spend <= LAY_LEAST; ++spend) {
+        Layout less;
+        if (layout_with(d, cus, spend, &less) && less.total <= SC_NOALLOC_WORKSPACE_BYTES) *lay = less;
+    }
     return true;
 }
 

@@ -49,8 +49,10 @@
 // (the same comparator boundaries) and 0x80 (-128) marking an element >= K or a padding
 // row.  The GEMM builds the fp4 fragments from them.
 //
-// N <= 128 with comparator streams (fused): no planes either; the GEMM builds its fragments
-// from the int8 rows themselves.
+// 64-row blocks (tall) read the same chunks, a row tile a quarter of a pair.
+//
+// N <= 128 with comparator streams and chunks that would not fit the array of sc_gemm_noalloc
+// (fused): no planes or chunks; the GEMM builds its fragments from the int8 rows themselves.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -112,6 +114,7 @@ constexpr int MAX_PLANS = 40;    // plans of a call (bits of the status words)
 constexpr int PLAN_GROUPS = 512; // most (plan, group) tables of a call, 8 KiB each
 constexpr int UNIT_PLAN = 1 << 24;   // a unit's partial index (below 2^22) and plan in one word
 
+constexpr int TROWS = 64;        // rows of a block of k_tgemm
 constexpr int OCH = 8;           // octets per block of the nibble-plane generator
 constexpr int RSLOTS = 4;        // int8-chunk GEMM: tables masked to a row length, per cycle group
 constexpr int64_t MFMA_EXACT = 1ll << 24;   // products one fp32 accumulator sums exactly
@@ -197,12 +200,15 @@ struct Layout {
     int nbB;           // batch entries of B planes (1 when B is broadcast)
     int KQP;           // element quads per octet, ceil(K/4) rounded up to 4
     int mbn;           // columns of B per GEMM block (256, or 128 when N <= 128)
-    int fused;         // N <= 128, comparator streams: the GEMM builds its fp4 fragments from
-                       // the int8 operands (no planes in the workspace)
+    int fused;         // N <= 128, comparator streams, long A: the GEMM builds its fp4 fragments from
+                       // the int8 operands (no planes or chunks in the workspace)
     int mbm;           // rows of A per GEMM block: 256 (row tiles taken in pairs that run at
                        // the pair's longest length; MT even) when mbn = 256 and MT > 1, else 128
     int rgen;          // 256-row GEMM with comparator streams: fragments built in the GEMM
                        // from int8 chunks and a per-group table (no planes)
+    int tall;          // rgen in blocks of 64 rows x 128 tall columns (k_tgemm): columns of 32 per wave,
+                       // 0 when the blocks have 256 rows
+    int tshift, rtiles;    // rgen: rows of a tile (256, or 64 with tall) as a shift, and row tiles
     int narrow;        // rgen with N <= 64: blocks of 256 rows x 64 columns
     int rslots;        // rgen: tables masked to a row length per cycle group (0 when narrow)
     int KC;            // 32-element chunks per row, ceil(K/32)
@@ -215,6 +221,7 @@ struct Layout {
     size_t off_Bp;
     size_t stride_batchB;          // bytes per B batch entry block
     int S;             // splits of the inner range per GEMM tile (1 = no split)
+    int Sleast;        // rgen: fewest parts that the tiles of a call with split tiles are run in
     int Smin;          // fewest splits that keep every part's fp32 sums exact (<= 2^24 products)
     int F;             // 256-row GEMM: tiles 0 .. F-1 run whole, tiles F.. in S parts each
     double q_perL, q_Lmean;   // 256-row GEMM split model: seconds per cycle of one tile, mean L

@@ -352,7 +352,7 @@ __device__ __forceinline__ void schedule_block(const int32_t *__restrict__ L, in
         // over pairs, then a scan; lengths that are not multiples of 32 in the upper half);
         // end = hstart[l - 1] (runs in order of decreasing length).  Up to 2048 pairs per pass.
         int4 *pair = ws_ptr<int4>(wsb, lay.off_pair);
-        const int npairs = lay.MT / 2;
+        const int npairs = lay.rtiles, sh8 = lay.tshift;      // (row tiles: 256 rows, or 64 with tall)
         for (int q0 = 0; q0 < npairs; q0 += 2048) {
             const int nq = min(npairs - q0, 2048);
             if (!one) {
@@ -362,7 +362,7 @@ __device__ __forceinline__ void schedule_block(const int32_t *__restrict__ L, in
                 for (int l = 1 + tid; l <= L_max; l += 1024) {
                     const int start = hstart[l], end = hstart[l - 1];
                     if (end <= start) continue;
-                    const int qa = max(start >> 8, q0), qb = min((end - 1) >> 8, q0 + nq - 1);
+                    const int qa = max(start >> sh8, q0), qb = min((end - 1) >> sh8, q0 + nq - 1);
                     if (qa > qb) continue;
                     const int add = l % 32 != 0 ? 0x10001 : 1;
                     atomicAdd(&dpair[qa - q0], add);
@@ -381,8 +381,8 @@ __device__ __forceinline__ void schedule_block(const int32_t *__restrict__ L, in
                     pc += tot;
                 }
                 if (q >= nq) continue;
-                const int p = (q0 + q) * 256;
-                const int hi = one ? lmin : length_at(p), lo = one ? lmin : length_at(min(p + 255, M - 1));
+                const int p = (q0 + q) << sh8;
+                const int hi = one ? lmin : length_at(p), lo = one ? lmin : length_at(min(p + (1 << sh8) - 1, M - 1));
                 pair[q0 + q] = make_int4(hi, lo, nd & 0xFFFF, nd >> 16);
                 const int k = plan_of(lo, lay.nplans, lay.pstep, L_max);
                 atomicOr(&sh.used[k >> 5], 1u << (k & 31));
@@ -537,7 +537,7 @@ __device__ __forceinline__ void plan_block(int k, const Layout &lay, int L_max, 
             if (tid == 0) sh.wmax = m;
         }
         __syncthreads();
-        const int64_t smin = lay.F > 0 ? lay.S : lay.Smin;
+        const int64_t smin = lay.Sleast;
         const int64_t steps = ((int64_t)lay.KC * ((S + L_max - p + 31) / 32) + smin - 1) / smin;
         if (steps * 32 * sh.wmax > 32767) S = p;
     }

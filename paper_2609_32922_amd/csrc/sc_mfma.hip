@@ -15,21 +15,23 @@
 // make_layout), so every partial sum is an exact integer, the int32 partial counts of a
 // split tile add exactly, and the count is independent of the summation order.
 //
-//   k_mplanes     nibble planes of A (sorted rows, per-row lengths) or B, one block per
+//   k_mplanes     nibble planes of A (sorted rows, per-row lengths) or B (C-BSG), one block per
 //                 128-row tile x 64 cycles x 64 elements; element parameters and an
-//                 8-cycle lookup table in LDS, 16-byte stores, 1 KB per wave; with
-//                 comparator streams (M <= 128) both operands in one launch (k_mplanes2)
-//   k_fgemm       N <= 128 with comparator streams where k_rgemm does not apply (M <= 128,
-//                 or 64 < N <= 128): 128x128 tile, the fp4 fragments of both operands built
+//                 8-cycle lookup table in LDS, 16-byte stores, 1 KB per wave
+//   k_fgemm       N <= 128 with comparator streams where chunks of A would not fit the array of
+//                 sc_gemm_noalloc: 128x128 tile, the fp4 fragments of both operands built
 //                 in LDS from the int8 rows (an 8-cycle table per octet indexed by the int8
-//                 byte), so no planes are written or read
-//   k_rchunks     int8 operands (A in the scheduler's row order) laid out in 32-element
+//                 byte), so no planes or chunks are written or read
+//   k_rprep       int8 operands (A in the scheduler's row order) laid out in 32-element
 //                 chunks per 256-row pair through LDS (rows read along, chunks written
-//                 contiguous), the input of k_rgemm; its last grid slice builds the table
-//                 entries of every 32-cycle group once per call
-//   k_rgemm       M > 128 and N > 128 (or N <= 64) with comparator streams: the tiles and
+//                 contiguous), the input of k_rgemm and k_tgemm; its first blocks divide the
+//                 work and build the tables of every slot group once per call
+//   k_tgemm       comparator streams: blocks of 64 rows x 128, 256, 512 or 640 columns, two per
+//                 CU, for attention heads, few rows or columns and calls that fill the chip
+//                 unevenly with 256 x 256 blocks; fragments as in k_rgemm
+//   k_rgemm       comparator streams, the other calls: the tiles and
 //                 division of k_qgemm, but every fp4 fragment is one LDS table read (a table
-//                 per 32-cycle group indexed by the int8 byte), so no planes exist and the
+//                 per 32-slot group indexed by the int8 byte), so no planes exist and the
 //                 loop has no stage buffers; rows ending inside a group read tables masked
 //                 to their length (a second variant masks every fragment when a row pair
 //                 holds too many such lengths); for N <= 64 blocks of 256 x 64, two per CU,
@@ -43,9 +45,9 @@
 //                 blocks, three LDS buffers of 4 slots (96 KB), memory instructions
 //                 interleaved one per MFMA.  Whole tiles in full rounds, the tiles of a last
 //                 partial round (or every tile, when row lengths vary) split along k.
-//   k_qgemm_reduce sums the partial counts of the split tiles of k_qgemm or k_rgemm and
+//   k_qgemm_reduce sums the partial counts of the split tiles of k_qgemm, k_rgemm or k_tgemm and
 //                 decodes (8-row blocks when few tiles are split, 32-row blocks otherwise)
-//   k_mgemm       the rest (M <= 128, or N <= 128 with C-BSG streams): 128x256 output
+//   k_mgemm       C-BSG streams with M <= 128 or N <= 128: 128x256 output
 //                 tile per 256-thread block (128x128 and 64x64 when N <= 128), 64x128 per
 //                 wave as 2x4 32x32 MFMA blocks, 4 slots (2 MFMA k-steps of 64) per LDS
 //                 stage, two LDS buffers (48 KB: two blocks per CU).  The 32x32x64 form
@@ -54,6 +56,8 @@
 //   k_mgemm_reduce sums the partial counts of split tiles and decodes
 #include <hip/hip_ext.h>
 #include <limits.h>
+
+#include <type_traits>
 
 #include "sc_internal.h"
 
@@ -285,21 +289,6 @@ __global__ __launch_bounds__(256) void k_mplanes(MPlaneArgs a, uint8_t *ws) {
     mplanes_block<POL, CBSG>(a, ws, sh, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
-// both sides in one launch (comparator streams): blocks [0, nA) are A's grid
-// (gxA x gy x batch), the rest B's (gxB x gy x nbB), so B's blocks fill A's last wave
-template <int POL>
-__global__ __launch_bounds__(256) void k_mplanes2(MPlaneArgs a, MPlaneArgs bb, int gxA, int gxB, int gy,
-                                                  int nA, uint8_t *ws) {
-    __shared__ MPlaneShared sh;
-    const int bid = blockIdx.x;
-    if (bid < nA) {
-        mplanes_block<POL, false>(a, ws, sh, bid % gxA, (bid / gxA) % gy, bid / (gxA * gy));
-    } else {
-        const int v = bid - nA;
-        mplanes_block<POL, false>(bb, ws, sh, v % gxB, (v / gxB) % gy, v / (gxB * gy));
-    }
-}
-
 template <bool CBSG>
 static void launch_mplanes_side(int polarity, dim3 grid, const MPlaneArgs &pa, uint8_t *ws,
                                 hipStream_t st) {
@@ -313,7 +302,6 @@ hipError_t launch_mplanes(const sc_gemm_desc &d, const Layout &lay, const int8_t
                           const int8_t *B, uint8_t *ws, hipStream_t st) {
     if (lay.KQP == 0) return hipSuccess;
     const unsigned qgroups = (unsigned)((lay.KQP + 15) / 16);
-    const bool cbsg = d.rng == SC_RNG_SOBOL8_CBSG;
     MPlaneArgs pa{};
     pa.X = A;
     pa.ld = d.lda;
@@ -334,11 +322,9 @@ hipError_t launch_mplanes(const sc_gemm_desc &d, const Layout &lay, const int8_t
     pa.off_r = lay.off_rA;
     pa.off_CA = lay.off_CA;
     const dim3 gA((unsigned)(lay.MT * pa.nchunk), qgroups, (unsigned)d.batch);
-    if (cbsg) {
-        launch_mplanes_side<true>(d.polarity, gA, pa, ws, st);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
+    launch_mplanes_side<true>(d.polarity, gA, pa, ws, st);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
 
     MPlaneArgs pb = pa;
     pb.X = B;
@@ -354,17 +340,7 @@ hipError_t launch_mplanes(const sc_gemm_desc &d, const Layout &lay, const int8_t
     pb.off_r = lay.off_rB;
     pb.off_CA = 0;
     const dim3 gB((unsigned)(lay.NT * pb.nchunk), qgroups, (unsigned)lay.nbB);
-    if (cbsg) {
-        launch_mplanes_side<false>(d.polarity, gB, pb, ws, st);
-        return hipGetLastError();
-    }
-    const int nA = (int)(gA.x * gA.y * gA.z), nB = (int)(gB.x * gB.y * gB.z);
-    if (d.polarity == SC_BIPOLAR_XNOR)
-        hipLaunchKernelGGL((k_mplanes2<SC_BIPOLAR_XNOR>), dim3((unsigned)(nA + nB)), dim3(256), 0, st, pa, pb,
-                           (int)gA.x, (int)gB.x, (int)qgroups, nA, ws);
-    else
-        hipLaunchKernelGGL((k_mplanes2<SC_UNIPOLAR_AND_SM>), dim3((unsigned)(nA + nB)), dim3(256), 0, st, pa, pb,
-                           (int)gA.x, (int)gB.x, (int)qgroups, nA, ws);
+    launch_mplanes_side<false>(d.polarity, gB, pb, ws, st);
     return hipGetLastError();
 }
 
@@ -859,8 +835,8 @@ static hipError_t launch_mgemm_tile(const MGemmArgs &g, const Layout &lay, uint8
 }
 
 // ----------------------------------------------------------------------------
-// Fused generation for N <= 128 (one B tile) with comparator streams: every A plane
-// would be written once and read once, so the block builds its fp4 fragments in LDS
+// Fused generation for N <= 128 (one B tile) with comparator streams and a long A (above): the
+// block builds its fp4 fragments in LDS
 // straight from the int8 operands instead.  Block = 128 rows of A x 128 columns of B,
 // four waves of 64 x 64 (2 x 2 MFMA blocks); a stage is 4 slots = 4 element quads of one
 // octet, so one 8-cycle lookup table per operand serves the whole stage.  Thread tid < 128
@@ -1451,20 +1427,21 @@ struct PQuad<true> {
         return make_int4((int)(int16_t)(x.x & 0xFFFF), x.x >> 16, (int)(int16_t)(x.y & 0xFFFF), x.y >> 16);
     }
 };
-template <bool BIP, int NK, int PC, bool P16>
+template <bool BIP, int NK, int PR, int PC, bool P16>
 __global__ __launch_bounds__(256) void k_qgemm_reduce(MGemmArgs g, Layout lay, uint8_t *ws) {
-    constexpr int QPT = 256 * PC / 4;         // quads per tile
+    constexpr bool TALL = PR == TROWS;        // tiles of k_tgemm, all split alike
+    constexpr int QPT = PR * PC / 4;          // quads per tile
     constexpr int BPT = QPT / (256 * NK);     // blocks per tile
     constexpr int CB = PC / 32;               // 32-column blocks of a piece
     constexpr int RPB = 32 * ((NK + CB - 1) / CB);   // rows a block's NK MFMA blocks span
-    static_assert(RPB <= 256, "rows of a block");
+    static_assert(RPB <= PR, "rows of a block");
     __shared__ int32_t srow[RPB], slen[RPB];
     __shared__ float sfac[RPB];
-    const int NTW = lay.NT / 2;
-    int F, SS;
-    q_division(g, lay, ws, F, SS);
+    const int NTW = TALL ? (g.N + PC - 1) / PC : lay.NT / 2;
+    int F = 0, SS = g.S;
+    if (!TALL) q_division(g, lay, ws, F, SS);
     const int tile = F + (int)(blockIdx.x / BPT), part = (int)(blockIdx.x % BPT);
-    if (tile >= g.batch * (lay.MT / 2) * NTW) return;
+    if (tile >= g.batch * lay.rtiles * NTW) return;
     size_t pbase = (size_t)(tile - F) * SS;
     if (lay.vsplit) {
         const int2 ti = ws_ptr<int2>(ws, lay.off_tinfo)[tile];
@@ -1492,8 +1469,8 @@ __global__ __launch_bounds__(256) void k_qgemm_reduce(MGemmArgs g, Layout lay, u
     uint8_t *wsa = ws + (size_t)b * lay.stride_batchA;
     if ((int)threadIdx.x < RPB) {
         const int r = rbase + (int)threadIdx.x;
-        const int i = ws_ptr<int32_t>(wsa, lay.off_perm)[tp * 256 + r];
-        const int Li = i >= 0 ? ws_ptr<int32_t>(wsa, lay.off_Ls)[tp * 256 + r] : 0;
+        const int i = ws_ptr<int32_t>(wsa, lay.off_perm)[tp * PR + r];
+        const int Li = i >= 0 ? ws_ptr<int32_t>(wsa, lay.off_Ls)[tp * PR + r] : 0;
         srow[threadIdx.x] = i;
         slen[threadIdx.x] = Li;
         sfac[threadIdx.x] = i >= 0 ? decode_factor(g.sA[(size_t)b * g.strideSA + i], Li) : 0.0f;
@@ -1528,7 +1505,7 @@ __global__ __launch_bounds__(256) void k_qgemm_reduce(MGemmArgs g, Layout lay, u
         const int qd = (part * 256 * NK + 256 * k + (int)threadIdx.x) >> 6;   // quad index of the wave
         const int blk = qd >> 2, qq = qd & 3;
         const int rl = (blk / CB) * 32 + 8 * qq + 4 * grp - rbase;   // first of its 4 rows, in the block
-        const int j = tw * 256 + (blk % CB) * 32 + i32;
+        const int j = tw * (PC == 64 ? 256 : PC) + (blk % CB) * 32 + i32;
         if (j >= g.N) continue;
         const float sBj = sBb[j];
         const int32_t P[4] = {sum[k].x, sum[k].y, sum[k].z, sum[k].w};
@@ -1546,16 +1523,23 @@ __global__ __launch_bounds__(256) void k_qgemm_reduce(MGemmArgs g, Layout lay, u
 
 template <bool BIP, bool P16>
 static void launch_qreduce_p(const MGemmArgs &g, const Layout &lay, uint8_t *ws, unsigned tail, hipStream_t st) {
-    if (lay.pcols == 64) {
-        if (tail * 16u < 1024u)
-            gemm_launch((k_qgemm_reduce<BIP, 1, 64, P16>), dim3(tail * 16u), dim3(256), st, true, g, lay, ws);
+    if (lay.tall) {
+        if (lay.tall == 1)
+            gemm_launch((k_qgemm_reduce<BIP, 1, TROWS, 128, P16>), dim3(tail * 8u), dim3(256), st, true, g, lay, ws);
+        else if (lay.tall == 2)
+            gemm_launch((k_qgemm_reduce<BIP, 1, TROWS, 256, P16>), dim3(tail * 16u), dim3(256), st, true, g, lay, ws);
         else
-            gemm_launch((k_qgemm_reduce<BIP, 4, 64, P16>), dim3(tail * 4u), dim3(256), st, true, g, lay, ws);
+            gemm_launch((k_qgemm_reduce<BIP, 1, TROWS, 512, P16>), dim3(tail * 32u), dim3(256), st, true, g, lay, ws);
+    } else if (lay.pcols == 64) {
+        if (tail * 16u < 1024u)
+            gemm_launch((k_qgemm_reduce<BIP, 1, 256, 64, P16>), dim3(tail * 16u), dim3(256), st, true, g, lay, ws);
+        else
+            gemm_launch((k_qgemm_reduce<BIP, 4, 256, 64, P16>), dim3(tail * 4u), dim3(256), st, true, g, lay, ws);
     } else {
         if (tail * 8u < 1024u)
-            gemm_launch((k_qgemm_reduce<BIP, 2, 256, P16>), dim3(tail * 32u), dim3(256), st, true, g, lay, ws);
+            gemm_launch((k_qgemm_reduce<BIP, 2, 256, 256, P16>), dim3(tail * 32u), dim3(256), st, true, g, lay, ws);
         else
-            gemm_launch((k_qgemm_reduce<BIP, 8, 256, P16>), dim3(tail * 8u), dim3(256), st, true, g, lay, ws);
+            gemm_launch((k_qgemm_reduce<BIP, 8, 256, 256, P16>), dim3(tail * 8u), dim3(256), st, true, g, lay, ws);
     }
 }
 template <bool BIP>
@@ -1821,7 +1805,7 @@ __device__ void units_division(const RChunkArgs &a, const Layout &lay, uint8_t *
 // shortest row) and 32-slot groups, the flag of a call with more row lengths ending inside a
 // group than masked tables, and the work division
 __device__ void prep_block(const RChunkArgs &a, const Layout &lay, uint8_t *ws, int4 *spair) {
-    const int npairs = lay.MT / 2, NTW = lay.NT / 2, L_max = a.L_max, tid = threadIdx.x;
+    const int npairs = lay.rtiles, NTW = lay.NT / 2, L_max = a.L_max, tid = threadIdx.x;
     const int64_t W1 = lay.narrow ? RW1_NARROW : 1, W2 = lay.narrow ? RW2_NARROW : 1, W3 = lay.narrow ? RW3_NARROW : 1;
     // the status words from the batch entries' records
     int bad = 0, longest = 0;
@@ -1880,14 +1864,14 @@ __device__ void table_block(int u, const RChunkArgs &a, const Layout &lay, uint8
     const int groups = lay.LBS / 32, tid = threadIdx.x;
     uint64_t used;
     if (a.batch == 1) {
-        const int4 r = ws_ptr<int4>(ws, lay.off_pair)[lay.MT / 2];
+        const int4 r = ws_ptr<int4>(ws, lay.off_pair)[lay.rtiles];
         used = (uint64_t)(uint32_t)r.w << 32 | (uint32_t)r.z;
     } else {
         if (tid < 2) sused[tid] = 0u;
         __syncthreads();
         uint32_t lo = 0u, hi = 0u;
         for (int b = tid; b < a.batch; b += 256) {
-            const int4 r = ws_ptr<int4>(ws + (size_t)b * lay.stride_batchA, lay.off_pair)[lay.MT / 2];
+            const int4 r = ws_ptr<int4>(ws + (size_t)b * lay.stride_batchA, lay.off_pair)[lay.rtiles];
             lo |= (uint32_t)r.z;
             hi |= (uint32_t)r.w;
         }
@@ -1983,9 +1967,10 @@ hipError_t launch_rprep(const sc_gemm_desc &d, const Layout &lay, const int8_t *
     // (a table block for each eighth of two plans' tables, or of every plan's first)
     const int groups = lay.LBS / RCH;
     a.nt = lay.KC > 0 ? 8 * groups * (lay.nplans < 2 ? lay.nplans : 2) + 8 * lay.nplans : 0;
-    a.gx[0] = lay.MT * BM / RC_ROWS;
-    // the 256 x 64 blocks read the first 64 rows of B's pair only
-    a.gx[1] = (lay.narrow ? 64 : lay.NT * BN) / RC_ROWS;
+    // (the 64-row blocks of A read their own rows only; the 256 x 64 blocks the first 64 rows of
+    // B's pair, the 64-row blocks no column past the last 32 with one in range)
+    a.gx[0] = lay.tall ? lay.rtiles : lay.MT * BM / RC_ROWS;
+    a.gx[1] = lay.narrow ? 1 : lay.tall ? (d.N + RC_ROWS - 1) / RC_ROWS : lay.NT * BN / RC_ROWS;
     a.gy = (lay.KC + RC_CH - 1) / RC_CH;
     const int64_t na = (int64_t)d.batch * a.gx[0] * a.gy, nb = (int64_t)lay.nbB * a.gx[1] * a.gy;
     if (1 + a.nt + na + nb > INT_MAX) return hipErrorInvalidValue;
@@ -2690,9 +2675,276 @@ static hipError_t launch_rgemm(const MGemmArgs &g, const Layout &lay, uint8_t *w
     return lay.narrow ? launch_rgemm_w<BIP, true>(g, lay, ws, st) : launch_rgemm_w<BIP, false>(g, lay, ws, st);
 }
 
+// ----------------------------------------------------------------------------
+// 64-row tiles of the int8-chunk GEMM
+// ----------------------------------------------------------------------------
+// For attention heads (short K, row lengths from 8 to 512 within a head) and calls with few rows
+// or columns.  A block takes 64 sorted rows x 128 C columns, two blocks per CU: wave w all 64 rows
+// (2 MFMA row blocks) x columns 32 C w .. (C column blocks), every k-step.  Bounds: MFMA, then
+// LDS reads (2 + C table reads per 2 C MFMAs, a read 8 LDS clocks per CU: 70 % of the MFMA time at
+// C = 5).  64 rows because a tile runs to its longest row and merges slots below its shortest:
+// on ViT-L/14 Q.K^T (577 rows a head) 256-row pairs issue 2.67 times the call's bit products, 64-row
+// tiles 1.39 times (1.2 with the phase in which only rows 0 .. 31 still run), and 577 columns fill
+// 640, not 768.  Two blocks per CU hide each other's table fills, first loads and decodes.
+template <int C>
+struct TData {
+    u2 a[2], b[C];                 // half a chunk: 8 elements of the lane's 2 A rows and C B columns
+};
+template <int C>
+struct TSrc {
+    __amdgpu_buffer_rsrc_t a, b;   // the pair's A chunks; the B chunks from the wave's first pair on
+    int voff;                      // the lane's row and half within a 32-row block of a chunk
+    int aoff, boff[C];             // byte offsets of A's rows and the wave's column blocks
+    uint32_t loA, loB;             // table columns (copy) of A and of B
+    const char *lut;
+    int KC;
+};
+template <int C>
+__device__ __forceinline__ void t_load(const TSrc<C> &q, int h, TData<C> &d) {
+    const int off = (h >> 1) * 256 * RCH + (h & 1) * 8;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) d.a[i] = __builtin_amdgcn_raw_buffer_load_b64(q.a, q.voff, off + q.aoff + i * 32 * RCH, 0);
+#pragma unroll
+    for (int c = 0; c < C; ++c) d.b[c] = __builtin_amdgcn_raw_buffer_load_b64(q.b, q.voff, off + q.boff[c], 0);
+}
+// the table row of element e (0..7) of a lane's half chunk
+__device__ __forceinline__ u4 t_look(const char *lut, u2 v, int e, uint32_t lo) {
+    return *reinterpret_cast<const u4 *>(lut + __builtin_amdgcn_perm(v[e >> 2], lo, 0x0C020000u | ((4u + (e & 3)) << 8)));
+}
+template <int NA, int C>
+struct TFrags {
+    u4 a[2][NA], b[4];
+};
+// the reads that the first k-step of a group needs: its A fragments and two B fragments
+template <int NA, int C>
+__device__ __forceinline__ void t_first(const TSrc<C> &q, const TData<C> &d, TFrags<NA, C> &f) {
+#pragma unroll
+    for (int i = 0; i < NA; ++i) f.a[0][i] = t_look(q.lut, d.a[i], 0, q.loA);
+#pragma unroll
+    for (int n = 0; n < 2; ++n) f.b[n] = t_look(q.lut, d.b[n % C], n / C, q.loB);
+}
+// The 8 k-steps of a half chunk, NA (1 or 2) row blocks running.  On entry and exit f holds the
+// next k-step's A fragments and two B fragments; a B fragment is read two column blocks ahead (four
+// registers sets in turn, so that C = 5 fits 256 registers), the next k-step's A fragments with
+// the first column blocks.
+template <int NA, int C>
+__device__ __forceinline__ void t_half(const TSrc<C> &q, const TData<C> &d, const TData<C> &nx, const u4 (&m)[2],
+                                       v16f (&acc)[2][C], TFrags<NA, C> &f) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        u4 fa[NA];
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            fa[i] = f.a[e & 1][i] & m[i];
+            f.a[(e + 1) & 1][i] = t_look(q.lut, e < 7 ? d.a[i] : nx.a[i], (e + 1) & 7, q.loA);
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int n = e * C + c, e2 = (n + 2) / C, c2 = (n + 2) % C;
+            f.b[(n + 2) & 3] = t_look(q.lut, e2 < 8 ? d.b[c2] : nx.b[c2], e2 & 7, q.loB);
+#pragma unroll
+            for (int i = 0; i < NA; ++i)
+                acc[i][c] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(frag(fa[i]), frag(f.b[n & 3]), acc[i][c],
+                                                                            4, 4, 0, 127, 0, 127);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+// half chunks of loads in flight past the current one: a half chunk of C = 1 is 16 MFMAs, 0.2 us
+template <int C>
+struct TAhead {
+    static constexpr int N = C >= 4 ? 1 : 3;
+};
+// half chunks h .. he-1 of a group, then on to half 0 of the next
+template <int NA, int C>
+__device__ __forceinline__ void t_group(const TSrc<C> &q, int h, int he, TData<C> (&d)[TAhead<C>::N + 1],
+                                        const u4 (&m)[2], v16f (&acc)[2][C]) {
+    constexpr int AH = TAhead<C>::N;
+    TFrags<NA, C> f;
+    t_first<NA, C>(q, d[0], f);
+    for (; h < he; ++h) {
+        int x = h + AH;
+        while (x >= 2 * q.KC) x -= 2 * q.KC;
+        t_load<C>(q, x, d[AH]);
+        t_half<NA, C>(q, d[0], d[1], m, acc, f);
+#pragma unroll
+        for (int k = 0; k < AH; ++k) d[k] = d[k + 1];
+    }
+}
+
+struct TLds {
+    u4 lut[256 * 16];
+    int32_t row[TROWS], len[TROWS];
+    float f[TROWS];
+};
+
+// One unit: part s of S of the chunk steps of tile `tile` (row tile rt of batch entry b x column tile
+// tw; the row tiles with the longest rows first), decoded here when S = 1, else stored as a partial
+// sum.  Rows ending inside a group are masked in the fragments.
+template <bool BIP, int C, bool SPLIT>
+__global__ __launch_bounds__(256, 2) void k_tgemm(MGemmArgs g, Layout lay, uint8_t *ws) {
+    constexpr int NT = 256, W = 128 * C, AH = TAhead<C>::N;
+    __shared__ TLds sh;
+    const int S = SPLIT ? g.S : 1, s = SPLIT ? (int)blockIdx.x % S : 0, tile = (int)blockIdx.x / S;
+    const int NTW = (g.N + W - 1) / W, tw = tile % NTW, tb = tile / NTW;
+    const int b = tb % g.batch, rt = tb / g.batch, bB = g.nbB == 1 ? 0 : b;
+    const int tid = threadIdx.x, lane = tid & 63, w = wave_uniform(tid >> 6), grp = lane >> 5, i32 = lane & 31;
+    uint8_t *wsa = ws + (size_t)b * lay.stride_batchA, *wsbB = ws + (size_t)bB * lay.stride_batchB;
+    const int4 ps = ws_ptr<int4>(wsa, lay.off_pair)[rt];   // {groups, plan, slots saved, slots of L_max}
+    const int32_t *perm = ws_ptr<int32_t>(wsa, lay.off_perm) + rt * TROWS;
+    const int32_t *Ls = ws_ptr<int32_t>(wsa, lay.off_Ls) + rt * TROWS;
+    const size_t pairb = (size_t)g.KC * 256 * RCH;
+    const int col0 = tw * W + 32 * C * w;                  // the wave's first column
+    const bool act = col0 < g.N;                           // (else it only takes part in the table fills)
+    TSrc<C> q;
+    q.a = __builtin_amdgcn_make_buffer_rsrc(ws_ptr<uint8_t>(wsa, lay.off_Ap) + (size_t)(rt >> 2) * pairb, 0, (int)pairb,
+                                            0x00020000);
+    // (the wave's columns lie in its first 256-row pair of B or the next one; a block of columns past
+    // the last pair reads the first block instead and goes unstored)
+    const int p0 = act ? col0 / 256 : 0, np = lay.NT / 2 - p0 > 1 ? 2 : 1;
+    q.b = __builtin_amdgcn_make_buffer_rsrc(ws_ptr<uint8_t>(wsbB, lay.off_Bp) + (size_t)p0 * pairb, 0, (int)(np * pairb),
+                                            0x00020000);
+    q.voff = i32 * RCH + grp * 16;
+    q.aoff = (rt & 3) * TROWS * RCH;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        const int col = act && col0 + 32 * c < g.N ? col0 + 32 * c : p0 * 256;
+        q.boff[c] = wave_uniform((int)((col / 256 - p0) * pairb) + col % 256 * RCH);
+    }
+    q.KC = g.KC > 0 ? g.KC : 1;
+    const uint32_t lrep = 16u * (uint32_t)(lane & (RREP - 1));
+    q.loA = lrep;
+    q.loB = lrep + 16u * RREP;
+    q.lut = reinterpret_cast<const char *>(sh.lut);
+    TData<C> d[AH + 1];
+    auto first_loads = [&](int c0) {
+#pragma unroll
+        for (int k = 0; k < AH; ++k) {
+            int h = 2 * c0 + k;
+            while (h >= 2 * q.KC) h -= 2 * q.KC;
+            t_load<C>(q, h, d[k]);
+        }
+    };
+    if (!SPLIT && g.KC > 0) first_loads(0);
+    // what the decode needs of each row
+    if (!SPLIT && tid < TROWS) {
+        const int i = perm[tid], L = i >= 0 ? Ls[tid] : 0;
+        sh.row[tid] = i;
+        sh.len[tid] = L;
+        sh.f[tid] = i >= 0 ? decode_factor(g.sA[(size_t)b * g.strideSA + i], L) : 0.0f;
+    }
+    const u4 *rtab = ws_ptr<u4>(ws, lay.off_rtab) + (size_t)ps.y * (g.LBS / RCH) * 512;
+    const int64_t nch = (int64_t)ps.x * g.KC, x0 = (int64_t)s * nch / S, x1 = (int64_t)(s + 1) * nch / S;
+    u4 ent[512 / NT];
+    if (x0 < x1) {
+        r_load_ent<NT>(ent, rtab + (size_t)(x0 / g.KC) * 512, tid);
+        if (SPLIT) first_loads((int)(x0 % g.KC));
+    }
+    int Lr[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int pr = perm[32 * i + i32], lr = Ls[32 * i + i32];
+        Lr[i] = pr >= 0 ? slot_length(lr, ps.z, ps.w, g.L_max) : 0;
+    }
+    // slots of the longest row of rows 32 .. 63 (the first of them, rows being sorted)
+    const int L1 = __builtin_amdgcn_readlane(Lr[1], 0);
+
+    v16f acc[2][C];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int c = 0; c < C; ++c) acc[i][c] = v16f{};
+    // groups in which both row blocks run, then those of rows 0 .. 31 alone
+    int64_t x = x0;
+    auto groups = [&](auto na) {
+        constexpr int NA = decltype(na)::value;
+        for (; x < x1;) {
+            const int G = (int)(x / g.KC);
+            if (NA == 2 && L1 <= RCH * G) break;
+            const int64_t xe = min(x1, (int64_t)(G + 1) * g.KC);
+            __syncthreads();      // every read of the previous group's table is done
+            r_fill_lut<NT>(sh.lut, ent, tid, 0u);
+            if (xe < x1) r_load_ent<NT>(ent, rtab + (size_t)(G + 1) * 512, tid);
+            __syncthreads();
+            if (act) {
+                u4 m[2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) m[i] = r_len_mask(Lr[i], G);
+                t_group<NA, C>(q, (int)(2 * (x - (int64_t)G * g.KC)), (int)(2 * (xe - (int64_t)G * g.KC)), d, m, acc);
+            }
+            x = xe;
+        }
+    };
+    groups(std::integral_constant<int, 2>{});
+    groups(std::integral_constant<int, 1>{});
+
+    if (SPLIT) {
+        if (!act) return;
+        const size_t bytes = (size_t)TROWS * W * (lay.p16 ? 2 : 4);
+        const __amdgpu_buffer_rsrc_t pr = __builtin_amdgcn_make_buffer_rsrc(
+            ws_ptr<uint8_t>(ws, lay.off_part) + ((size_t)tile * S + s) * bytes, 0, (int)bytes, 0x00020000);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                if (lay.p16) store_block16<W>(acc[i][c], pr, lane, i, C * w + c);
+                else store_block<W>(acc[i][c], pr, lane, i, C * w + c);
+            }
+        return;
+    }
+    __syncthreads();
+    if (!act) return;
+    // a store instruction writes 32 adjacent columns of two rows, straight from the accumulators
+    float sBj[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        const int j = col0 + 32 * c + i32;
+        sBj[c] = j < g.N ? g.sB[(size_t)b * g.strideSB + j] : 0.0f;
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int r = 32 * i + 8 * (e >> 2) + 4 * grp + (e & 3);
+            const int row = sh.row[r], L = sh.len[r];
+            const float f = sh.f[r];
+            if (row < 0) continue;
+            const size_t off = (size_t)b * g.strideO + (size_t)row * g.ldo + col0 + i32;
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                if (col0 + 32 * c + i32 >= g.N) continue;
+                const float P = acc[i][c][e];
+                g.out[off + 32 * c] = (P * f) * sBj[c];
+                if (g.counts) g.counts[off + 32 * c] = L > 0 ? (BIP ? (g.K * L + (int)P) / 2 : (int)P) : 0;
+            }
+        }
+}
+
+template <bool BIP, int C>
+static hipError_t launch_tgemm_c(const MGemmArgs &g, const Layout &lay, uint8_t *ws, hipStream_t st) {
+    const unsigned tiles = (unsigned)(g.batch * lay.rtiles) * (unsigned)((g.N + 128 * C - 1) / (128 * C));
+    if constexpr (C < 5) {
+        if (g.S > 1) {
+            gemm_launch((k_tgemm<BIP, C, true>), dim3(tiles * (unsigned)g.S), dim3(256), st, false, g, lay, ws);
+            const hipError_t e = hipGetLastError();
+            return e != hipSuccess ? e : launch_qreduce<BIP>(g, lay, ws, tiles, st);
+        }
+    }
+    gemm_launch((k_tgemm<BIP, C, false>), dim3(tiles), dim3(256), st, true, g, lay, ws);
+    return hipGetLastError();
+}
+template <bool BIP>
+static hipError_t launch_tgemm(const MGemmArgs &g, const Layout &lay, uint8_t *ws, hipStream_t st) {
+    return lay.tall == 5   ? launch_tgemm_c<BIP, 5>(g, lay, ws, st)
+           : lay.tall == 4 ? launch_tgemm_c<BIP, 4>(g, lay, ws, st)
+           : lay.tall == 2 ? launch_tgemm_c<BIP, 2>(g, lay, ws, st)
+                           : launch_tgemm_c<BIP, 1>(g, lay, ws, st);
+}
+
 template <bool BIP>
 static hipError_t launch_mgemm_pol(const MGemmArgs &g, const Layout &lay, uint8_t *ws,
                                    hipStream_t st) {
+    if (lay.tall) return launch_tgemm<BIP>(g, lay, ws, st);
     if (lay.mbm == 256) return lay.rgen ? launch_rgemm<BIP>(g, lay, ws, st) : launch_qgemm<BIP>(g, lay, ws, st);
     if (lay.mbn == 256) return launch_mgemm_tile<BIP, 256>(g, lay, ws, st);
     return launch_mgemm_tile<BIP, 128>(g, lay, ws, st);

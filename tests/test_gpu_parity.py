@@ -735,3 +735,67 @@ def test_slot_plans(dev, oracle_mod, case):
     for h in {0, hint}:
         out, cnt = _run(g, dev, L_hint=h)
         _compare(g, 0, np.arange(M), np.arange(N), out, cnt, oracle_mod, "plans%s hint %d" % (case, h))
+
+
+# 64-row tiles of the int8-chunk GEMM: blocks of 64 rows x 128 C columns.  The shapes take C = 1, 2, 4
+# and 5, whole tiles and parts (int16 and int32 partial counts), last row tiles of 1 and of 64
+# rows, columns ending inside a 32-column block, in a wave's first block and with waves past N,
+# one and several chunks of K, lengths that end rows 32.. of a tile early, broadcast B, M = 1.
+TALL = [
+    # batch, M, N, K, L_max, lengths, polarity, broadcast_B, seed
+    (1, 64, 64, 256, 64, "uniform", 0, False, 701),     # C = 1 in 4 parts, int16
+    (1, 65, 130, 33, 70, "random", 0, False, 703),      # C = 1 whole
+    (1, 96, 700, 512, 128, "uniform", 0, False, 705),   # C = 1 in 8 parts
+    (1, 1, 3, 1000, 300, "uniform", 1, False, 707),
+    (20, 700, 600, 33, 96, "skew", 1, False, 709),      # C = 2
+    (1, 1025, 2000, 640, 128, "skew", 0, False, 711),   # C = 2 in parts
+    (1, 900, 3000, 100, 64, "uniform", 1, False, 713),
+    (1, 900, 3000, 900, 64, "uniform", 0, False, 715),  # C = 4 in parts
+    (60, 140, 620, 40, 64, "random", 0, True, 717),     # C = 5
+    (40, 129, 577, 64, 512, "skew", 0, False, 719),
+    (3, 130, 129, 0, 40, "random", 1, False, 721),      # K = 0
+    (1, 100, 100, 40032, 3352, "uniform", 0, False, 723),   # 9 parts (exactness)
+]
+
+
+@pytest.mark.parametrize("case", TALL, ids=[str(c) for c in TALL])
+def test_row_tiles_of_64(dev, oracle_mod, case):
+    batch, M, N, K, L_max, kind, pol, bcast, seed = case
+    rng = np.random.default_rng(seed)
+    g = W.random_gemm(rng, batch, M, N, K, L_max, pol, seed, broadcast_B=bcast)
+    if kind == "uniform":
+        g.L[:] = L_max
+    elif kind == "skew":
+        g.L = np.maximum(0, L_max * rng.random(g.L.shape) ** 4).astype(np.int32)
+        g.L[:, 0] = L_max
+    _note("64-row tiles %s" % (case,))
+    big = K > 10000
+    for hint in {0, 0 if kind == "uniform" else int(g.L.mean()) or 1}:
+        out, cnt = _run(g, dev, L_hint=hint)
+        for b in sorted({0, batch // 2, batch - 1}):
+            rows = np.array([0, 63, 64, M - 1]) if big else (np.arange(M) if M * N < 800000 else
+                                                             np.union1d(_sample(M, rng, 60), [0, 63, 64, M - 1]))
+            cols = np.array([0, N - 1]) if big else np.arange(N)
+            _compare(g, b, rows, cols, out, cnt, oracle_mod, "tall%s b%d" % (case, b))
+
+
+def test_noalloc_keeps_long_narrow_calls(dev, oracle_mod):
+    # chunks of this A (72 MB) do not fit the array of sc_gemm_noalloc: the layout that takes the
+    # operands as they are does, and the call goes on to run there
+    import torch
+    import paper_2609_32922_amd as scg
+    M, N, K, L = 30000, 100, 2400, 64
+    rng = np.random.default_rng(731)
+    g = W.random_gemm(rng, 1, M, N, K, L, 0, 731, uniform_L=L)
+    A, sA, B, sB, Lt = _to_dev(g, dev)
+    d = scg.make_desc(A, B, L, 0, 731)
+    assert scg.sc_gemm_workspace_size(d) <= scg.SC_NOALLOC_WORKSPACE_BYTES
+    out = torch.empty((1, M, N), dtype=torch.float32, device=dev)
+    cnt = torch.empty((1, M, N), dtype=torch.int32, device=dev)
+    _note("no-alloc call with a long narrow operand")
+    rc = scg.sc_gemm_noalloc(d, A.data_ptr(), sA.data_ptr(), B.data_ptr(), sB.data_ptr(), Lt.data_ptr(),
+                             out.data_ptr(), cnt.data_ptr(), 0, int(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0
+    torch.cuda.synchronize()
+    rows = np.union1d(_sample(M, rng, 20), [0, M - 1])
+    _compare(g, 0, rows, np.arange(N), out.cpu().numpy(), cnt.cpu().numpy(), oracle_mod, "noalloc long narrow")
