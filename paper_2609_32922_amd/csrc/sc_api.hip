@@ -4,6 +4,7 @@
 #include <math.h>
 
 #include <atomic>
+#include <initializer_list>
 #include <mutex>
 
 #include "sc_internal.h"
@@ -111,14 +112,16 @@ static int device_cus() {
 // the 128-row kernels could not take their operands as they are
 enum { LAY_FULL, LAY_ONE_PLAN, LAY_LEAST };
 
-static bool layout_with(const sc_gemm_desc &d, int cus, int spend, Layout *lay) {
+// cbsg: of the tables of a C-BSG call (d's source is then taken as the LFSR)
+static bool layout_with(const sc_gemm_desc &d, int cus, int spend, bool cbsg, Layout *lay) {
     Layout l{};
+    l.cbsg = cbsg;
     l.cus = cus > 0 ? cus : DEFAULT_CUS;
     l.KQP = (int)round_up((d.K + 3) / 4, 4);
     l.words_per_L = (int64_t)l.KQP * 64;
     l.MT = (d.M + BM - 1) / BM;
     l.NT = (d.N + BN - 1) / BN;
-    const bool lfsr = d.rng == SC_RNG_LFSR32;
+    const bool lfsr = d.rng == SC_RNG_LFSR32 || cbsg;
     const double Lmean = d.L_hint > 0 ? d.L_hint : d.L_max;
     const int KC = (d.K + 31) / 32;
     const bool one_length = Lmean >= d.L_max, long_tiles = (int64_t)KC * ((int64_t)(Lmean + 31) / 32) >= 16;
@@ -146,7 +149,9 @@ static bool layout_with(const sc_gemm_desc &d, int cus, int spend, Layout *lay) 
     w.cus = l.cus;
     w.one = one_length;
     const bool bip = d.polarity == SC_BIPOLAR_XNOR;
-    w.gmean = ceil(mean_slots(Lmean, bip) / 32.0);
+    // (C-BSG: counters k and L - 1 - k share a slot, or nearly none of B's classes repeat up to 128)
+    const double slots = !cbsg ? mean_slots(Lmean, bip) : bip ? (d.L_max + 1) / 2 : fmin(d.L_max, 127);
+    w.gmean = ceil(slots / 32.0);
     w.gmax = one_length ? w.gmean : (d.L_max + 31) / 32;
     const int64_t rsteps = (int64_t)KC * ((d.L_max + 31) / 32);
     w.Smin = 1;
@@ -185,7 +190,6 @@ static bool layout_with(const sc_gemm_desc &d, int cus, int spend, Layout *lay) 
     l.LBS = (int)round_up(d.L_max, LCH);
     l.nbB = (d.strideB == 0) ? 1 : d.batch;
     if (l.nbB < 1) l.nbB = 1;
-    const bool cbsg = d.rng == SC_RNG_SOBOL8_CBSG;
 
     // the status word is always the first word of the workspace
     size_t off = 0;
@@ -197,13 +201,13 @@ static bool layout_with(const sc_gemm_desc &d, int cus, int spend, Layout *lay) 
     l.off_rB = off;
     if (!l.rgen) off = align256(off + (size_t)l.LBS * 4);
     l.off_CA = off;
-    if (cbsg) off = align256(off + (size_t)(d.L_max + 1) * CA_COLS * 2);
+    if (!lfsr) off = align256(off + (size_t)(d.L_max + 1) * CA_COLS * 2);
     // Slot plans: while a tile's products sum to less than 2^24 in magnitude whatever slots hold
     // them (K x L_max; so every part is exact), and more than one group of 32 cycles exists.
     // At most 32 plans past the first, and at most PLAN_GROUPS tables.
     l.nplans = 1;
     l.pstep = LCH;
-    if (spend == LAY_FULL && l.rgen && l.LBS > 32 && (int64_t)l.KC * 32 * l.LBS < MFMA_EXACT) {
+    if (spend == LAY_FULL && !cbsg && l.rgen && l.LBS > 32 && (int64_t)l.KC * 32 * l.LBS < MFMA_EXACT) {
         const int n = PLAN_GROUPS / (l.LBS / 32) < 32 ? PLAN_GROUPS / (l.LBS / 32) : 32;
         l.pstep = (int)round_up((d.L_max + n - 1) / n, 8);
         l.nplans = 1 + (d.L_max + l.pstep - 1) / l.pstep;
@@ -395,8 +399,10 @@ static bool layout_with(const sc_gemm_desc &d, int cus, int spend, Layout *lay) 
     l.Sleast = tall || l.F > 0 ? l.S : l.Smin;
     if (l.rgen && !l.vsplit && l.S > 1) {
         const int64_t smin = l.Sleast;
-        const int64_t steps = (int64_t)l.KC * (l.LBS / 32);
-        l.p16 = (steps + smin - 1) / smin <= P16_STEPS;
+        // (a step of a C-BSG call's slots, two cycles each, twice as much)
+        const bool two = cbsg && bip;
+        const int64_t steps = (int64_t)l.KC * (two ? ((d.L_max + 1) / 2 + 31) / 32 : l.LBS / 32);
+        l.p16 = (steps + smin - 1) / smin <= P16_STEPS / (two ? 2 : 1);
     }
     l.off_part = off;
     if (pieces > 0 && (l.S > 1 || l.vsplit)) {
@@ -420,14 +426,34 @@ static bool layout_with(const sc_gemm_desc &d, int cus, int spend, Layout *lay) 
 }
 
 bool make_layout(const sc_gemm_desc &d, int cus, Layout *lay) {
-    if (!layout_with(d, cus, LAY_FULL, lay)) return false;
+    if (!layout_with(d, cus, LAY_FULL, false, lay)) return false;
     // a call that fits sc_gemm_noalloc's array without the tables of the slot plans, or without
     // chunks of its operands, keeps fitting it
     for (int spend = LAY_ONE_PLAN; lay->total > SC_NOALLOC_WORKSPACE_BYTES && spend <= LAY_LEAST; ++spend) {
         Layout less;
-        if (layout_with(d, cus, spend, &less) && less.total <= SC_NOALLOC_WORKSPACE_BYTES) *lay = less;
+        if (layout_with(d, cus, spend, false, &less) && less.total <= SC_NOALLOC_WORKSPACE_BYTES) *lay = less;
     }
     return true;
+}
+
+// Products of a C-BSG call from which the tables are tried: there the launches that may return at
+// once (two, about 5 us, beside the chunks' 7) are small against the planes' path (over 200 us)
+static constexpr double CBSG_TABLES = 4e11;
+bool make_cbsg_layout(const sc_gemm_desc &d, int cus, const Layout &planes, Layout *lay) {
+    if (d.rng != SC_RNG_SOBOL8_CBSG || d.batch < 1 || d.K < 1 || (d.L_hint > 0 && d.L_hint < d.L_max) ||
+        (double)d.batch * d.M * d.N * d.K * d.L_max < CBSG_TABLES)
+        return false;
+    if (round_up(d.K, 32) * round_up(d.L_max, 32) >= MFMA_EXACT || !layout_with(d, cus, LAY_FULL, true, lay) || !lay->rgen)
+        return false;
+    const size_t base = planes.total;
+    if (lay->total > SIZE_MAX - base) return false;
+    for (size_t *o : {&lay->off_rA, &lay->off_rB, &lay->off_status, &lay->off_CA, &lay->off_plan, &lay->off_pslots,
+                      &lay->off_rtab, &lay->off_perm, &lay->off_Ls, &lay->off_tileL, &lay->off_tileOff, &lay->off_pair,
+                      &lay->off_Ap, &lay->off_Bp, &lay->off_part, &lay->off_units, &lay->off_tinfo, &lay->off_slot,
+                      &lay->total})
+        *o += base;
+    // a call whose planes fit sc_gemm_noalloc's array keeps fitting it
+    return planes.total > SC_NOALLOC_WORKSPACE_BYTES || lay->total <= SC_NOALLOC_WORKSPACE_BYTES;
 }
 
 static int check_desc(const sc_gemm_desc *d) {
@@ -458,12 +484,19 @@ static int check_desc(const sc_gemm_desc *d) {
 
 // Checks of one call (before anything is enqueued) and its workspace layout.
 static int check_call(const sc_gemm_desc *desc, const int8_t *A, const float *sA, const int8_t *B,
-                      const float *sB, const int32_t *L_per_row, const float *out, Layout *lay) {
+                      const float *sB, const int32_t *L_per_row, const float *out, Layout *lay, Layout *tables) {
     const int rc = check_desc(desc);
     if (rc != SC_OK) return rc;
     const sc_gemm_desc &d = *desc;
     // a descriptor whose workspace cannot be laid out is refused as sc_gemm_workspace_size refuses it
-    if (!make_layout(d, device_cus(), lay)) return SC_ERR_SHAPE;
+    const int cus = device_cus();
+    if (!make_layout(d, cus, lay)) return SC_ERR_SHAPE;
+    if (make_cbsg_layout(d, cus, *lay, tables)) {
+        lay->off_skip = tables->off_status + 3 * 4;
+        lay->total = tables->total;
+    } else {
+        tables->rgen = 0;
+    }
     // a pointer may be NULL only when the array it points to has no elements
     const bool anyM = d.batch > 0 && d.M > 0, anyN = d.batch > 0 && d.N > 0;
     if ((anyM && d.K > 0 && A == nullptr) || (anyN && d.K > 0 && B == nullptr) ||
@@ -473,9 +506,10 @@ static int check_call(const sc_gemm_desc *desc, const int8_t *A, const float *sA
     return SC_OK;
 }
 
-// The launch sequence of one call on workspace ws (lay.total bytes, 256-byte aligned).
-static int enqueue(const sc_gemm_desc &d, const Layout &lay, const int8_t *A, const float *sA, const int8_t *B,
-                   const float *sB, const int32_t *L_per_row, float *out, int32_t *counts, uint8_t *ws,
+// The launch sequence of one call on workspace ws (lay.total bytes, 256-byte aligned); tables: of
+// a C-BSG call whose rows may all have one length (rgen), or none
+static int enqueue(const sc_gemm_desc &d, const Layout &lay, const Layout &tables, const int8_t *A, const float *sA,
+                   const int8_t *B, const float *sB, const int32_t *L_per_row, float *out, int32_t *counts, uint8_t *ws,
                    hipStream_t st) {
     uint32_t *rA = reinterpret_cast<uint32_t *>(ws + lay.off_rA);
     // one batch entry with LFSR sequences: the scheduler's single block also clears the
@@ -483,18 +517,20 @@ static int enqueue(const sc_gemm_desc &d, const Layout &lay, const int8_t *A, co
     // int8-chunk GEMM's scheduler and k_rprep write all that k_draws would
     const bool empty = d.batch == 0 || d.M == 0 || d.N == 0;
     const bool fuse = !empty && (lay.rgen || (d.batch == 1 && d.rng == SC_RNG_LFSR32));
+    const bool try_tables = tables.rgen != 0 && !empty;
     hipError_t e = hipSuccess;
-    if (!fuse) {
+    // (the tables' first two launches also write what the planes path's first two would)
+    if (try_tables && (launch_schedule(d, tables, L_per_row, ws, false, &lay, st) != hipSuccess ||
+                       launch_rprep(d, tables, A, B, ws, st) != hipSuccess))
+        return SC_ERR_HIP;
+    if (!fuse && !try_tables) {
         e = launch_draws(d.seed, d.rng, lay.LBS, rA, reinterpret_cast<uint32_t *>(ws + lay.off_rB), nullptr, -1,
                          reinterpret_cast<uint32_t *>(ws + lay.off_status), st);
         if (e != hipSuccess) return SC_ERR_HIP;
     }
     if (empty) return SC_OK;
 
-    if (d.rng == SC_RNG_SOBOL8_CBSG &&
-        launch_cbsg_table(rA, d.L_max, reinterpret_cast<uint16_t *>(ws + lay.off_CA), st) != hipSuccess)
-        return SC_ERR_HIP;
-    if ((e = launch_schedule(d, lay, L_per_row, ws, fuse, st)) != hipSuccess) return SC_ERR_HIP;
+    if (!try_tables && (e = launch_schedule(d, lay, L_per_row, ws, fuse, nullptr, st)) != hipSuccess) return SC_ERR_HIP;
     if (lay.rgen) {
         if ((e = launch_rprep(d, lay, A, B, ws, st)) != hipSuccess) return SC_ERR_HIP;
     } else if (!lay.fused) {
@@ -508,6 +544,7 @@ static int enqueue(const sc_gemm_desc &d, const Layout &lay, const int8_t *A, co
     set_gemm_events(ev0, ev1);
     e = lay.fused ? launch_fgemm(d, lay, A, B, sA, sB, out, counts, ws, st)
                   : launch_mgemm(d, lay, sA, sB, out, counts, ws, st);
+    if (e == hipSuccess && try_tables) e = launch_mgemm(d, tables, sA, sB, out, counts, ws, st);
     const bool taken = gemm_events_taken();
     set_gemm_events(nullptr, nullptr);
     if (e != hipSuccess) return SC_ERR_HIP;
@@ -571,36 +608,37 @@ int sc_gemm_workspace_size(const sc_gemm_desc *desc, size_t *bytes) {
     if (bytes == nullptr) return SC_ERR_NULL;
     const int rc = check_desc(desc);
     if (rc != SC_OK) return rc;
-    Layout lay;
-    if (!make_layout(*desc, device_cus(), &lay)) return SC_ERR_SHAPE;
-    *bytes = lay.total;
+    Layout lay, tables;
+    const int cus = device_cus();
+    if (!make_layout(*desc, cus, &lay)) return SC_ERR_SHAPE;
+    *bytes = make_cbsg_layout(*desc, cus, lay, &tables) ? tables.total : lay.total;
     return SC_OK;
 }
 
 int sc_gemm(const sc_gemm_desc *desc, const int8_t *A, const float *sA, const int8_t *B,
             const float *sB, const int32_t *L_per_row, float *out, int32_t *counts, void *workspace,
             size_t workspace_bytes, void *stream) {
-    Layout lay;
-    const int rc = check_call(desc, A, sA, B, sB, L_per_row, out, &lay);
+    Layout lay, tables;
+    const int rc = check_call(desc, A, sA, B, sB, L_per_row, out, &lay, &tables);
     if (rc != SC_OK) return rc;
     if (workspace == nullptr || workspace_bytes < lay.total ||
         (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0)
         return SC_ERR_WORKSPACE;
-    return enqueue(*desc, lay, A, sA, B, sB, L_per_row, out, counts, reinterpret_cast<uint8_t *>(workspace),
+    return enqueue(*desc, lay, tables, A, sA, B, sB, L_per_row, out, counts, reinterpret_cast<uint8_t *>(workspace),
                    reinterpret_cast<hipStream_t>(stream));
 }
 
 int sc_gemm_noalloc(const sc_gemm_desc *desc, const int8_t *A, const float *sA, const int8_t *B,
                     const float *sB, const int32_t *L_per_row, float *out, int32_t *counts,
                     int32_t *status_out, void *stream) {
-    Layout lay;
-    const int rc = check_call(desc, A, sA, B, sB, L_per_row, out, &lay);
+    Layout lay, tables;
+    const int rc = check_call(desc, A, sA, B, sB, L_per_row, out, &lay, &tables);
     if (rc != SC_OK) return rc;
     if (lay.total > SC_NOALLOC_WORKSPACE_BYTES) return SC_ERR_WORKSPACE;
     uint8_t *ws = nullptr;
     if (!scratch_address(&ws)) return SC_ERR_HIP;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    const int e = enqueue(*desc, lay, A, sA, B, sB, L_per_row, out, counts, ws, st);
+    const int e = enqueue(*desc, lay, tables, A, sA, B, sB, L_per_row, out, counts, ws, st);
     if (e != SC_OK) return e;
     // the status word (offset 0 of every workspace) of this call, for the caller
     if (status_out != nullptr &&

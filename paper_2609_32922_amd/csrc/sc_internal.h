@@ -6,7 +6,7 @@
 //              tile-pair cycle count of the call (256-row GEMM), then one uint32: nonzero
 //              when some 256-row pair holds more row lengths that end inside a slot group
 //              than the int8-chunk GEMM has masked tables (rslots; it then masks its
-//              fragments).  Cleared by k_draws (or k_schedule), or, int8-chunk GEMM, written
+//              fragments), then one uint32: nonzero when a C-BSG call's tables serve.  Cleared by k_draws (or k_schedule), or, int8-chunk GEMM, written
 //              by k_rprep
 //   draws      rA[LBS], rB[LBS]                   uint32, comparator sequences (not with rgen)
 //   CA         C-BSG only: CA[L][beta] = #{l < L : rA_l < beta}, uint16 [L_max+1][257]
@@ -109,6 +109,12 @@ __host__ __device__ inline double quad_split_time(int64_t tiles, int s, double p
 // below its prefix p_k, and cycle p_k + j keeps a slot of its own, S_k + j: a 256-row pair
 // takes the plan with the largest prefix no longer than its shortest row, and a row of L >=
 // p_k cycles ends after S_k + L - p_k slots.  Prefixes: multiples of pstep, and L_max.
+//
+// C-BSG calls whose rows all have L = L_max cycles take the same GEMM: A's bit of counter k is
+// [k < c(n)], c(n) = #{l < L : class(rA_l) <= n}, so it is [n >= the (k + 1)-th smallest class of A's
+// draws].  Bipolar: A holds sgn D_k = [k < c] - [k < L - c], the same at k and L - 1 - k, so the two
+// share a slot: half the cycles.  The host cannot see the lengths, so it enqueues this path (first)
+// and the planes path, and the one that does not serve returns at once.
 constexpr int SLOT_CYCLES = 4;
 constexpr int MAX_PLANS = 40;    // plans of a call (bits of the status words)
 constexpr int PLAN_GROUPS = 512; // most (plan, group) tables of a call, 8 KiB each
@@ -209,6 +215,8 @@ struct Layout {
     int tall;          // rgen in blocks of 64 rows x 128 tall columns (k_tgemm): columns of 32 per wave,
                        // 0 when the blocks have 256 rows
     int tshift, rtiles;    // rgen: rows of a tile (256, or 64 with tall) as a shift, and row tiles
+    int cbsg;          // rgen: the tables of a C-BSG call whose rows all have L_max cycles (below)
+    size_t off_skip;   // planes of such a call: a word that is nonzero when its tables serve (0: none)
     int narrow;        // rgen with N <= 64: blocks of 256 rows x 64 columns
     int rslots;        // rgen: tables masked to a row length per cycle group (0 when narrow)
     int KC;            // 32-element chunks per row, ceil(K/32)
@@ -243,15 +251,18 @@ struct Layout {
 // Host-side layout computation for a device with `cus` compute units (no HIP calls).
 // Returns false on overflow or when no split count up to MAX_SPLIT keeps the counts exact.
 bool make_layout(const sc_gemm_desc &d, int cus, Layout *lay);
+// The layout of a C-BSG call's tables behind its planes layout; false when it has none.
+bool make_cbsg_layout(const sc_gemm_desc &d, int cus, const Layout &planes, Layout *lay);
 
 // Kernel launchers (sc_kernels.hip).  All return hipSuccess or the launch error.
 hipError_t launch_draws(uint64_t seed, int rng, int n, uint32_t *rA, uint32_t *rB,
                         uint8_t *bytes_out, int op_only, uint32_t *status, hipStream_t st);
-hipError_t launch_cbsg_table(const uint32_t *rA, int L_max, uint16_t *CA, hipStream_t st);
 // draws: also clear the status words and make the comparator sequences (one batch entry only);
-// with rgen also the slot plans
+// with rgen also the slot plans, with C-BSG planes also the table CA (from k_draws' sequences)
+// planes (with the tables of a C-BSG call): the layout of its planes, for which the same launch
+// writes all that k_draws and its own scheduler would, but the status words (k_rprep)
 hipError_t launch_schedule(const sc_gemm_desc &d, const Layout &lay, const int32_t *L,
-                           uint8_t *ws, bool draws, hipStream_t st);
+                           uint8_t *ws, bool draws, const Layout *planes, hipStream_t st);
 
 // counting GEMM (sc_mfma.hip)
 // Profiling events of the next launch_mgemm / launch_fgemm on this host thread (sc_gemm's
@@ -276,6 +287,13 @@ __host__ __device__ inline int64_t fused_extent(int rows, int64_t ld, int K) {
     return rows > 0 && K > 0 ? (int64_t)(rows - 1) * ld + K : 0;
 }
 
+// Where the scheduler of a C-BSG call's tables leaves what the planes path reads
+struct PlanesOut {
+    int MT, mbm, LBS;
+    int64_t words_per_L;
+    size_t off_perm, off_Ls, off_tileL, off_tileOff, off_rA, off_rB, off_CA, stride_batchA;
+};
+
 // cycles below which slot plan k merges (k < nplans), and the plan of a pair whose shortest row
 // has L cycles
 __host__ __device__ inline int plan_prefix(int k, int nplans, int pstep, int L_max) {
@@ -283,6 +301,11 @@ __host__ __device__ inline int plan_prefix(int k, int nplans, int pstep, int L_m
 }
 __host__ __device__ inline int plan_of(int L, int nplans, int pstep, int L_max) {
     return nplans == 1 ? 0 : L >= L_max ? nplans - 1 : L / pstep;
+}
+// a kernel of the path (tables, or planes) that does not serve this C-BSG call
+__device__ __forceinline__ bool not_serving(const Layout &lay, uint8_t *ws) {
+    return (lay.cbsg && ws_ptr<uint32_t>(ws, lay.off_status)[3] == 0u) ||
+           (lay.off_skip != 0 && *ws_ptr<uint32_t>(ws, lay.off_skip) != 0u);
 }
 // slots of a row of L cycles in a pair whose plan saves `save` slots and gives L_max `top` slots
 // (top counts whole groups: the slots past the last cycle are zero)

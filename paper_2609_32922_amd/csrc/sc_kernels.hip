@@ -5,11 +5,11 @@
 //                through jump-ahead; it also clears the status words.  With one batch
 //                entry and LFSR sequences k_schedule does both instead (one launch fewer),
 //                and the int8-chunk GEMM needs neither
-//   k_cbsg_table C-BSG only: CA[L][beta] = ones of A's stream in its first L cycles
 //   k_schedule   per-row length scheduler: validates L_i, counting-sorts rows by L
 //                (descending) so that a 128-row tile runs for the longest length it
 //                holds (Sec. 4.2: row i stops after its own l_i cycles; Sec. 4.1: the
-//                cost grows with the sum of the l_i)
+//                cost grows with the sum of the l_i); with C-BSG planes one more block makes
+//                CA[L][beta] = ones of A's stream in its first L cycles
 //   k_schedule_plans  the same for the int8-chunk GEMM, with its slot plans beside it
 #include "sc_internal.h"
 
@@ -127,9 +127,8 @@ hipError_t launch_draws(uint64_t seed, int rng, int n, uint32_t *rA, uint32_t *r
 
 // CA[L][beta] = #{l < L : rA_l < beta} for L = 0..L_max, beta = 0..256 (one thread per
 // boundary; L_max <= 256 draws staged in LDS)
-__global__ __launch_bounds__(320) void k_cbsg_table(const uint32_t *__restrict__ rA, int L_max,
-                                                    uint16_t *__restrict__ CA) {
-    __shared__ uint32_t r[CBSG_L_MAX];
+__device__ __forceinline__ void cbsg_table_block(const uint32_t *rA, int L_max, uint16_t *__restrict__ CA,
+                                                 uint32_t *r) {
     const int beta = threadIdx.x;
     for (int l = threadIdx.x; l < L_max; l += blockDim.x) r[l] = rA[l];
     __syncthreads();
@@ -140,11 +139,6 @@ __global__ __launch_bounds__(320) void k_cbsg_table(const uint32_t *__restrict__
         c += r[l] < (uint32_t)beta ? 1u : 0u;
     }
     CA[(size_t)L_max * CA_COLS + beta] = (uint16_t)c;
-}
-
-hipError_t launch_cbsg_table(const uint32_t *rA, int L_max, uint16_t *CA, hipStream_t st) {
-    hipLaunchKernelGGL(k_cbsg_table, dim3(1), dim3(320), 0, st, rA, L_max, CA);
-    return hipGetLastError();
 }
 
 // ----------------------------------------------------------------------------
@@ -180,7 +174,7 @@ struct SchedLds {
 template <bool RGEN>
 __device__ __forceinline__ void schedule_block(const int32_t *__restrict__ L, int64_t strideL, int M, int L_max,
                                                const Layout &lay, uint8_t *ws, uint64_t seed, int rng, int ndraws,
-                                               SchedLds &sh) {
+                                               SchedLds &sh, const PlanesOut &po) {
     int *hist = sh.hist, *hstart = sh.hstart, *dpair = sh.dpair;
     int &lmin = sh.lmin, &lmax = sh.lmax;
     const int b = blockIdx.x, tid = threadIdx.x;
@@ -390,8 +384,29 @@ __device__ __forceinline__ void schedule_block(const int32_t *__restrict__ L, in
         }
         __syncthreads();
         if (tid == 0)
-            pair[npairs] = make_int4((int)sh.bad, (int)round_up(one ? lmin : length_at(0), MSTEP), (int)sh.used[0],
-                                     (int)sh.used[1]);
+            pair[npairs] = make_int4((int)sh.bad, (int)round_up(one ? lmin : length_at(0), MSTEP),
+                                     lay.cbsg ? (one ? lmin : length_at(M - 1)) : (int)sh.used[0], (int)sh.used[1]);
+        if (lay.cbsg) {
+            // the planes path's rows (as above, in its own place) and tiles (as below)
+            uint8_t *wsp = ws + (size_t)b * po.stride_batchA;
+            for (int p = tid; p < po.MT * BM; p += 1024) {
+                const bool in = p < lay.MT * BM;
+                ws_ptr<int32_t>(wsp, po.off_perm)[p] = in ? perm[p] : -1;
+                ws_ptr<int32_t>(wsp, po.off_Ls)[p] = in ? Ls[p] : 0;
+            }
+            int64_t carry = 0;
+            for (int c = 0; c < po.MT; c += 1024) {
+                const int t = c + tid, p = (po.mbm == 2 * BM ? (t & ~1) : t) * BM;
+                const int tl = t >= po.MT || p >= M ? 0 : (int)round_up(one ? lmin : length_at(p), MSTEP);
+                int64_t tot;
+                const int64_t ex = block_excl_scan<1024>((int64_t)tl * po.words_per_L, &tot);
+                if (t < po.MT) {
+                    ws_ptr<int32_t>(wsp, po.off_tileL)[t] = tl;
+                    ws_ptr<int64_t>(wsp, po.off_tileOff)[t] = carry + ex;
+                }
+                carry += tot;
+            }
+        }
     } else {
         // tile lengths (first sorted row of a tile holds its longest length; a pair of tiles
         // that one 256-row block takes runs at the pair's longest length) and the tiles' plane
@@ -431,7 +446,7 @@ struct PlanLds {
     int deg[512];                       // live cycles of each class: A's, then B's
     int mark[512];                      // the round in which the class was taken
     int cnt[512], base[512];            // cycles, and first slot, of each class
-    uint32_t own[SC_L_MAX_LIMIT];       // slot: class | side << 8 | cycles << 9
+    uint32_t own[SC_L_MAX_LIMIT];       // slot: class | side << 8 | cycles << 9 | second class << 16
     uint32_t part[SC_L_MAX_LIMIT];      // slot: its cycles' classes on the other side, a byte each
     int wg[SC_L_MAX_LIMIT / 32];        // cycles of each group
     int leaf[8], left[8];               // per round: a class of one live cycle exists; cycles are left
@@ -443,7 +458,9 @@ __device__ __forceinline__ void plan_block(int k, const Layout &lay, int L_max, 
                                            PlanLds &sh) {
     constexpr int EPT = SC_L_MAX_LIMIT / 1024;    // cycles per thread
     const int tid = threadIdx.x;
-    const int p = plan_prefix(k, lay.nplans, lay.pstep, L_max);
+    const int p = lay.cbsg ? L_max : plan_prefix(k, lay.nplans, lay.pstep, L_max);
+    const int rng = lay.cbsg ? SC_RNG_SOBOL8_CBSG : SC_RNG_LFSR32;
+    uint2 *slots = ws_ptr<uint2>(ws, lay.off_pslots) + (size_t)k * lay.LBS;
     int ca[EPT], cb[EPT], rank[EPT];
     uint32_t live = 0u, onB = 0u;
     if (tid < 512) {
@@ -459,12 +476,39 @@ __device__ __forceinline__ void plan_block(int k, const Layout &lay, int L_max, 
         const int l = i * 1024 + tid;
         ca[i] = cb[i] = rank[i] = 0;
         if (l >= L_max) continue;
-        const int ra = (int)draw_value(seed, SC_RNG_LFSR32, 0, l), rb = (int)draw_value(seed, SC_RNG_LFSR32, 1, l);
+        const int ra = (int)draw_value(seed, rng, 0, l), rb = (int)draw_value(seed, rng, 1, l);
         ca[i] = bip ? class_bipolar(ra) : class_unipolar(ra);
         cb[i] = 256 + (bip ? class_bipolar(rb) : class_unipolar(rb));
         if (l < p) live |= 1u << i;
     }
     __syncthreads();
+    if (lay.cbsg) {
+        // A's classes in increasing order (L_max <= 256 draws, one per thread), B's beside them
+        if (tid < L_max) sh.part[tid] = (uint32_t)ca[0];
+        __syncthreads();
+        if (tid < L_max) {
+            int at = 0;
+            for (int l = 0; l < L_max; ++l) at += (int)sh.part[l] < ca[0] || ((int)sh.part[l] == ca[0] && l < tid) ? 1 : 0;
+            sh.own[at] = (uint32_t)ca[0];
+            sh.own[CBSG_L_MAX + tid] = (uint32_t)(cb[0] - 256);
+        }
+        __syncthreads();
+        if (bip) {
+            // slot j: counters j and L - 1 - j, A = [n >= u] + [n >= v] - 1 there
+            const int S = (L_max + 1) / 2, j = tid, e = L_max - 1 - tid;
+            if (j < S)
+                slots[j] = make_uint2(sh.own[e] | (j == e ? 1u : 2u) << 9 | sh.own[j] << 16,
+                                      sh.own[CBSG_L_MAX + j] | (j == e ? 255u : sh.own[CBSG_L_MAX + e]) << 8 | 0xFFFF0000u);
+            if (tid < 32 && S + tid < (int)round_up(S, 32)) slots[S + tid] = make_uint2(0u, 0xFFFFFFFFu);
+            if (tid == 0) ws_ptr<int4>(ws, lay.off_plan)[k] = make_int4(L_max, S, S, 0);
+            return;
+        }
+        if (tid < L_max) {
+            ca[0] = (int)sh.own[tid];
+            sh.part[tid] = 0xFFFFFFFFu;
+        }
+        __syncthreads();
+    }
 #pragma unroll
     for (int i = 0; i < EPT; ++i)
         if ((live >> i) & 1u) {
@@ -517,7 +561,7 @@ __device__ __forceinline__ void plan_block(int k, const Layout &lay, int L_max, 
         reinterpret_cast<uint8_t *>(&sh.part[slot])[j] = (uint8_t)(o & 255);
         if (j == 0) {
             const int n = min(SLOT_CYCLES, sh.cnt[v] - (rank[i] - j));
-            sh.own[slot] = (uint32_t)(v & 255) | (b ? 0x100u : 0u) | ((uint32_t)n << 9);
+            sh.own[slot] = (uint32_t)(v & 255) * 0x10001u | (b ? 0x100u : 0u) | ((uint32_t)n << 9);
             if (lay.p16) atomicAdd(&sh.wg[slot / 32], n);
         }
     }
@@ -542,13 +586,12 @@ __device__ __forceinline__ void plan_block(int k, const Layout &lay, int L_max, 
         if (steps * 32 * sh.wmax > 32767) S = p;
     }
     const bool merged = S < p;
-    uint2 *slots = ws_ptr<uint2>(ws, lay.off_pslots) + (size_t)k * lay.LBS;
     for (int i = tid; merged && i < S; i += 1024) slots[i] = make_uint2(sh.own[i], sh.part[i]);
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
         const int l = i * 1024 + tid;
         if (l < L_max && (l >= p || !merged))
-            slots[S + l - p] = make_uint2((uint32_t)ca[i] | (1u << 9), (uint32_t)(cb[i] - 256) | 0xFFFFFF00u);
+            slots[S + l - p] = make_uint2((uint32_t)ca[i] * 0x10001u | (1u << 9), (uint32_t)(cb[i] - 256) | 0xFFFFFF00u);
     }
     const int T = S + L_max - p;
     if (tid < 32 && T + tid < (int)round_up(T, 32)) slots[T + tid] = make_uint2(0u, 0xFFFFFFFFu);
@@ -558,7 +601,12 @@ __device__ __forceinline__ void plan_block(int k, const Layout &lay, int L_max, 
 __global__ __launch_bounds__(1024) void k_schedule(const int32_t *__restrict__ L, int64_t strideL, int M, int L_max,
                                                    Layout lay, uint8_t *ws, uint64_t seed, int rng, int ndraws) {
     __shared__ SchedLds sh;
-    schedule_block<false>(L, strideL, M, L_max, lay, ws, seed, rng, ndraws, sh);
+    if (rng == SC_RNG_SOBOL8_CBSG && blockIdx.x == gridDim.x - 1) {
+        cbsg_table_block(ws_ptr<uint32_t>(ws, lay.off_rA), L_max, ws_ptr<uint16_t>(ws, lay.off_CA),
+                         reinterpret_cast<uint32_t *>(sh.hist));
+        return;
+    }
+    schedule_block<false>(L, strideL, M, L_max, lay, ws, seed, rng, ndraws, sh, PlanesOut{});
 }
 
 // Int8-chunk GEMM: blocks 0 .. batch-1 schedule a batch entry each, the rest make a slot plan each
@@ -568,21 +616,46 @@ union SchedPlanLds {
 };
 __global__ __launch_bounds__(1024) void k_schedule_plans(const int32_t *__restrict__ L, int64_t strideL, int batch,
                                                          int M, int L_max, Layout lay, uint8_t *ws, uint64_t seed,
-                                                         int polarity) {
+                                                         int polarity, PlanesOut po) {
     __shared__ SchedPlanLds sh;
-    if ((int)blockIdx.x < batch) schedule_block<true>(L, strideL, M, L_max, lay, ws, seed, SC_RNG_LFSR32, 0, sh.s);
-    else plan_block((int)blockIdx.x - batch, lay, L_max, ws, seed, polarity == SC_BIPOLAR_XNOR, sh.p);
+    if ((int)blockIdx.x < batch) {
+        schedule_block<true>(L, strideL, M, L_max, lay, ws, seed, SC_RNG_LFSR32, 0, sh.s, po);
+    } else if ((int)blockIdx.x - batch == lay.nplans) {
+        // (C-BSG) the planes path's sequences and table CA
+        uint32_t *rA = ws_ptr<uint32_t>(ws, po.off_rA), *rB = ws_ptr<uint32_t>(ws, po.off_rB);
+        for (int l = threadIdx.x; l < po.LBS; l += 1024) {
+            rA[l] = draw_value(seed, SC_RNG_SOBOL8_CBSG, 0, l);
+            rB[l] = draw_value(seed, SC_RNG_SOBOL8_CBSG, 1, l);
+        }
+        __syncthreads();
+        cbsg_table_block(rA, L_max, ws_ptr<uint16_t>(ws, po.off_CA), reinterpret_cast<uint32_t *>(sh.s.hist));
+    } else plan_block((int)blockIdx.x - batch, lay, L_max, ws, seed, polarity == SC_BIPOLAR_XNOR, sh.p);
 }
 
 hipError_t launch_schedule(const sc_gemm_desc &d, const Layout &lay, const int32_t *L, uint8_t *ws,
-                           bool draws, hipStream_t st) {
+                           bool draws, const Layout *planes, hipStream_t st) {
     if (lay.rgen) {
-        hipLaunchKernelGGL(k_schedule_plans, dim3((unsigned)(d.batch + lay.nplans)), dim3(1024), 0, st, L, d.strideL,
-                           d.batch, d.M, d.L_max, lay, ws, d.seed, d.polarity);
+        PlanesOut po{};
+        if (planes != nullptr) {
+            po.MT = planes->MT;
+            po.mbm = planes->mbm;
+            po.LBS = planes->LBS;
+            po.words_per_L = planes->words_per_L;
+            po.off_perm = planes->off_perm;
+            po.off_Ls = planes->off_Ls;
+            po.off_tileL = planes->off_tileL;
+            po.off_tileOff = planes->off_tileOff;
+            po.off_rA = planes->off_rA;
+            po.off_rB = planes->off_rB;
+            po.off_CA = planes->off_CA;
+            po.stride_batchA = planes->stride_batchA;
+        }
+        hipLaunchKernelGGL(k_schedule_plans, dim3((unsigned)(d.batch + lay.nplans + (lay.cbsg ? 1 : 0))), dim3(1024), 0,
+                           st, L, d.strideL, d.batch, d.M, d.L_max, lay, ws, d.seed, d.polarity, po);
         return hipGetLastError();
     }
     if (draws && d.batch != 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_schedule, dim3((unsigned)d.batch), dim3(1024), 0, st, L, d.strideL, d.M, d.L_max, lay, ws,
+    hipLaunchKernelGGL(k_schedule, dim3((unsigned)d.batch + (d.rng == SC_RNG_SOBOL8_CBSG ? 1u : 0u)), dim3(1024), 0, st, L, d.strideL, d.M, d.L_max, lay, ws,
                        d.seed, d.rng, draws ? lay.LBS : 0);
     return hipGetLastError();
 }

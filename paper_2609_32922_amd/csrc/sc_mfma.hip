@@ -118,7 +118,7 @@ struct MPlaneArgs {
     int per_row;                // 1: A side (sorted rows, per-row lengths)
     size_t stride_batch;
     size_t off_perm, off_Ls, off_tileL, off_tileOff;
-    size_t off_planes, off_r, off_CA;
+    size_t off_planes, off_r, off_CA, off_skip;
 };
 
 // Comparator mode (CBSG = false): nibble of element d at cycle l is +1 for r_l < beta_d,
@@ -283,19 +283,20 @@ __device__ __forceinline__ void mplanes_block(const MPlaneArgs &a, uint8_t *ws, 
     }
 }
 
-template <int POL, bool CBSG>
-__global__ __launch_bounds__(256) void k_mplanes(MPlaneArgs a, uint8_t *ws) {
+// both sides in one launch: blocks [0, nA) are A's grid (gxA x gy x batch), the rest B's (gxB x gy
+// x nbB), so B's blocks fill A's last wave
+template <int POL>
+__global__ __launch_bounds__(256) void k_mplanes(MPlaneArgs a, MPlaneArgs bb, int gxA, int gxB, int gy, int nA,
+                                                 uint8_t *ws) {
     __shared__ MPlaneShared sh;
-    mplanes_block<POL, CBSG>(a, ws, sh, blockIdx.x, blockIdx.y, blockIdx.z);
-}
-
-template <bool CBSG>
-static void launch_mplanes_side(int polarity, dim3 grid, const MPlaneArgs &pa, uint8_t *ws,
-                                hipStream_t st) {
-    if (polarity == SC_BIPOLAR_XNOR)
-        hipLaunchKernelGGL((k_mplanes<SC_BIPOLAR_XNOR, CBSG>), grid, dim3(256), 0, st, pa, ws);
-    else
-        hipLaunchKernelGGL((k_mplanes<SC_UNIPOLAR_AND_SM, CBSG>), grid, dim3(256), 0, st, pa, ws);
+    if (a.off_skip != 0 && *ws_ptr<uint32_t>(ws, a.off_skip) != 0u) return;
+    const int bid = blockIdx.x;
+    if (bid < nA) {
+        mplanes_block<POL, true>(a, ws, sh, bid % gxA, (bid / gxA) % gy, bid / (gxA * gy));
+    } else {
+        const int v = bid - nA;
+        mplanes_block<POL, false>(bb, ws, sh, v % gxB, (v / gxB) % gy, v / (gxB * gy));
+    }
 }
 
 hipError_t launch_mplanes(const sc_gemm_desc &d, const Layout &lay, const int8_t *A,
@@ -321,10 +322,8 @@ hipError_t launch_mplanes(const sc_gemm_desc &d, const Layout &lay, const int8_t
     pa.off_planes = lay.off_Ap;
     pa.off_r = lay.off_rA;
     pa.off_CA = lay.off_CA;
+    pa.off_skip = lay.off_skip;
     const dim3 gA((unsigned)(lay.MT * pa.nchunk), qgroups, (unsigned)d.batch);
-    launch_mplanes_side<true>(d.polarity, gA, pa, ws, st);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
 
     MPlaneArgs pb = pa;
     pb.X = B;
@@ -340,7 +339,13 @@ hipError_t launch_mplanes(const sc_gemm_desc &d, const Layout &lay, const int8_t
     pb.off_r = lay.off_rB;
     pb.off_CA = 0;
     const dim3 gB((unsigned)(lay.NT * pb.nchunk), qgroups, (unsigned)lay.nbB);
-    launch_mplanes_side<false>(d.polarity, gB, pb, ws, st);
+    const int nA = (int)(gA.x * gA.y * gA.z), nB = (int)(gB.x * gB.y * gB.z);
+    if (d.polarity == SC_BIPOLAR_XNOR)
+        hipLaunchKernelGGL((k_mplanes<SC_BIPOLAR_XNOR>), dim3((unsigned)(nA + nB)), dim3(256), 0, st, pa, pb,
+                           (int)gA.x, (int)gB.x, (int)qgroups, nA, ws);
+    else
+        hipLaunchKernelGGL((k_mplanes<SC_UNIPOLAR_AND_SM>), dim3((unsigned)(nA + nB)), dim3(256), 0, st, pa, pb,
+                           (int)gA.x, (int)gB.x, (int)qgroups, nA, ws);
     return hipGetLastError();
 }
 
@@ -680,6 +685,7 @@ __device__ __forceinline__ void mstage(int64_t st, int64_t nst, int64_t k0, int6
 // element e of lane l is row 8*(e/4) + 4*(l/32) + e%4, column l%32 of its 32x32 block.
 template <bool BIP, bool SPLIT, int WB>
 __global__ __launch_bounds__(256, 2) void k_mgemm(MGemmArgs g, Layout lay, uint8_t *ws) {
+    if (not_serving(lay, ws)) return;
     constexpr int BUF = MTile<WB>::BUF, NCB = MTile<WB>::NCB;
     __shared__ u4 smem[2 * BUF];
     const int NTW = lay.NT / (WB / BN);
@@ -782,6 +788,7 @@ __global__ __launch_bounds__(256, 2) void k_mgemm(MGemmArgs g, Layout lay, uint8
 // rows and columns are dropped only at the decode.
 template <bool BIP, int WB>
 __global__ __launch_bounds__(256) void k_mgemm_reduce(MGemmArgs g, Layout lay, uint8_t *ws) {
+    if (not_serving(lay, ws)) return;
     constexpr int NK = 32 * (WB / 4) / 256;           // row x column-quad items per thread
     const int NTW = lay.NT / (WB / BN);
     const int tile = blockIdx.x >> 2, quarter = blockIdx.x & 3;
@@ -1310,6 +1317,7 @@ __device__ __forceinline__ bool q_unit(const MGemmArgs &g, const Layout &lay, ui
 // units beyond those (a grid sized for a larger split) return at once.
 template <bool BIP>
 __global__ __launch_bounds__(256, 1) void k_qgemm(MGemmArgs g, Layout lay, uint8_t *ws) {
+    if (not_serving(lay, ws)) return;
     static_assert(QKS % 2 == 0, "the fragment sets alternate within a stage");
     __shared__ u4 smem[QNBUF * QBUF];
     __shared__ DecodeLds dl;                          // filled after the k loop
@@ -1429,6 +1437,7 @@ struct PQuad<true> {
 };
 template <bool BIP, int NK, int PR, int PC, bool P16>
 __global__ __launch_bounds__(256) void k_qgemm_reduce(MGemmArgs g, Layout lay, uint8_t *ws) {
+    if (not_serving(lay, ws)) return;
     constexpr bool TALL = PR == TROWS;        // tiles of k_tgemm, all split alike
     constexpr int QPT = PR * PC / 4;          // quads per tile
     constexpr int BPT = QPT / (256 * NK);     // blocks per tile
@@ -1602,11 +1611,12 @@ __device__ __forceinline__ uint32_t r_entry(const uint2 (&slots)[8], int side, i
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         const uint2 t = slots[j];
-        const int cycles = (int)(t.x >> 9);
+        const int cycles = (int)((t.x >> 9) & 7u);
         int sum;
         if ((int)((t.x >> 8) & 1u) == side) {
+            // (+-1 from one class twice; two classes with C-BSG)
             sum = n >= (int)(t.x & 255u) ? 1 : 0;
-            if (BIP) sum = 2 * sum - 1;
+            if (BIP) sum += (n >= (int)(t.x >> 16) ? 1 : 0) - 1;
             if (cycles == 0) sum = 0;
         } else {
             sum = 0;
@@ -1809,11 +1819,14 @@ __device__ void prep_block(const RChunkArgs &a, const Layout &lay, uint8_t *ws, 
     const int64_t W1 = lay.narrow ? RW1_NARROW : 1, W2 = lay.narrow ? RW2_NARROW : 1, W3 = lay.narrow ? RW3_NARROW : 1;
     // the status words from the batch entries' records
     int bad = 0, longest = 0;
+    bool serves = lay.cbsg != 0;       // (C-BSG tables: every row valid and of L_max cycles)
     for (int b = tid; b < a.batch; b += 256) {
         const int4 r = ws_ptr<int4>(ws + (size_t)b * lay.stride_batchA, lay.off_pair)[npairs];
         bad |= r.x;
         longest = max(longest, r.y);
+        serves = serves && r.x == 0 && r.z == L_max;
     }
+    serves = !__syncthreads_or(!serves);
     if (tid == 0) spair[0] = make_int4(0, 0, 0, 0);
     __syncthreads();
     if (bad != 0) atomicOr(&spair[0].x, bad);
@@ -1823,6 +1836,13 @@ __device__ void prep_block(const RChunkArgs &a, const Layout &lay, uint8_t *ws, 
         uint32_t *status = ws_ptr<uint32_t>(ws, lay.off_status);
         status[0] = (uint32_t)spair[0].x;
         status[1] = (uint32_t)spair[0].y;
+        status[3] = serves ? 1u : 0u;
+        if (lay.cbsg) {               // the planes path's (the call's own) status words
+            uint32_t *call = ws_ptr<uint32_t>(ws, 0);
+            call[0] = (uint32_t)spair[0].x;
+            call[1] = (uint32_t)spair[0].y;
+            call[2] = 0u;
+        }
     }
     __syncthreads();
     bool over = false;
@@ -1862,8 +1882,10 @@ __device__ void prep_block(const RChunkArgs &a, const Layout &lay, uint8_t *ws, 
 // a whole table of one side per block took 3 to 4 us each, behind a chain of three loads.
 __device__ void table_block(int u, const RChunkArgs &a, const Layout &lay, uint8_t *ws, uint32_t *sused) {
     const int groups = lay.LBS / 32, tid = threadIdx.x;
-    uint64_t used;
-    if (a.batch == 1) {
+    uint64_t used = 1;
+    if (lay.cbsg) {
+        // (one plan)
+    } else if (a.batch == 1) {
         const int4 r = ws_ptr<int4>(ws, lay.off_pair)[lay.rtiles];
         used = (uint64_t)(uint32_t)r.w << 32 | (uint32_t)r.z;
     } else {
@@ -1902,6 +1924,8 @@ __device__ void table_block(int u, const RChunkArgs &a, const Layout &lay, uint8
 constexpr int RC_ROWS = 64, RC_CH = 8;
 constexpr int RC_CSTRIDE = RC_ROWS * 2 + 1;      // u4 per chunk in LDS (+1: banks shift by chunk)
 __global__ __launch_bounds__(256) void k_rprep(RChunkArgs a, Layout lay, uint8_t *ws) {
+    // (a C-BSG call with other lengths, one batch entry: its chunks go unread)
+    if (lay.cbsg && a.batch == 1 && blockIdx.x != 0 && ws_ptr<int4>(ws, lay.off_pair)[lay.rtiles].z != a.L_max) return;
     __shared__ u4 sm[RC_CH * RC_CSTRIDE];     // (one region for the three kinds of block)
     static_assert(UNIT_PAIRS * sizeof(int4) <= sizeof(sm), "the prep block's pairs fit");
     if (blockIdx.x == 0) {
@@ -2641,6 +2665,7 @@ union RLdsW {
 template <bool BIP>
 __global__ __launch_bounds__(256, 1) void k_rgemm(MGemmArgs g, Layout lay, uint8_t *ws) {
     __shared__ RLdsW sh;
+    if (not_serving(lay, ws)) return;
     if (ws_ptr<uint32_t>(ws, lay.off_status)[2] != 0u) rgemm_body<BIP, true, false, false>(g, lay, ws, sh.m);
     else rgemm_body<BIP, false, false, true>(g, lay, ws, sh.t);
 }
@@ -2649,6 +2674,7 @@ __global__ __launch_bounds__(256, 1) void k_rgemm(MGemmArgs g, Layout lay, uint8
 template <bool BIP>
 __global__ __launch_bounds__(256, 2) void k_rgemm_n(MGemmArgs g, Layout lay, uint8_t *ws) {
     __shared__ RLds<false> sh;
+    if (not_serving(lay, ws)) return;
     if (ws_ptr<uint32_t>(ws, lay.off_status)[2] != 0u) rgemm_body<BIP, true, true, false>(g, lay, ws, sh);
     else rgemm_body<BIP, false, true, false>(g, lay, ws, sh);
 }
@@ -2785,6 +2811,7 @@ template <bool BIP, int C, bool SPLIT>
 __global__ __launch_bounds__(256, 2) void k_tgemm(MGemmArgs g, Layout lay, uint8_t *ws) {
     constexpr int NT = 256, W = 128 * C, AH = TAhead<C>::N;
     __shared__ TLds sh;
+    if (not_serving(lay, ws)) return;
     const int S = SPLIT ? g.S : 1, s = SPLIT ? (int)blockIdx.x % S : 0, tile = (int)blockIdx.x / S;
     const int NTW = (g.N + W - 1) / W, tw = tile % NTW, tb = tile / NTW;
     const int b = tb % g.batch, rt = tb / g.batch, bB = g.nbB == 1 ? 0 : b;

@@ -799,3 +799,38 @@ def test_noalloc_keeps_long_narrow_calls(dev, oracle_mod):
     torch.cuda.synchronize()
     rows = np.union1d(_sample(M, rng, 20), [0, M - 1])
     _compare(g, 0, rows, np.arange(N), out.cpu().numpy(), cnt.cpu().numpy(), oracle_mod, "noalloc long narrow")
+
+
+# C-BSG calls of one row length from 4e11 products on: the tables of the int8-chunk GEMM (bipolar
+# counters k and L - 1 - k share a slot; unipolar slots from the plan) in place of the planes, and
+# the same sizes with other lengths, where the planes serve and the tables return at once.  Odd
+# and even L, the full period, several batch entries, 64 columns, one row short of L_max.
+CBSG_TABLES = [
+    # batch, M, N, K, L_max, lengths, polarity, broadcast_B, seed
+    (2, 3000, 2050, 300, 129, "one", 0, False, 801),
+    (1, 4000, 3000, 288, 128, "one", 1, True, 803),
+    (1, 3001, 2900, 200, 256, "one", 1, False, 805),
+    (1, 3001, 2900, 200, 255, "one", 0, False, 807),
+    (24, 8224, 64, 130, 256, "one", 0, False, 809),
+    (3, 2100, 2050, 300, 129, "short", 0, False, 811),
+    (1, 4000, 3000, 288, 128, "random", 1, False, 813),
+    (2, 3000, 2050, 300, 129, "below", 0, True, 815),
+]
+
+
+@pytest.mark.parametrize("case", CBSG_TABLES, ids=[str(c) for c in CBSG_TABLES])
+def test_cbsg_tables(dev, oracle_mod, case):
+    batch, M, N, K, L_max, kind, pol, bcast, seed = case
+    rng = np.random.default_rng(seed)
+    g = W.random_gemm(rng, batch, M, N, K, L_max, pol, seed, broadcast_B=bcast, uniform_L=L_max)
+    if kind == "short":
+        g.L[batch - 1, M // 2] = L_max - 1
+    elif kind == "below":
+        g.L[:] = L_max - 1
+    elif kind == "random":
+        g.L = rng.integers(0, L_max + 1, g.L.shape).astype(np.int32)
+    _note("cbsg tables %s" % (case,))
+    out, cnt = _run(g, dev, rng=1)
+    for b in sorted({0, batch - 1}):
+        rows = np.union1d(_sample(M, rng, 12), [M // 2])
+        _compare(g, b, rows, np.arange(N), out, cnt, oracle_mod, "cbsg tables%s b%d" % (case, b), rng=1)
