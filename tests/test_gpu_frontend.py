@@ -157,3 +157,50 @@ def test_device_pipeline_with_threshold_table(dev, oracle_mod):
         nz = o_ref != 0
         assert np.all(o[~nz] == 0)
         assert np.max(np.abs(o[nz] - o_ref[nz]) / np.abs(o_ref[nz])) <= 1e-6
+
+
+@pytest.mark.parametrize("K", [1, 3, 4, 255, 256, 257, 768, 769, 1280, 1284, 2047, 2048, 2052, 5000])
+def test_quantize_row_lengths_and_ties(dev, oracle_mod, K):
+    """Every register-held row length and the block per longer row, aligned and not (K, and rows of
+    a wider matrix from an odd column on), at quotients on and beside the halves, where the
+    product with the reciprocal may not decide, and with scales at both ends of fp32."""
+    import torch
+    import paper_2609_32922_amd as scg
+    rng = np.random.default_rng(K)
+    rows = 9
+    X = rng.standard_normal((rows, K)).astype(np.float32)
+    for i, top in enumerate((127.0, 1.0, 3.0e38, 1.3e-36, 2e-43, 0.0)):
+        # quotients k / 2 of the scale top / 127, nudged by up to 2 ulps
+        s = np.float32(top) / np.float32(127)
+        h = (rng.integers(-254, 255, K) * np.float32(0.5)).astype(np.float32) * s
+        h = np.where(rng.random(K) < 0.5, np.nextafter(h, np.float32(0)), h).astype(np.float32)
+        h[rng.integers(K)] = np.float32(top)
+        X[i] = np.clip(h, -np.float32(top), np.float32(top))
+    _note("quantize K=%d" % K)
+    for per_tensor in (False, True):
+        Q, s, m = scg.quantize(_t(X, dev), per_tensor=per_tensor, want_rowmax=True)
+        ref = oracle_mod.quantize_tensor_fp32(X) if per_tensor else oracle_mod.quantize_rows_fp32(X)
+        assert np.array_equal(Q.cpu().numpy(), ref[0]) and np.array_equal(s.cpu().numpy(), ref[1])
+    # rows inside wider matrices, from a column that is no multiple of 4 on: single elements
+    wide = torch.zeros((rows, K + 11), device=dev)
+    wide[:, 5:5 + K] = _t(X, dev)
+    Qw = torch.full((rows, K + 7), 55, dtype=torch.int8, device=dev)
+    sw = torch.empty(rows, device=dev)
+    rc = scg.sc_quantize(1, rows, K, wide.data_ptr() + 5 * 4, K + 11, 0, 0, Qw.data_ptr() + 3, K + 7, 0, sw.data_ptr(), 0,
+                         rows, int(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0
+    ref = oracle_mod.quantize_rows_fp32(X)
+    Qw = Qw.cpu().numpy()
+    assert np.array_equal(Qw[:, 3:3 + K], ref[0]) and np.array_equal(sw.cpu().numpy(), ref[1])
+    assert (Qw[:, :3] == 55).all() and (Qw[:, 3 + K:] == 55).all()
+
+
+@pytest.mark.parametrize("M", [1, 1023, 1024, 1025, 20481, 40000])
+def test_mp_lengths_many_blocks(dev, oracle_mod, M):
+    import paper_2609_32922_amd as scg
+    g = np.random.default_rng(M).gamma(2.0, 1.0, (2, M)).astype(np.float32)
+    tau, ladder = [0.5, 0.25, 0.1], [256, 128, 64, 32]
+    _note("mp lengths M=%d" % M)
+    L = scg.mp_lengths(_t(g, dev), tau, ladder).cpu().numpy()
+    for b in range(2):
+        assert np.array_equal(L[b], oracle_mod.mp_lengths_fp32(g[b], tau, ladder))
