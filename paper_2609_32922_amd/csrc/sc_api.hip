@@ -186,6 +186,7 @@ static bool layout_with(const sc_gemm_desc &d, int cus, int spend, bool cbsg, La
     l.tshift = tall ? 6 : 8;
     l.rtiles = tall ? (d.M + TROWS - 1) / TROWS : l.MT / 2;
     l.rslots = l.narrow || tall ? 0 : RSLOTS;
+    l.halves = l.rgen && !l.narrow && !tall;
     l.KC = (d.K + 31) / 32;
     l.LBS = (int)round_up(d.L_max, LCH);
     l.nbB = (d.strideB == 0) ? 1 : d.batch;
@@ -375,7 +376,7 @@ static bool layout_with(const sc_gemm_desc &d, int cus, int spend, bool cbsg, La
         // its decode and a minimum step: W <= w1 wmax.  A range of cost T = ceil(W / sl) <=
         // w1 wmax / sl + 1 holds at most T / w2 + 1 steps, which must stay below RSTEP_EXACT;
         // the 256 x 64 blocks' ranges hold up to twice T.)
-        const int64_t w1 = l.narrow ? RW1_NARROW : 1, w2 = l.narrow ? RW3_NARROW : 1;   // (w2: the lightest step)
+        const int64_t w1 = l.narrow ? RW1_NARROW : RW1_WIDE, w2 = l.narrow ? RW3_NARROW : RW2_WIDE;   // (w2: the lightest step)
         const int64_t wmax = tiles * ((int64_t)l.KC * (l.LBS / 32) + 7);
         const int64_t den = (w2 * (RSTEP_EXACT - 2) - 1) / (l.narrow ? 2 : 1);
         int64_t sl = l.q_slots;

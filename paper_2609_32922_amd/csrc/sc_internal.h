@@ -131,7 +131,9 @@ constexpr int64_t RSTEP_EXACT = MFMA_EXACT / (32 * 32);   // int8-chunk GEMM chu
 // Cost of a chunk step of the 256 x 64 int8-chunk GEMM in the work division, while all of a
 // wave's row blocks run (RW1) and once only the first two do (RW2): half the MFMAs and two
 // thirds of the table reads (measured on attention-V: 9/16 of a full step's time, against
-// 8/16, 10/16 and 11/16); the 256 x 256 blocks weigh every step 1
+// 8/16, 10/16 and 11/16).  The 256 x 256 blocks: a step of a group of 32 slots, and of a last
+// group of at most 16 (half the MFMAs, the same number of wider-spread table reads)
+constexpr int64_t RW1_WIDE = 8, RW2_WIDE = 5;
 constexpr int64_t RW1_NARROW = 16, RW2_NARROW = 9;
 // ... and once only the first one does (RW3: one A read and two MFMAs per k-step, beside two B
 // reads; measured on attention-V: 5/16 against 3, 4, 7 and 9); the smallest of the three
@@ -217,6 +219,7 @@ struct Layout {
     int tshift, rtiles;    // rgen: rows of a tile (256, or 64 with tall) as a shift, and row tiles
     int cbsg;          // rgen: the tables of a C-BSG call whose rows all have L_max cycles (below)
     size_t off_skip;   // planes of such a call: a word that is nonzero when its tables serve (0: none)
+    int halves;        // 256 x 256 blocks of rgen: a tile's last group of at most 16 slots runs half the MFMAs
     int narrow;        // rgen with N <= 64: blocks of 256 rows x 64 columns
     int rslots;        // rgen: tables masked to a row length per cycle group (0 when narrow)
     int KC;            // 32-element chunks per row, ceil(K/32)

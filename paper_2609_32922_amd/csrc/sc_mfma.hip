@@ -1684,12 +1684,16 @@ __device__ __forceinline__ u4 r_half(const int8_t *xrow, int d0, int K, bool vec
     return v;
 }
 
+// cost of a chunk step of phase p (below)
+__device__ __forceinline__ int64_t unit_weight(const Layout &lay, int p) {
+    return lay.narrow ? (p == 1 ? RW1_NARROW : p == 2 ? RW2_NARROW : RW3_NARROW) : p == 1 ? RW1_WIDE : RW2_WIDE;
+}
 constexpr int UNIT_PAIRS = 1024;   // pairs whose steps the division keeps in LDS
 // Chunk steps of a pair's tiles at weight W1, W2 and W3 (below), and its plan, from its slots ps
 __device__ __forceinline__ int4 pair_steps(int4 ps, int b, int tp, const RChunkArgs &a, const Layout &lay, uint8_t *ws) {
     uint8_t *wsb = ws + (size_t)b * lay.stride_batchA;
-    const int g0 = ps.x;
-    int g1 = g0, g2 = g0;
+    const int g0 = ps.x & 0xFFFF;
+    int g1 = lay.halves ? g0 - (ps.x >> 16) : g0, g2 = g0;
     if (lay.narrow) {
         // (padding rows have length 0 in the layout)
         const int32_t *Ls = ws_ptr<int32_t>(wsb, lay.off_Ls) + tp * 256;
@@ -1738,7 +1742,7 @@ __device__ void units_division(const RChunkArgs &a, const Layout &lay, uint8_t *
     const int NTW = lay.NT / 2, npairs = lay.MT / 2, slots = lay.sk_slots;
     const int tiles = a.batch * npairs * NTW;
     const int per = (tiles + 255) / 256, t0 = min(tid * per, tiles), t1 = min(t0 + per, tiles);
-    const I W1 = lay.narrow ? RW1_NARROW : 1, W2 = lay.narrow ? RW2_NARROW : 1, W3 = lay.narrow ? RW3_NARROW : 1;
+    const I W1 = (I)unit_weight(lay, 1), W2 = (I)unit_weight(lay, 2), W3 = (I)unit_weight(lay, 3);
     const I E = 5 * W1;
     auto cost = [&](int4 n) -> I {
         const I c = n.x * W1 + n.y * W2 + n.z * W3;
@@ -1816,7 +1820,7 @@ __device__ void units_division(const RChunkArgs &a, const Layout &lay, uint8_t *
 // group than masked tables, and the work division
 __device__ void prep_block(const RChunkArgs &a, const Layout &lay, uint8_t *ws, int4 *spair) {
     const int npairs = lay.rtiles, NTW = lay.NT / 2, L_max = a.L_max, tid = threadIdx.x;
-    const int64_t W1 = lay.narrow ? RW1_NARROW : 1, W2 = lay.narrow ? RW2_NARROW : 1, W3 = lay.narrow ? RW3_NARROW : 1;
+    const int64_t W1 = unit_weight(lay, 1), W2 = unit_weight(lay, 2), W3 = unit_weight(lay, 3);
     // the status words from the batch entries' records
     int bad = 0, longest = 0;
     bool serves = lay.cbsg != 0;       // (C-BSG tables: every row valid and of L_max cycles)
@@ -1859,7 +1863,10 @@ __device__ void prep_block(const RChunkArgs &a, const Layout &lay, uint8_t *ws, 
         int nd = save % 32 != 0 ? pi.z : pi.w;
         if (pi.x >= L_max && (save % 32 != 0 || L_max % 32 != 0)) --nd;
         over = over || nd > lay.rslots;
-        const int4 ps = make_int4((slot_length(pi.x, save, top, L_max) + 31) / 32, k, save, top);
+        // (256 x 256 blocks: the tile's last group may need half the MFMAs)
+        const int most = pi.x >= L_max ? h.z : slot_length(pi.x, save, top, L_max), left = most % 32;
+        const bool half = lay.halves && left > 0 && left <= 16;
+        const int4 ps = make_int4((most + 31) / 32 | (half ? 1 << 16 : 0), k, save, top);
         *pair = ps;
         if (lay.vsplit) {
             const int4 n = pair_steps(ps, b, tp, a, lay, ws);
@@ -2030,8 +2037,15 @@ __device__ __forceinline__ void r_load_ent(u4 (&ent)[512 / NT], const u4 *tab, i
 // address 65536 + byte * 256 + (k * RREP1 + copy) * 16.  Each store instruction rotates the
 // copy by the lane, so that a wave's 64 lanes spread over 8 (masked: 4) 16-byte columns of the
 // 256-byte rows instead of all falling into one.
-template <int NT>
-__device__ __forceinline__ void r_fill_lut(u4 *lut, const u4 (&ent)[512 / NT], int tid, uint32_t rems) {
+// HALF: a group of which at most the first 16 slots are in use (a tile's last one): each entry is its
+// first half twice, so that 8-byte reads have 16 copies (masked: 8) to spread over.
+constexpr int RHS = RCH / 2;
+__device__ __forceinline__ u4 r_twice(u4 x) { return u4{x[0], x[1], x[0], x[1]}; }
+template <int NT, bool HALF = false>
+__device__ __forceinline__ void r_fill_lut(u4 *lut, const u4 (&ent0)[512 / NT], int tid, uint32_t rems) {
+    u4 ent[512 / NT];
+#pragma unroll
+    for (int i = 0; i < 512 / NT; ++i) ent[i] = HALF ? r_twice(ent0[i]) : ent0[i];
     constexpr int BPT = 256 / NT;     // bytes per thread
     const int lane = tid & 63;
 #pragma unroll
@@ -2045,7 +2059,7 @@ __device__ __forceinline__ void r_fill_lut(u4 *lut, const u4 (&ent)[512 / NT], i
         }
         int k = 0;
         for (uint32_t m = rems; m != 0u; m &= m - 1u, ++k) {
-            const u4 xm = ent[i] & r_len_mask(__builtin_ctz(m), 0);
+            const u4 lm = r_len_mask(__builtin_ctz(m), 0), xm = ent[i] & (HALF ? r_twice(lm) : lm);
 #pragma unroll
             for (int j = 0; j < RREP1; ++j) row[256 * 16 + k * RREP1 + ((j + lane) & (RREP1 - 1))] = xm;
         }
@@ -2192,6 +2206,23 @@ __device__ __forceinline__ void r_frags_q(const RSrc &q, const RData<NB> &d, con
     if (MASK) f.a[0] &= m[0];
 }
 
+// Fragments of k-step E of a half group: the 16 slots of elements 2E and 2E + 1, an 8-byte read each
+// (half the k-steps, and the MFMAs, of a group of 32 slots)
+template <int E>
+__device__ __forceinline__ u4 r_look2(const RSrc &q, const u4 &v, uint32_t lo) {
+    constexpr uint32_t s0 = 0x0C020000u | ((4u + (2 * E & 3)) << 8), s1 = 0x0C020000u | ((4u + ((2 * E + 1) & 3)) << 8);
+    const u2 x = *reinterpret_cast<const u2 *>(q.lut + __builtin_amdgcn_perm(v[(2 * E) >> 2], lo, s0));
+    const u2 y = *reinterpret_cast<const u2 *>(q.lut + __builtin_amdgcn_perm(v[(2 * E) >> 2], lo, s1));
+    return u4{x[0], x[1], y[0], y[1]};
+}
+template <int E>
+__device__ __forceinline__ void r_frags2(const RSrc &q, const RData<4> &d, RFrags<4> &f) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) f.b[c] = r_look2<E>(q, d.b[c], q.loB);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) f.a[i] = r_look2<E>(q, d.a[i], q.loA[i]);
+}
+
 // Stage S (k-steps 2S, 2S+1) of a chunk: fragment set 0 holds k-step 2S on entry and the
 // next k-step (2S + 2, or the next chunk's first) on exit; stage 0 loads the next chunk.
 // A chunk has KS / 2 stages (RShape).
@@ -2204,14 +2235,14 @@ __device__ __forceinline__ void r_mask(const u4 (&m)[4], RFrags<NB> &f) {
 }
 
 // a quarter holds 2 NB MFMAs (A blocks 2h, 2h + 1 with every B block)
-template <bool LOADS, int NB>
+template <bool LOADS, int NB, int R = 1>
 __device__ __forceinline__ void r_quarter_reads() {
-    // the 4 + NB table reads of the next fragments with their address bytes
+    // the table reads of the next 4 + NB fragments (R each) with their address bytes
 #pragma unroll
     for (int k = 0; k < 2 * NB; ++k) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // MFMA
-        __builtin_amdgcn_sched_group_barrier(0x002, 1, 0);   // VALU (address)
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // LDS read
+        __builtin_amdgcn_sched_group_barrier(0x002, R, 0);   // VALU (address)
+        __builtin_amdgcn_sched_group_barrier(0x100, R, 0);   // LDS read
         if (LOADS) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // global load
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -2359,6 +2390,44 @@ __device__ __forceinline__ void r_chunks(const RSrc &q, int c, int ce, RData<NB>
     }
 }
 
+// Stage S (k-steps 2S, 2S + 1 of 8) of a chunk of a half group, and its chunks, as r_stage and r_chunks
+template <int S, bool MASK>
+__device__ __forceinline__ void r_stage2(const RSrc &q, int cnext, RData<4> &cur, RData<4> &nxt, const u4 (&m)[4],
+                                         const bool (&fin)[4], v16f (&acc)[4][4], RFrags<4> (&f)[2]) {
+    if (S == 0) r_load(q, cnext, nxt);
+    r_frags2<2 * S + 1>(q, cur, f[1]);
+    q_mma_half(acc, f[0], 0);
+    r_quarter_reads<S == 0, 4, 2>();
+    if (MASK) r_mask(m, f[1]);
+    q_mma_half(acc, f[0], 1);
+    r_quarter_masks<MASK, 4>();
+    if (S < 3) {
+        r_frags2<(2 * S + 2) & 7>(q, cur, f[0]);
+    } else {
+        if (!MASK) r_finish(nxt, fin);
+        r_frags2<0>(q, nxt, f[0]);
+    }
+    q_mma_half(acc, f[1], 0);
+    r_quarter_reads<false, 4, 2>();
+    if (MASK) r_mask(m, f[0]);
+    q_mma_half(acc, f[1], 1);
+    r_quarter_masks<MASK, 4>();
+}
+template <bool MASK>
+__device__ __forceinline__ void r_chunks2(const RSrc &q, int c, int ce, RData<4> &cur, RData<4> &nxt, const u4 (&m)[4],
+                                          const bool (&fin)[4], v16f (&acc)[4][4], RFrags<4> (&f)[2]) {
+    r_frags2<0>(q, cur, f[0]);
+    if (MASK) r_mask(m, f[0]);
+    for (; c < ce; ++c) {
+        const int x = c + 1 < q.KC ? c + 1 : 0;
+        r_stage2<0, MASK>(q, x, cur, nxt, m, fin, acc, f);
+        r_stage2<1, MASK>(q, x, cur, nxt, m, fin, acc, f);
+        r_stage2<2, MASK>(q, x, cur, nxt, m, fin, acc, f);
+        r_stage2<3, MASK>(q, x, cur, nxt, m, fin, acc, f);
+        cur = nxt;
+    }
+}
+
 // One work unit, as in k_qgemm: tile `tile` over chunk steps [s, s + 1) / S of the pair's
 // (group, chunk) steps, whole tiles decoded here, parts stored as partial sums.  Rows that
 // have ended read the padding byte, whose table row is zero; a row that ends inside a
@@ -2473,7 +2542,7 @@ __device__ __forceinline__ void rgemm_body(const MGemmArgs &g, const Layout &lay
         r_load_ent<NT>(ent, rtab + (size_t)(xs / q.KC) * 512, tid);
         r_load(q, (int)(xs % q.KC), cur);
     }
-    const int ngroups = ps.x;
+    const int ngroups = ps.x & 0xFFFF, full = NARROW ? ngroups : ngroups - (ps.x >> 16);   // (groups of 32 slots)
     auto slen = [&](int L) { return slot_length(L, ps.z, ps.w, g.L_max); };
 
     const int64_t nch = (int64_t)ngroups * g.KC;
@@ -2512,7 +2581,7 @@ __device__ __forceinline__ void rgemm_body(const MGemmArgs &g, const Layout &lay
     const int Lh0 = wave_uniform(p0 >= 0 ? slen(l0) : 0), Lh1 = wave_uniform(p1 >= 0 ? slen(l1) : 0);
     const int Lh01 = wave_uniform(p01 >= 0 ? slen(l01) : 0);
 
-    const uint32_t lrep = 16u * (uint32_t)(lane & (RREP - 1));
+    const uint32_t lrep = 16u * (uint32_t)(lane & (RREP - 1)), lrep2 = 8u * (uint32_t)(lane & (2 * RREP - 1));
     q.loB = lrep + 16u * RREP;
     q.lut = reinterpret_cast<const char *>(lut);
 
@@ -2530,11 +2599,12 @@ __device__ __forceinline__ void rgemm_body(const MGemmArgs &g, const Layout &lay
     // loops, so that a later phase holds none of an earlier one's registers.
     if (NARROW && !split) d_put(dl, drow, tid);   // (read after the epilogue's first barrier)
     int64_t x = x0;
-    auto group_start = [&](int G, int64_t xe, bool (&fin)[4]) {
+    auto group_start = [&](int G, int64_t xe, bool (&fin)[4], auto half) {
+        constexpr bool HALF = decltype(half)::value;
         const uint32_t rm = TABLES ? rems[G] : 0u;
         // every read of the previous group's table is done before it is replaced
         __syncthreads();
-        r_fill_lut<NT>(lut, ent, tid, rm);
+        r_fill_lut<NT, HALF>(lut, ent, tid, rm);
         if (xe < x1) {
             r_load_ent<NT>(ent, rtab + (size_t)(G + 1) * 512, tid);
         }
@@ -2545,32 +2615,46 @@ __device__ __forceinline__ void rgemm_body(const MGemmArgs &g, const Layout &lay
         for (int i = 0; i < 4; ++i) {
             const int rem = Lr[i] - RCH * G;
             fin[i] = rem <= 0;
-            q.loA[i] = lrep;
+            q.loA[i] = HALF ? lrep2 : lrep;
             if (MASK) {
                 m[i] = r_len_mask(Lr[i], G);
+                if (HALF) m[i] = r_twice(m[i]);
             } else if (TABLES && rem > 0 && rem < RCH) {
                 const uint32_t k = (uint32_t)__popc(rm & ((1u << rem) - 1u));
-                q.loA[i] = 0x10000u | (16u * (k * RREP1 + (uint32_t)(lane & (RREP1 - 1))));
+                q.loA[i] = 0x10000u | (HALF ? 64u * k + 8u * (uint32_t)(lane & (2 * RREP1 - 1))
+                                            : 16u * (k * RREP1 + (uint32_t)(lane & (RREP1 - 1))));
             }
         }
+        if (HALF) q.loB = lrep2 + 16u * RREP;
         if (!MASK) r_finish(cur, fin);
     };
+    constexpr std::false_type whole;
     for (; x < x1;) {
         const int G = (int)(x / g.KC);
-        if (SKIP && Lh1 <= RCH * G) break;
+        if (SKIP ? Lh1 <= RCH * G : G >= full) break;
         const int64_t xe = min(x1, (int64_t)(G + 1) * g.KC);
         bool fin[4];
-        group_start(G, xe, fin);
+        group_start(G, xe, fin, whole);
         r_frags<0, MASK>(q, cur, m, f[0]);
         r_chunks<MASK>(q, (int)(x - (int64_t)G * g.KC), (int)(xe - (int64_t)G * g.KC), cur, nxt, m, fin, acc, f);
         x = xe;
+    }
+    // (256 x 256) the tile's last group, at most 16 of its slots in use
+    if constexpr (!NARROW) {
+        if (x < x1) {
+            bool fin[4];
+            group_start(ngroups - 1, x1, fin, std::true_type{});
+            r_chunks2<MASK>(q, (int)(x - (int64_t)(ngroups - 1) * g.KC), (int)(x1 - (int64_t)(ngroups - 1) * g.KC), cur, nxt, m,
+                            fin, acc, f);
+            x = x1;
+        }
     }
     for (; SKIP && x < x1;) {
         const int G = (int)(x / g.KC);
         if (Lh01 <= RCH * G) break;
         const int64_t xe = min(x1, (int64_t)(G + 1) * g.KC);
         bool fin[4];
-        group_start(G, xe, fin);
+        group_start(G, xe, fin, whole);
         r_frags_h<0, MASK>(q, cur, m, f[0]);
         r_chunks_h<MASK>(q, (int)(x - (int64_t)G * g.KC), (int)(xe - (int64_t)G * g.KC), cur, nxt, m, fin, acc, f);
         x = xe;
@@ -2580,7 +2664,7 @@ __device__ __forceinline__ void rgemm_body(const MGemmArgs &g, const Layout &lay
         if (Lh0 <= RCH * G) break;
         const int64_t xe = min(x1, (int64_t)(G + 1) * g.KC);
         bool fin[4];
-        group_start(G, xe, fin);
+        group_start(G, xe, fin, whole);
         r_frags_q<0, MASK>(q, cur, m, f[0]);
         r_chunks_q<MASK>(q, (int)(x - (int64_t)G * g.KC), (int)(xe - (int64_t)G * g.KC), cur, nxt, m, fin, acc, f);
         x = xe;
