@@ -834,3 +834,38 @@ def test_cbsg_tables(dev, oracle_mod, case):
     for b in sorted({0, batch - 1}):
         rows = np.union1d(_sample(M, rng, 12), [M // 2])
         _compare(g, b, rows, np.arange(N), out, cnt, oracle_mod, "cbsg tables%s b%d" % (case, b), rng=1)
+
+
+# 256 x 256 blocks (calls large enough for them): both variants (a fragment mask per row; masked tables
+# for at most four lengths a pair), last groups of at most 16 slots and longer ones, whole tiles,
+# ranges and parts, ragged M, N and K.
+WIDE = [
+    # batch, M, N, K, L_max, lengths, hint, polarity, broadcast_B, seed
+    (2, 2500, 2500, 600, 128, "random", 60, 0, False, 851),
+    (2, 2500, 2500, 600, 128, "ladder", 60, 1, True, 853),
+    (1, 5000, 2600, 500, 256, "random", 80, 1, False, 855),
+    (1, 5000, 2600, 500, 256, "below", 0, 0, False, 857),     # one length short of L_max
+    (2, 2600, 2600, 520, 160, "one", 0, 0, False, 859),       # 103 slots: a last group of 7
+    (1, 4100, 4100, 300, 128, "one", 0, 1, False, 861),       # parts of int16 counts
+    (1, 4100, 3300, 770, 200, "ladder", 60, 0, False, 863),
+]
+
+
+@pytest.mark.parametrize("case", WIDE, ids=[str(c) for c in WIDE])
+def test_blocks_of_256(dev, oracle_mod, case):
+    batch, M, N, K, L_max, kind, hint, pol, bcast, seed = case
+    rng = np.random.default_rng(seed)
+    g = W.random_gemm(rng, batch, M, N, K, L_max, pol, seed, broadcast_B=bcast, uniform_L=L_max)
+    if kind == "random":
+        g.L = (L_max * rng.random(g.L.shape) ** 2).astype(np.int32)
+        g.L[:, :2] = (0, L_max)
+    elif kind == "ladder":
+        g.L = rng.choice([L_max, 3 * L_max // 4, L_max // 2, L_max // 3], g.L.shape).astype(np.int32)
+    elif kind == "below":
+        g.L[:] = L_max - 3
+    _note("256-row blocks %s" % (case,))
+    out, cnt = _run(g, dev, L_hint=hint)
+    for b in range(batch):
+        order = np.argsort(-g.L[b], kind="stable")
+        rows = np.unique(np.concatenate([_sample(M, rng, 8), order[::max(1, M // 24)], order[:3], order[-3:]]))
+        _compare(g, b, rows, np.arange(N), out, cnt, oracle_mod, "wide%s b%d" % (case, b))
