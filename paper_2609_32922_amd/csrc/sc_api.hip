@@ -161,8 +161,11 @@ static bool layout_with(const sc_gemm_desc &d, int cus, int spend, bool cbsg, La
     if (few) w.Smin = (int)((rsteps + RSTEP_EXACT - 1) / RSTEP_EXACT);
     if (few && round_up(d.L_max, MSTEP) * l.KQP * 4 > SC_KL_LIMIT) return false;
     if (w.Smin < 1) w.Smin = 1;
+    // (an output past 31-bit offsets is decoded by the split-sum pass, so it takes parts)
+    const bool far = ((int64_t)(d.M - 1) * d.ldo + d.N) * 4 > TALL_BYTES;
+    if (far && few && w.Smin < 2) w.Smin = 2;
     int tallC = 0, tallS = 1;
-    if (lfsr && !l.narrow && !l.fused && (few || spend != LAY_LEAST)) {
+    if (lfsr && !l.narrow && !l.fused && (few || (spend != LAY_LEAST && !far))) {
         double best = few ? 1e30 : est_wide(w);
         for (int c : {1, 2, 4, 5})
             for (int S = w.Smin; S <= (c == 5 ? 1 : w.Smin > MAX_SPLIT ? w.Smin : MAX_SPLIT); ++S) {

@@ -121,6 +121,7 @@ constexpr int PLAN_GROUPS = 512; // most (plan, group) tables of a call, 8 KiB e
 constexpr int UNIT_PLAN = 1 << 24;   // a unit's partial index (below 2^22) and plan in one word
 
 constexpr int TROWS = 64;        // rows of a block of k_tgemm
+constexpr int64_t TALL_BYTES = 0x7FFFFFFC;   // largest output of a batch entry that k_tgemm decodes itself
 constexpr int OCH = 8;           // octets per block of the nibble-plane generator
 constexpr int RSLOTS = 4;        // int8-chunk GEMM: tables masked to a row length, per cycle group
 constexpr int64_t MFMA_EXACT = 1ll << 24;   // products one fp32 accumulator sums exactly

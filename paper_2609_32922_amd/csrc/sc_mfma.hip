@@ -358,6 +358,7 @@ struct MGemmArgs {
     int64_t strideSA, strideSB, strideO, ldo;
     float *out;
     int32_t *counts;
+    int64_t obytes;         // bytes of one batch entry of the output
     int vec_out, vec_cnt;   // four adjacent columns of out (counts) at a multiple of 4 are 16-byte aligned
 };
 
@@ -2884,9 +2885,12 @@ __device__ __forceinline__ void t_group(const TSrc<C> &q, int h, int he, TData<C
 
 struct TLds {
     u4 lut[256 * 16];
-    int32_t row[TROWS], len[TROWS];
-    float f[TROWS];
+    alignas(16) int32_t row[TROWS];
+    alignas(16) int32_t len[TROWS];
+    alignas(16) float f[TROWS];
 };
+// a byte offset past the end of any output of TALL_BYTES (twice it stays below 2^32)
+constexpr uint32_t T_DROP = (uint32_t)TALL_BYTES;
 
 // One unit: part s of S of the chunk steps of tile `tile` (row tile rt of batch entry b x column tile
 // tw; the row tiles with the longest rows first), decoded here when S = 1, else stored as a partial
@@ -3005,28 +3009,46 @@ __global__ __launch_bounds__(256, 2) void k_tgemm(MGemmArgs g, Layout lay, uint8
     }
     __syncthreads();
     if (!act) return;
-    // a store instruction writes 32 adjacent columns of two rows, straight from the accumulators
+    // A store instruction writes 32 adjacent columns of two rows, straight from the accumulators, as
+    // buffer stores: a 32-bit offset per row, and one past the end (dropped) for padding rows and columns
+    // past N, so that no store sits behind a branch (branches and 64-bit addresses: 20 us a tile of
+    // ViT-L/14 Q.K^T, the call 201 us against 161).
     float sBj[C];
+    uint32_t coff[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         const int j = col0 + 32 * c + i32;
         sBj[c] = j < g.N ? g.sB[(size_t)b * g.strideSB + j] : 0.0f;
+        coff[c] = j < g.N ? 4u * (uint32_t)j : T_DROP;
     }
+    const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(g.out + (size_t)b * g.strideO, 0, (int)g.obytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
+        g.counts ? g.counts + (size_t)b * g.strideO : nullptr, 0, g.counts ? (int)g.obytes : 0, 0x00020000);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int r = 32 * i + 8 * (e >> 2) + 4 * grp + (e & 3);
-            const int row = sh.row[r], L = sh.len[r];
-            const float f = sh.f[r];
-            if (row < 0) continue;
-            const size_t off = (size_t)b * g.strideO + (size_t)row * g.ldo + col0 + i32;
+        for (int e4 = 0; e4 < 4; ++e4) {
+            const int r = 32 * i + 8 * e4 + 4 * grp;
+            const int4 row = *reinterpret_cast<const int4 *>(&sh.row[r]), len = *reinterpret_cast<const int4 *>(&sh.len[r]);
+            const float4 f4 = *reinterpret_cast<const float4 *>(&sh.f[r]);
+            const int rows[4] = {row.x, row.y, row.z, row.w}, lens[4] = {len.x, len.y, len.z, len.w};
+            const float f[4] = {f4.x, f4.y, f4.z, f4.w};
 #pragma unroll
-            for (int c = 0; c < C; ++c) {
-                if (col0 + 32 * c + i32 >= g.N) continue;
-                const float P = acc[i][c][e];
-                g.out[off + 32 * c] = (P * f) * sBj[c];
-                if (g.counts) g.counts[off + 32 * c] = L > 0 ? (BIP ? (g.K * L + (int)P) / 2 : (int)P) : 0;
+            for (int k = 0; k < 4; ++k) {
+                // (an offset of T_DROP or more is past the end; the sum of two stays below 2^32)
+                const uint32_t ro4 = rows[k] < 0 ? T_DROP : (uint32_t)rows[k] * (uint32_t)g.ldo * 4u;
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint((acc[i][c][4 * e4 + k] * f[k]) * sBj[c]), ro,
+                                                          ro4 + coff[c], 0, 0);
+                if (g.counts) {
+                    const int L = lens[k], KL = g.K * L;
+#pragma unroll
+                    for (int c = 0; c < C; ++c) {
+                        const int p = (int)acc[i][c][4 * e4 + k];
+                        __builtin_amdgcn_raw_buffer_store_b32((uint32_t)(L > 0 ? (BIP ? (KL + p) / 2 : p) : 0), rc, ro4 + coff[c], 0, 0);
+                    }
+                }
             }
         }
 }
@@ -3083,6 +3105,7 @@ static MGemmArgs make_gemm_args(const sc_gemm_desc &d, const Layout &lay, const 
     g.ldo = d.ldo;
     g.out = out;
     g.counts = counts;
+    g.obytes = d.M > 0 ? ((int64_t)(d.M - 1) * d.ldo + d.N) * 4 : 0;
     g.vec_out = reinterpret_cast<uintptr_t>(out) % 16 == 0 && d.ldo % 4 == 0 && d.strideO % 4 == 0;
     g.vec_cnt = reinterpret_cast<uintptr_t>(counts) % 16 == 0 && d.ldo % 4 == 0 && d.strideO % 4 == 0;
     return g;
