@@ -1954,7 +1954,29 @@ __global__ __launch_bounds__(256) void k_rprep(RChunkArgs a, Layout lay, uint8_t
     uint8_t *wsb = ws + (size_t)b * a.stride_batch[side];
     const int tid = threadIdx.x, hl = tid & 15;         // hl = 2 * chunk + half
     const bool vec = a.vec[side] != 0;
-    for (int pass = 0; pass < RC_ROWS / 16; ++pass) {
+    if (vec && (hl >> 1) < nc && (c0 + (hl >> 1)) * RCH + 16 * (hl & 1) + 16 <= a.K) {
+        // whole 16 bytes of aligned rows: a thread's rows, then all its loads, then its stores (in turn
+        // they took the compensator's layout 12.4 us instead of 10.7)
+        constexpr int NP = RC_ROWS / 16;
+        const int d0 = (c0 + (hl >> 1)) * RCH + 16 * (hl & 1);
+        int src[NP];
+        u4 v[NP];
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const int r = r0 + p * 16 + (tid >> 4);
+            src[p] = side == 0 ? ws_ptr<int32_t>(wsb, a.off_perm)[r] : (r < a.rows[side] ? r : -1);
+        }
+        // (a padding row reads row 0)
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+            v[p] = *reinterpret_cast<const u4 *>(a.X[side] + (size_t)b * a.strideX[side] + (size_t)max(src[p], 0) * a.ld[side] + d0);
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[p][k] = src[p] >= 0 ? r_clamp4(v[p][k]) : 0x80808080u;
+            sm[(hl >> 1) * RC_CSTRIDE + (p * 16 + (tid >> 4)) * 2 + (hl & 1)] = v[p];
+        }
+    } else for (int pass = 0; pass < RC_ROWS / 16; ++pass) {
         const int rl = pass * 16 + (tid >> 4), r = r0 + rl;
         if ((hl >> 1) >= nc) continue;
         const int src = side == 0 ? ws_ptr<int32_t>(wsb, a.off_perm)[r] : (r < a.rows[side] ? r : -1);
