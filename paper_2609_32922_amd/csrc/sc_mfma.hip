@@ -2844,40 +2844,49 @@ __device__ __forceinline__ void t_load(const TSrc<C> &q, int h, TData<C> &d) {
 __device__ __forceinline__ u4 t_look(const char *lut, u2 v, int e, uint32_t lo) {
     return *reinterpret_cast<const u4 *>(lut + __builtin_amdgcn_perm(v[e >> 2], lo, 0x0C020000u | ((4u + (e & 3)) << 8)));
 }
+// How far ahead fragments are read: A's in k-steps (2 C MFMAs of 32 clocks each), B's in column
+// blocks.  A table read takes up to 200 clocks beside the other waves', so short k-steps look
+// further ahead (48 tokens through ViT-B fc1: 31.3 us a call with A one and B two ahead, 30.5 so)
+template <int C>
+struct TReads {
+    static constexpr int A = C == 1 ? 3 : C == 2 ? 2 : 1, B = C == 1 ? 3 : 2, RA = C <= 2 ? 4 : 2;
+};
 template <int NA, int C>
 struct TFrags {
-    u4 a[2][NA], b[4];
+    u4 a[TReads<C>::RA][NA], b[4];
 };
-// the reads that the first k-step of a group needs: its A fragments and two B fragments
+// the reads ahead of a group's first k-step
 template <int NA, int C>
 __device__ __forceinline__ void t_first(const TSrc<C> &q, const TData<C> &d, TFrags<NA, C> &f) {
 #pragma unroll
-    for (int i = 0; i < NA; ++i) f.a[0][i] = t_look(q.lut, d.a[i], 0, q.loA);
+    for (int e = 0; e < TReads<C>::A; ++e)
 #pragma unroll
-    for (int n = 0; n < 2; ++n) f.b[n] = t_look(q.lut, d.b[n % C], n / C, q.loB);
+        for (int i = 0; i < NA; ++i) f.a[e][i] = t_look(q.lut, d.a[i], e, q.loA);
+#pragma unroll
+    for (int n = 0; n < TReads<C>::B; ++n) f.b[n] = t_look(q.lut, d.b[n % C], n / C, q.loB);
 }
 // The 8 k-steps of a half chunk, NA (1 or 2) row blocks running.  On entry and exit f holds the
-// next k-step's A fragments and two B fragments; a B fragment is read two column blocks ahead (four
-// registers sets in turn, so that C = 5 fits 256 registers), the next k-step's A fragments with
-// the first column blocks.
+// fragments read ahead (TReads): register sets in turn, so that C = 5 fits 256 registers.
 template <int NA, int C>
 __device__ __forceinline__ void t_half(const TSrc<C> &q, const TData<C> &d, const TData<C> &nx, const u4 (&m)[2],
                                        v16f (&acc)[2][C], TFrags<NA, C> &f) {
+    constexpr int DA = TReads<C>::A, DB = TReads<C>::B, RA = TReads<C>::RA;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         u4 fa[NA];
 #pragma unroll
         for (int i = 0; i < NA; ++i) {
-            fa[i] = f.a[e & 1][i] & m[i];
-            f.a[(e + 1) & 1][i] = t_look(q.lut, e < 7 ? d.a[i] : nx.a[i], (e + 1) & 7, q.loA);
+            fa[i] = f.a[e & (RA - 1)][i] & m[i];
+            f.a[(e + DA) & (RA - 1)][i] = t_look(q.lut, e + DA < 8 ? d.a[i] : nx.a[i], (e + DA) & 7, q.loA);
         }
 #pragma unroll
         for (int c = 0; c < C; ++c) {
-            const int n = e * C + c, e2 = (n + 2) / C, c2 = (n + 2) % C;
-            f.b[(n + 2) & 3] = t_look(q.lut, e2 < 8 ? d.b[c2] : nx.b[c2], e2 & 7, q.loB);
+            const int n = e * C + c, e2 = (n + DB) / C, c2 = (n + DB) % C;
+            const u4 fb = f.b[n & 3];
+            f.b[(n + DB) & 3] = t_look(q.lut, e2 < 8 ? d.b[c2] : nx.b[c2], e2 & 7, q.loB);
 #pragma unroll
             for (int i = 0; i < NA; ++i)
-                acc[i][c] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(frag(fa[i]), frag(f.b[n & 3]), acc[i][c],
+                acc[i][c] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(frag(fa[i]), frag(fb), acc[i][c],
                                                                             4, 4, 0, 127, 0, 127);
         }
         __builtin_amdgcn_sched_barrier(0);
