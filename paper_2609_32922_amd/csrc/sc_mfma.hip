@@ -1646,41 +1646,13 @@ struct RChunkArgs {
     int L_max, batch;
 };
 
-// One 16-byte half of a chunk: bytes d0 .. d0 + 15 of row xrow (K bytes; null: a padding
-// row), clamped to [-127, 127], 0x80 past K.
-__device__ __forceinline__ u4 r_half(const int8_t *xrow, int d0, int K, bool vec) {
-    u4 v = u4{0x80808080u, 0x80808080u, 0x80808080u, 0x80808080u};
-    if (xrow == nullptr || d0 >= K) return v;
-    if (vec && d0 + 16 <= K) {
-        v = *reinterpret_cast<const u4 *>(xrow + d0);
-    } else {
-        // any byte alignment: the two aligned 16-byte blocks that cover the 16 bytes, each
-        // loaded only when it holds a byte of the row before K (an aligned block never crosses
-        // a page, so it is readable when one of its bytes is; the first always holds byte d0),
-        // then shifted into place; bytes at or past K are replaced below
-        const uintptr_t p = reinterpret_cast<uintptr_t>(xrow + d0);
-        const uintptr_t end = reinterpret_cast<uintptr_t>(xrow + K);
-        const u4 *w = reinterpret_cast<const u4 *>(p & ~(uintptr_t)15);
-        const u4 lo = w[0];
-        const u4 hi = reinterpret_cast<uintptr_t>(w + 1) < end ? w[1] : v;   // (v: padding bytes)
-        const uint32_t t[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-        const uint32_t q = (uint32_t)(p >> 2) & 3u, sh = (uint32_t)(p & 3);
-        // dwords q .. q + 4 of t, picked with selects (q differs between the rows of a wave)
-        uint32_t wv[5];
+// 16 bytes of a chunk, of which the first n belong to the row: clamped to [-127, 127], 0x80 past them
+__device__ __forceinline__ u4 r_finish_half(u4 v, int n) {
 #pragma unroll
-        for (int k = 0; k < 5; ++k)
-            wv[k] = q == 0 ? t[k] : q == 1 ? t[k + 1] : q == 2 ? t[k + 2] : t[k + 3];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = __builtin_amdgcn_alignbyte(wv[k + 1], wv[k], sh);
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = r_clamp4(v[k]);
-    if (d0 + 16 > K) {          // the elements past K keep the padding byte
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (d0 + 4 * k + j >= K) v[k] = (v[k] & ~(0xFFu << (8 * j))) | ((uint32_t)RPAD << (8 * j));
+    for (int k = 0; k < 4; ++k) {
+        const int m = n - 4 * k;
+        const uint32_t keep = m >= 4 ? 0xFFFFFFFFu : m <= 0 ? 0u : (1u << (8 * m)) - 1u;
+        v[k] = (r_clamp4(v[k]) & keep) | (0x80808080u & ~keep);
     }
     return v;
 }
@@ -1931,10 +1903,14 @@ __device__ void table_block(int u, const RChunkArgs &a, const Layout &lay, uint8
 // contiguous in the chunk layout.  The same launch holds the prep block and the tables.
 constexpr int RC_ROWS = 64, RC_CH = 8;
 constexpr int RC_CSTRIDE = RC_ROWS * 2 + 1;      // u4 per chunk in LDS (+1: banks shift by chunk)
+constexpr int RC_RAW = RC_CH * RCH / 16 + 1;     // unaligned rows: 16-byte blocks that cover 256 bytes
+constexpr int RC_RSTRIDE = RC_RAW * 4 + 1;       // dwords per row of them in LDS
+constexpr int RC_LDS = RC_ROWS * (RC_RSTRIDE + 1) / 4;   // u4: those and a word per row
+static_assert(RC_LDS >= RC_CH * RC_CSTRIDE, "the aligned rows' chunks fit");
 __global__ __launch_bounds__(256) void k_rprep(RChunkArgs a, Layout lay, uint8_t *ws) {
     // (a C-BSG call with other lengths, one batch entry: its chunks go unread)
     if (lay.cbsg && a.batch == 1 && blockIdx.x != 0 && ws_ptr<int4>(ws, lay.off_pair)[lay.rtiles].z != a.L_max) return;
-    __shared__ u4 sm[RC_CH * RC_CSTRIDE];     // (one region for the three kinds of block)
+    __shared__ u4 sm[RC_LDS];                 // (one region for the three kinds of block)
     static_assert(UNIT_PAIRS * sizeof(int4) <= sizeof(sm), "the prep block's pairs fit");
     if (blockIdx.x == 0) {
         prep_block(a, lay, ws, reinterpret_cast<int4 *>(sm));
@@ -1953,42 +1929,74 @@ __global__ __launch_bounds__(256) void k_rprep(RChunkArgs a, Layout lay, uint8_t
     const int nc = min(RC_CH, a.KC - c0);
     uint8_t *wsb = ws + (size_t)b * a.stride_batch[side];
     const int tid = threadIdx.x, hl = tid & 15;         // hl = 2 * chunk + half
-    const bool vec = a.vec[side] != 0;
-    if (vec && (hl >> 1) < nc && (c0 + (hl >> 1)) * RCH + 16 * (hl & 1) + 16 <= a.K) {
-        // whole 16 bytes of aligned rows: a thread's rows, then all its loads, then its stores (in turn
-        // they took the compensator's layout 12.4 us instead of 10.7)
-        constexpr int NP = RC_ROWS / 16;
-        const int d0 = (c0 + (hl >> 1)) * RCH + 16 * (hl & 1);
-        int src[NP];
-        u4 v[NP];
-#pragma unroll
-        for (int p = 0; p < NP; ++p) {
-            const int r = r0 + p * 16 + (tid >> 4);
-            src[p] = side == 0 ? ws_ptr<int32_t>(wsb, a.off_perm)[r] : (r < a.rows[side] ? r : -1);
-        }
-        // (a padding row reads row 0)
-#pragma unroll
-        for (int p = 0; p < NP; ++p)
-            v[p] = *reinterpret_cast<const u4 *>(a.X[side] + (size_t)b * a.strideX[side] + (size_t)max(src[p], 0) * a.ld[side] + d0);
-#pragma unroll
-        for (int p = 0; p < NP; ++p) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) v[p][k] = src[p] >= 0 ? r_clamp4(v[p][k]) : 0x80808080u;
-            sm[(hl >> 1) * RC_CSTRIDE + (p * 16 + (tid >> 4)) * 2 + (hl & 1)] = v[p];
-        }
-    } else for (int pass = 0; pass < RC_ROWS / 16; ++pass) {
-        const int rl = pass * 16 + (tid >> 4), r = r0 + rl;
-        if ((hl >> 1) >= nc) continue;
-        const int src = side == 0 ? ws_ptr<int32_t>(wsb, a.off_perm)[r] : (r < a.rows[side] ? r : -1);
-        const int8_t *xrow = src >= 0 ? a.X[side] + (size_t)b * a.strideX[side] + (size_t)src * a.ld[side] : nullptr;
-        sm[(hl >> 1) * RC_CSTRIDE + rl * 2 + (hl & 1)] = r_half(xrow, (c0 + (hl >> 1)) * RCH + 16 * (hl & 1), a.K, vec);
-    }
-    __syncthreads();
     u4 *out = reinterpret_cast<u4 *>(ws_ptr<uint8_t>(wsb, a.off_out[side])) + (size_t)(r0 >> 8) * a.KC * 512 +
               (r0 & 255) * 2;
+    auto row_of = [&](int rl) {
+        const int r = r0 + rl;
+        return side == 0 ? ws_ptr<int32_t>(wsb, a.off_perm)[r] : (r < a.rows[side] ? r : -1);
+    };
+    // (a padding row stands for row 0; its bytes are replaced)
+    auto row_ptr = [&](int src) { return a.X[side] + (size_t)b * a.strideX[side] + (size_t)max(src, 0) * a.ld[side]; };
+    if (a.vec[side] != 0) {
+        // aligned rows: a thread's rows, then all its loads, then its stores (in turn they took the
+        // compensator's layout 12.4 us instead of 10.0).  A block of 16 bytes is readable when its first
+        // byte belongs to the row (an aligned block never crosses a page).
+        constexpr int NP = RC_ROWS / 16;
+        const int d0 = (c0 + (hl >> 1)) * RCH + 16 * (hl & 1);
+        if ((hl >> 1) < nc) {
+            int src[NP];
+            u4 v[NP];
+#pragma unroll
+            for (int p = 0; p < NP; ++p) src[p] = row_of(p * 16 + (tid >> 4));
+#pragma unroll
+            for (int p = 0; p < NP; ++p) v[p] = *reinterpret_cast<const u4 *>(row_ptr(src[p]) + (d0 < a.K ? d0 : 0));
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+                sm[(hl >> 1) * RC_CSTRIDE + (p * 16 + (tid >> 4)) * 2 + (hl & 1)] =
+                    r_finish_half(v[p], src[p] >= 0 ? a.K - d0 : 0);
+        }
+        __syncthreads();
+        for (int k = tid; k < nc * RC_ROWS * 2; k += 256) {
+            const int c = k / (RC_ROWS * 2), e = k % (RC_ROWS * 2);
+            out[(size_t)(c0 + c) * 512 + e] = sm[c * RC_CSTRIDE + e];
+        }
+        return;
+    }
+    // any byte alignment: each row's 256 bytes are staged as the RC_RAW aligned 16-byte blocks that cover
+    // them (those that hold a byte of the row), 69 dwords a row so that the dword reads spread over
+    // the banks, and shifted into place on the way out (attention-V's 577-byte rows: 199 -> 191 us a call
+    // against two global loads and a select network per 16 bytes)
+    uint32_t *raw = reinterpret_cast<uint32_t *>(sm);
+    int32_t *srow = reinterpret_cast<int32_t *>(raw + RC_ROWS * RC_RSTRIDE);
+    if (tid < RC_ROWS) srow[tid] = row_of(tid);
+    __syncthreads();
+    constexpr int NL = (RC_ROWS * RC_RAW + 255) / 256;
+    u4 v[NL];
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+        const int i = k * 256 + tid, rl = i / RC_RAW, blk = i % RC_RAW;
+        v[k] = u4{0u, 0u, 0u, 0u};
+        if (i >= RC_ROWS * RC_RAW) continue;
+        const int8_t *x = row_ptr(srow[rl]);
+        const uintptr_t w = (reinterpret_cast<uintptr_t>(x + c0 * RCH) & ~(uintptr_t)15) + 16 * (uintptr_t)blk;
+        if (w < reinterpret_cast<uintptr_t>(x + a.K)) v[k] = *reinterpret_cast<const u4 *>(w);
+    }
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+        const int i = k * 256 + tid, rl = i / RC_RAW, blk = i % RC_RAW;
+        if (i >= RC_ROWS * RC_RAW) continue;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) raw[rl * RC_RSTRIDE + blk * 4 + j] = v[k][j];
+    }
+    __syncthreads();
     for (int k = tid; k < nc * RC_ROWS * 2; k += 256) {
-        const int c = k / (RC_ROWS * 2), e = k % (RC_ROWS * 2);
-        out[(size_t)(c0 + c) * 512 + e] = sm[c * RC_CSTRIDE + e];
+        const int c = k / (RC_ROWS * 2), e = k % (RC_ROWS * 2), rl = e >> 1, src = srow[rl];
+        const int at = (int)(reinterpret_cast<uintptr_t>(row_ptr(src)) & 15) + c * RCH + 16 * (e & 1);
+        const uint32_t *t = raw + rl * RC_RSTRIDE + (at >> 2);
+        u4 x;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[j] = __builtin_amdgcn_alignbyte(t[j + 1], t[j], (uint32_t)at & 3u);
+        out[(size_t)(c0 + c) * 512 + e] = r_finish_half(x, src >= 0 ? a.K - ((c0 + c) * RCH + 16 * (e & 1)) : 0);
     }
 }
 
