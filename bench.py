@@ -173,7 +173,9 @@ def main():
                 "unit": "TFLOP/s", "frac": 2 * achieved / PEAK_FP4_FLOPS, "traffic": traffic,
                 "kernel": "%s<%s>" % (gemm_kernel_name(g_dom, rng == scg.SC_RNG_LFSR32),
                                       "bipolar" if g_dom.polarity == 0 else "unipolar"),
-                "kernel_ms": gemm_ms, "kernel_ms_steps": len(timed), "kernel_stream_bit_ops_per_s": achieved}
+                "kernel_ms": gemm_ms, "kernel_ms_steps": len(timed), "kernel_stream_bit_ops_per_s": achieved,
+                "counts": "bit products of the call; cycles whose draws share a class share one "
+                          "multiply-add of the kernel, so frac is not bounded by 1"}
 
     valu = None
     if not args.no_valu_peak:
@@ -237,17 +239,17 @@ def settle_clock(step, stream, batch=10, min_s=0.1, max_s=3.0, tol=0.01):
 
 
 def gemm_kernel_name(g, comparator):
-    """The counting kernel the library takes for this shape (see make_layout): 256-row blocks
-    for M > 128 (fragments from int8 chunks with comparator streams, 256 or, for N <= 64, 64
-    columns wide; fp4 planes with C-BSG when N > 128); fragments from the int8 rows for other
-    N <= 128 with comparator streams; 128-row planes otherwise."""
-    if comparator and g.M > 128 and (g.N > 128 or g.N <= 64):
-        return "k_rgemm"
-    if g.M > 128 and g.N > 128:
-        return "k_qgemm"
-    if comparator and g.N <= 128:
-        return "k_fgemm"
-    return "k_mgemm"
+    """The counting kernel the library takes for the workloads' shapes (its estimates decide; see
+    make_layout): blocks of 256 rows x 64 columns for N <= 64, of 64 rows for few rows or columns and
+    for short tiles with varying lengths, else of 256 x 256.  C-BSG calls run on the same kernels when
+    every row has L_max cycles and the call is large, else on fp4 planes."""
+    if not comparator and (g.L.min() < g.L_max or g.bitops() < 4e11):
+        return "k_qgemm" if g.M > 128 and g.N > 128 else "k_mgemm"
+    if g.M > 128 and g.N <= 64:
+        return "k_rgemm_n"
+    if g.M <= 128 or g.N <= 128 or (g.K * float(g.L.mean()) < 16 * 1024 and g.L.min() < g.L_max):
+        return "k_tgemm"
+    return "k_rgemm"
 
 
 def valu_peak():

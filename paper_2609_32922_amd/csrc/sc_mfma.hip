@@ -1573,16 +1573,16 @@ static hipError_t launch_qgemm(const MGemmArgs &g, const Layout &lay, uint8_t *w
 // ----------------------------------------------------------------------------
 // 256 x 256 GEMM with fragments built from int8 chunks (comparator streams)
 // ----------------------------------------------------------------------------
-// One comparator sequence per operand makes the 32 stream bits of an element over the
-// cycles 32G .. 32G + 31 a function of its int8 value alone: one 16-byte fp4 slot row.  The
-// GEMM keeps that table for its current cycle group G in LDS and builds every MFMA
+// One comparator sequence per operand makes what an element holds in the 32 slots of a group (cycles,
+// or cycles merged by the pair's slot plan) a function of its int8 value alone: one 16-byte fp4 slot
+// row.  The GEMM keeps that table for its current group G in LDS and builds every MFMA
 // fragment with one table read indexed by the element's byte, so the operands stream in
-// as bytes (k_rchunks lays them out) instead of as fp4 planes 8 L times their size.
+// as bytes (k_rprep lays them out) instead of as fp4 planes 8 L times their size.
 // Slot rows: a k-step takes one element per lane half (lanes 0-31 the elements 0..15 of
 // their row's chunk, lanes 32-63 the elements 16..31, one element per k-step) over the 32
-// cycles of the group; both operands use the same order, so the k-step sums the products
-// of matching elements and cycles.
-constexpr int RCH = 32;          // elements per chunk, cycles per group
+// slots of the group; both operands use the same order, so the k-step sums the products
+// of matching elements and slots.
+constexpr int RCH = 32;          // elements per chunk, slots per group
 constexpr int RREP = 8;          // copies of each table entry (16-byte reads spread over the banks)
 constexpr int RPAD = 0x80;       // chunk byte of a padding element or row: the table gives zero
 constexpr int RREP1 = 4;         // copies of each masked table entry
