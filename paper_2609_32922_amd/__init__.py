@@ -20,21 +20,22 @@ __all__ = ["gemm", "make_desc", "comparator_sequence", "quantize", "mp_lengths",
            "SC_UNIPOLAR_AND_SM", "SC_RNG_LFSR32", "SC_RNG_SOBOL8_CBSG"]
 
 
-def _stream_handle(stream):
+def _stream_handle(stream, device_index=None):
+    """The stream's handle, or that of the device's (default: current device's) current stream,
+    read without building a torch.cuda.Stream object (0.2 us of host time instead of 2.7)."""
     import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+    if stream is not None:
+        return int(stream.cuda_stream)
+    if device_index is None:
+        device_index = torch.cuda.current_device()
+    return torch._C._cuda_getCurrentRawStream(device_index)
 
 
 def make_desc(A, B, L_max: int, polarity: int, seed: int, L_hint: int = 0,
               rng: int = SC_RNG_LFSR32) -> ScGemmDesc:
     """Descriptor for contiguous A [batch, M, K] and B [batch or 1, N, K] tensors."""
-    if A.dim() == 2:
-        A = A.unsqueeze(0)
-    if B.dim() == 2:
-        B = B.unsqueeze(0)
-    batch, M, K = A.shape
-    nb, N, K2 = B.shape
+    batch, M, K = A.shape if A.dim() != 2 else (1, *A.shape)
+    nb, N, K2 = B.shape if B.dim() != 2 else (1, *B.shape)
     if K2 != K or nb not in (1, batch):
         raise ValueError("A is [batch, M, K], B must be [batch or 1, N, K]")
     d = ScGemmDesc()
@@ -91,22 +92,19 @@ def gemm(A, sA, B, sB, L, *, L_max: int, polarity: int = SC_BIPOLAR_XNOR, seed: 
     """
     import torch
     squeeze = A.dim() == 2
-    A3 = A.unsqueeze(0) if A.dim() == 2 else A
-    B3 = B.unsqueeze(0) if B.dim() == 2 else B
-    d = make_desc(A3, B3, L_max, polarity, seed, L_hint, rng)
-    dev = A3.device
-    for t, name in ((A3, "A"), (B3, "B"), (sA, "sA"), (sB, "sB"), (L, "L")):
+    d = make_desc(A, B, L_max, polarity, seed, L_hint, rng)
+    dev = A.device
+    for t, name in ((A, "A"), (B, "B"), (sA, "sA"), (sB, "sB"), (L, "L")):
         if not t.is_cuda or not t.is_contiguous() or t.device != dev:
             raise ValueError("%s must be a contiguous tensor on %s" % (name, dev))
-    if A3.dtype != torch.int8 or B3.dtype != torch.int8 or sA.dtype != torch.float32 \
+    if A.dtype != torch.int8 or B.dtype != torch.int8 or sA.dtype != torch.float32 \
             or sB.dtype != torch.float32 or L.dtype != torch.int32:
         raise TypeError("dtypes: A, B int8; sA, sB float32; L int32")
     batch, M, N = d.batch, d.M, d.N
-    if sA.numel() != batch * M or L.numel() != batch * M or sB.numel() != B3.shape[0] * N:
+    if sA.numel() != batch * M or L.numel() != batch * M or sB.numel() != (B.shape[0] if B.dim() == 3 else 1) * N:
         raise ValueError("scale or length vector has the wrong size")
     oshape = (M, N) if squeeze else (batch, M, N)
-    s = stream if stream is not None else torch.cuda.current_stream(dev)
-    foreign = s != torch.cuda.current_stream(dev)
+    foreign = stream is not None and stream != torch.cuda.current_stream(dev)
     made = []
     if out is None:
         out = torch.empty(oshape, dtype=torch.float32, device=dev)
@@ -125,14 +123,14 @@ def gemm(A, sA, B, sB, L, *, L_max: int, polarity: int = SC_BIPOLAR_XNOR, seed: 
     else:
         ws = workspace.ensure(nbytes)
     if foreign:
-        # the caching allocator must not hand these blocks out again before `s` is done
+        # the caching allocator must not hand these blocks out again before `stream` is done
         for t in made:
-            t.record_stream(s)
+            t.record_stream(stream)
     if prof_events is not None:
         d.prof_event_begin = prof_events[0]
         d.prof_event_end = prof_events[1]
-    sh = int(s.cuda_stream)
-    rc = sc_gemm(d, A3.data_ptr(), sA.data_ptr(), B3.data_ptr(), sB.data_ptr(), L.data_ptr(),
+    sh = _stream_handle(stream, dev.index)
+    rc = sc_gemm(d, A.data_ptr(), sA.data_ptr(), B.data_ptr(), sB.data_ptr(), L.data_ptr(),
                  out.data_ptr(), counts.data_ptr() if counts is not None else 0, ws.ptr, ws.nbytes, sh)
     if rc != SC_OK:
         raise ScError(rc, "sc_gemm")
@@ -159,21 +157,20 @@ def quantize(X, per_tensor: bool = False, want_rowmax: bool = False, stream=None
     Returns (Q int8, scale float32 [batch, rows], rowmax float32 or None).
     """
     import torch
-    squeeze = X.dim() == 2
-    X3 = X.unsqueeze(0) if squeeze else X
-    if not X3.is_cuda or not X3.is_contiguous() or X3.dtype != torch.float32:
+    if not X.is_cuda or not X.is_contiguous() or X.dtype != torch.float32:
         raise ValueError("X must be a contiguous float32 device tensor")
-    batch, rows, K = X3.shape
-    Q = torch.empty((batch, rows, K), dtype=torch.int8, device=X.device)
-    scale = torch.empty((batch, rows), dtype=torch.float32, device=X.device)
-    rowmax = torch.empty((batch, rows), dtype=torch.float32, device=X.device) if want_rowmax else None
-    rc = sc_quantize(batch, rows, K, X3.data_ptr(), K, rows * K, int(per_tensor), Q.data_ptr(), K,
+    shape, dev = X.shape, X.device
+    batch, rows, K = shape if X.dim() != 2 else (1, *shape)
+    # the outputs are made in the caller's rank: a view of each costs the host 1 us, and the
+    # kernels of a small call take less time than this function
+    Q = torch.empty(shape, dtype=torch.int8, device=dev)
+    scale = torch.empty(shape[:-1], dtype=torch.float32, device=dev)
+    rowmax = torch.empty(shape[:-1], dtype=torch.float32, device=dev) if want_rowmax else None
+    rc = sc_quantize(batch, rows, K, X.data_ptr(), K, rows * K, int(per_tensor), Q.data_ptr(), K,
                      rows * K, scale.data_ptr(), rowmax.data_ptr() if rowmax is not None else 0,
                      rows, _stream_handle(stream))
     if rc != SC_OK:
         raise ScError(rc, "sc_quantize")
-    if squeeze:
-        return Q[0], scale[0], (rowmax[0] if rowmax is not None else None)
     return Q, scale, rowmax
 
 
@@ -181,14 +178,12 @@ def mp_lengths(metric, tau, ladder, stream=None):
     """Per-row stream lengths (int32 device tensor shaped like ``metric``) from a row
     metric [batch, M] (or [M]) with thresholds ``tau`` and length ladder ``ladder``."""
     import torch
-    squeeze = metric.dim() == 1
-    m2 = metric.unsqueeze(0) if squeeze else metric
-    if not m2.is_cuda or not m2.is_contiguous() or m2.dtype != torch.float32:
+    if not metric.is_cuda or not metric.is_contiguous() or metric.dtype != torch.float32:
         raise ValueError("metric must be a contiguous float32 device tensor")
-    batch, M = m2.shape
-    L = torch.empty((batch, M), dtype=torch.int32, device=metric.device)
-    rc = sc_mp_lengths(batch, M, m2.data_ptr(), M, list(tau), list(ladder), L.data_ptr(), M,
+    batch, M = metric.shape if metric.dim() != 1 else (1, *metric.shape)
+    L = torch.empty(metric.shape, dtype=torch.int32, device=metric.device)
+    rc = sc_mp_lengths(batch, M, metric.data_ptr(), M, list(tau), list(ladder), L.data_ptr(), M,
                        _stream_handle(stream))
     if rc != SC_OK:
         raise ScError(rc, "sc_mp_lengths")
-    return L[0] if squeeze else L
+    return L

@@ -204,3 +204,40 @@ def test_mp_lengths_many_blocks(dev, oracle_mod, M):
     L = scg.mp_lengths(_t(g, dev), tau, ladder).cpu().numpy()
     for b in range(2):
         assert np.array_equal(L[b], oracle_mod.mp_lengths_fp32(g[b], tau, ladder))
+
+
+@pytest.mark.parametrize("shape", [(5, 48), (1, 5, 48), (3, 4, 16)])
+def test_binding_ranks_and_current_stream(dev, oracle_mod, shape):
+    """Outputs have the rank of their input, own contiguous memory, and the launches go to the
+    current stream or the given one: the same values on the default stream, on a current side
+    stream and on a passed side stream."""
+    import torch
+    import paper_2609_32922_amd as scg
+    g = torch.Generator(device="cpu").manual_seed(11)
+    x = torch.randn(shape, generator=g).to(dev)
+    tau, ladder = [0.5, 0.25, 0.1], [64, 40, 24, 12]
+    B = torch.randint(-127, 128, (7, shape[-1]), dtype=torch.int8, generator=g).to(dev)
+    sB = torch.full((7,), 0.02, device=dev)
+
+    def call(stream):
+        q, s, m = scg.quantize(x, want_rowmax=True, stream=stream)
+        L = scg.mp_lengths(m, tau, ladder, stream=stream)
+        out, counts = scg.gemm(q, s, B, sB, L, L_max=64, seed=3, want_counts=True, stream=stream)
+        return q, s, m, L, out, counts
+
+    _note("binding shape=%s" % (shape,))
+    side = torch.cuda.Stream()
+    want = call(None)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        current = call(None)
+    torch.cuda.synchronize()
+    given = call(side)
+    torch.cuda.synchronize()
+    shapes = [shape, shape[:-1], shape[:-1], shape[:-1], shape[:-1] + (7,), shape[:-1] + (7,)]
+    for w, c, v, sh in zip(want, current, given, shapes):
+        assert tuple(w.shape) == tuple(sh) and w.is_contiguous()
+        assert torch.equal(w, c) and torch.equal(w, v)
+    A = x.cpu().numpy().reshape(-1, shape[-1])
+    absmax = np.abs(A).max(axis=1)
+    assert np.array_equal(want[2].cpu().numpy().reshape(-1), absmax)
