@@ -170,6 +170,8 @@ static bool layout_with(const sc_gemm_desc &d, int cus, int spend, bool cbsg, La
         for (int c : {1, 2, 4, 5})
             for (int S = w.Smin; S <= (c == 5 ? 1 : w.Smin > MAX_SPLIT ? w.Smin : MAX_SPLIT); ++S) {
                 if (S > w.Smin && w.KC * w.gmean / S < TPART) break;
+                // (units are counted in 32 bits)
+                if (w.batch * ((d.M + TROWS - 1) / TROWS) * ceil(d.N / (128.0 * c)) * S > INT_MAX) break;
                 const double t = est_tall(w, c, S);
                 if (t < best) {
                     best = t;
@@ -179,6 +181,7 @@ static bool layout_with(const sc_gemm_desc &d, int cus, int spend, bool cbsg, La
             }
     }
     const bool tall = tallC > 0;
+    if (few && !tall && !l.fused) return false;
     l.mbn = (l.NT > 1 || l.narrow || tall) && !l.fused ? 2 * BN : BN;
     l.NT = (int)round_up(l.NT, l.mbn / BN);
     l.mbm = ((l.MT > 1 && l.mbn == 2 * BN) || tall) ? 2 * BM : BM;
@@ -282,7 +285,6 @@ static bool layout_with(const sc_gemm_desc &d, int cus, int spend, bool cbsg, La
     l.tall = tallC;
     if (tall) {
         tiles = (int64_t)(d.batch > 0 ? d.batch : 0) * l.rtiles * (((int64_t)d.N + 128 * tallC - 1) / (128 * tallC));
-        if (tiles * MAX_SPLIT > INT_MAX) return false;
     }
 
     // Division of the GEMM tiles into work units.
@@ -433,8 +435,16 @@ static bool layout_with(const sc_gemm_desc &d, int cus, int spend, bool cbsg, La
     return true;
 }
 
+// Most bytes that plans and chunks may add to a call's workspace.  An operand's chunks are as large as the
+// operand (31 x at K = 1), so without a bound a call whose operands nearly fill the card would no longer
+// fit it: 128 x 1272922 x 93 x 243 takes 1.3 GB in k_fgemm and 43 GB in chunks beside 263 GB of operands.
+static constexpr size_t MOST_EXTRA = (size_t)8 << 30;
 bool make_layout(const sc_gemm_desc &d, int cus, Layout *lay) {
-    if (!layout_with(d, cus, LAY_FULL, false, lay)) return false;
+    if (!layout_with(d, cus, LAY_FULL, false, lay)) return layout_with(d, cus, LAY_LEAST, false, lay);
+    if (lay->total > MOST_EXTRA) {
+        Layout least;
+        if (layout_with(d, cus, LAY_LEAST, false, &least) && least.total < lay->total - MOST_EXTRA) *lay = least;
+    }
     // a call that fits sc_gemm_noalloc's array without the tables of the slot plans, or without
     // chunks of its operands, keeps fitting it
     for (int spend = LAY_ONE_PLAN; lay->total > SC_NOALLOC_WORKSPACE_BYTES && spend <= LAY_LEAST; ++spend) {
@@ -454,7 +464,7 @@ bool make_cbsg_layout(const sc_gemm_desc &d, int cus, const Layout &planes, Layo
     if (round_up(d.K, 32) * round_up(d.L_max, 32) >= MFMA_EXACT || !layout_with(d, cus, LAY_FULL, true, lay) || !lay->rgen)
         return false;
     const size_t base = planes.total;
-    if (lay->total > SIZE_MAX - base) return false;
+    if (lay->total > MOST_EXTRA || lay->total > SIZE_MAX - base) return false;
     for (size_t *o : {&lay->off_rA, &lay->off_rB, &lay->off_status, &lay->off_CA, &lay->off_plan, &lay->off_pslots,
                       &lay->off_rtab, &lay->off_perm, &lay->off_Ls, &lay->off_tileL, &lay->off_tileOff, &lay->off_pair,
                       &lay->off_Ap, &lay->off_Bp, &lay->off_part, &lay->off_units, &lay->off_tinfo, &lay->off_slot,

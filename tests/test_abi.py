@@ -163,6 +163,18 @@ def test_exactness_bound_splits(lib):
         assert lib.sc_gemm_workspace_size(cb) > 0
 
 
+@pytest.mark.parametrize("batch,M,N,K,L_max,rng,least", [
+    (128, 1272922, 93, 243, 32, 0, 1318814464),       # few columns: 43 GB as chunks
+    (42, 197751, 127, 6310, 8, 1, 210053849600),      # C-BSG: 53 GB of tables beside the planes
+    (45, 300785, 8, 1200, 32, 1, 260003242240),       # (17 GB)
+])
+def test_workspace_of_large_operands(lib, batch, M, N, K, L_max, rng, least):
+    # chunks and tables add at most 8 GiB to what the operands' own layout (planes, or none) needs
+    d = _desc(lib, batch=batch, M=M, N=N, K=K, lda=K, ldb=K, ldo=N, strideA=M * K, strideO=M * N,
+              strideSA=M, strideL=M, L_max=L_max, rng=rng)
+    assert least * 0.9 < lib.sc_gemm_workspace_size(d) <= least + (8 << 30)
+
+
 def test_workspace_size_values(lib):
     d = _desc(lib)
     n1 = lib.sc_gemm_workspace_size(d)
