@@ -509,12 +509,16 @@ __device__ __forceinline__ void d_rows(const DecodeLds &d, const float *T, int r
 // rb * (PC / 32) + cb for a piece PC columns wide.  Lane (grp, i32) of quad q holds rows
 // 32 rb + 8 q + 4 grp + j (j = 0..3) of column 32 cb + i32: the four accumulator elements
 // 4q .. 4q + 3 of its 32 x 32 block, stored as one 16-byte store (a wave writes 1 KB at a time).
+// The whole offset is per lane.  A buffer store of more than 8 bytes a lane reads its data after it
+// issued, also with an offset in a scalar register: the compiler leaves out the wait states before a
+// write to those data registers then, and the next block's first conversion went into the partial
+// sums of lanes 12 .. 15 of every 16 (64-row tiles of 256 and 512 columns in int32 parts).
 template <int PC>
 __device__ __forceinline__ void store_block(const v16f &a, __amdgpu_buffer_rsrc_t pr, int lane, int rb, int cb) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const v4i v = {(int)a[4 * q], (int)a[4 * q + 1], (int)a[4 * q + 2], (int)a[4 * q + 3]};
-        __builtin_amdgcn_raw_buffer_store_b128(v, pr, lane * 16, (((rb * (PC / 32) + cb) * 4 + q) * 64) * 16, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(v, pr, ((((rb * (PC / 32) + cb) * 4 + q) * 64) + lane) * 16, 0, 0);
     }
 }
 

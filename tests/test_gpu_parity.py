@@ -779,6 +779,32 @@ def test_row_tiles_of_64(dev, oracle_mod, case):
             _compare(g, b, rows, cols, out, cnt, oracle_mod, "tall%s b%d" % (case, b))
 
 
+# Parts with int32 partial counts in blocks of 256 and 512 columns: every row, and columns of each wave's
+# first 32-column block, lanes 12 .. 15 of every 16 above all (there one row of the last quad was stored
+# with the next block's value, by chance of timing)
+INT32_PARTS = [
+    # M, N, K, L_max, lengths, polarity, seed
+    (335, 2314, 3072, 192, "skew", 0, 741),       # C = 2 in 8 parts
+    (206, 2733, 2630, 96, "uniform", 1, 743),
+    (1316, 1046, 2063, 128, "uniform", 0, 745),   # C = 4 in 8 parts
+    (1316, 1046, 2063, 128, "skew", 1, 747),
+]
+
+
+@pytest.mark.parametrize("case", INT32_PARTS, ids=[str(c) for c in INT32_PARTS])
+def test_row_tiles_of_64_int32_parts(dev, oracle_mod, case):
+    M, N, K, L_max, kind, pol, seed = case
+    rng = np.random.default_rng(seed)
+    g = W.random_gemm(rng, 1, M, N, K, L_max, pol, seed, uniform_L=L_max)
+    if kind == "skew":
+        g.L[0] = (L_max * rng.random(M) ** 2).astype(np.int32)
+    j = np.arange(N)
+    cols = j[(j < 32) | (j >= N - 40) | ((j % 64 < 32) & (j % 16 >= 12) & (j % 3 == 0))]
+    _note("64-row tiles, int32 parts %s" % (case,))
+    out, cnt = _run(g, dev)
+    _compare(g, 0, np.arange(M), cols, out, cnt, oracle_mod, "int32 parts%s" % (case,))
+
+
 def test_noalloc_keeps_long_narrow_calls(dev, oracle_mod):
     # chunks of this A (72 MB) do not fit the array of sc_gemm_noalloc: the layout that takes the
     # operands as they are does, and the call goes on to run there
