@@ -2041,9 +2041,13 @@ hipError_t launch_rprep(const sc_gemm_desc &d, const Layout &lay, const int8_t *
     a.L_max = d.L_max;
     a.batch = d.batch;
     // with K = 0 no chunk and no table is read
-    // (a table block for each eighth of two plans' tables, or of every plan's first)
+    // (a table block for each eighth of a table, up to 768 or what two plans' tables and every plan's first
+    // take.  Calls of many lengths use most plans, and with the second number alone their blocks built
+    // five tables each, one after the other: 11477 x 52 x 64 at L = 256 57.5 us a call against 54.4, and 52.1
+    // before there were plans; ViT-L/14 Q.K^T 181 against 177.  Blocks with nothing to do cost 0.2 us at most.)
     const int groups = lay.LBS / RCH;
-    a.nt = lay.KC > 0 ? 8 * groups * (lay.nplans < 2 ? lay.nplans : 2) + 8 * lay.nplans : 0;
+    const int least = 8 * groups * (lay.nplans < 2 ? lay.nplans : 2) + 8 * lay.nplans;
+    a.nt = lay.KC > 0 ? min(8 * groups * lay.nplans, max(768, least)) : 0;
     // (the 64-row blocks of A read their own rows only; the 256 x 64 blocks the first 64 rows of
     // B's pair, the 64-row blocks no column past the last 32 with one in range)
     a.gx[0] = lay.tall ? lay.rtiles : lay.MT * BM / RC_ROWS;
