@@ -207,9 +207,8 @@ hipError_t launch_quantize(int batch, int rows, int K, const float *X, int64_t l
 // thread, all their loads in flight at once), then the lengths of its own rows: latency-bound,
 // and one block per call took 17 us for 18464 rows, most of it in the divisions (4 us now).
 constexpr int MREG = 20;
-__global__ __launch_bounds__(1024) void k_mp_lengths(int M, const float *__restrict__ metric,
-                                                     int64_t strideM, MpParams p, int32_t *L_out,
-                                                     int64_t strideL) {
+__global__ __launch_bounds__(1024) void k_mp_lengths(int M, const float *metric, int64_t strideM, MpParams p,
+                                                     int32_t *L_out, int64_t strideL) {
     __shared__ float pmin[16], pmax[16];
     const int b = blockIdx.x, tid = threadIdx.x;
     const float *g = metric + (size_t)b * strideM;
@@ -253,8 +252,12 @@ __global__ __launch_bounds__(1024) void k_mp_lengths(int M, const float *__restr
 
 hipError_t launch_mp_lengths(int batch, int M, const float *metric, int64_t strideM,
                              const MpParams &p, int32_t *L_out, int64_t strideL, hipStream_t st) {
-    // (a block reads every metric, so their number is bounded)
-    const int blocks = (M + 1023) / 1024 < 32 ? (M + 1023) / 1024 : 32;
+    // (a block reads every metric, so their number is bounded.  Lengths that are written over the metrics
+    // take one block per operator call: another one would read metrics that are lengths already)
+    const uintptr_t m0 = reinterpret_cast<uintptr_t>(metric), l0 = reinterpret_cast<uintptr_t>(L_out);
+    const uintptr_t span = ((uintptr_t)(batch - 1) * (uintptr_t)(strideM > strideL ? strideM : strideL) + (uintptr_t)M) * 4;
+    const bool apart = m0 >= l0 ? m0 - l0 >= span : l0 - m0 >= span;
+    const int most = apart ? 32 : 1, blocks = (M + 1023) / 1024 < most ? (M + 1023) / 1024 : most;
     hipLaunchKernelGGL(k_mp_lengths, dim3((unsigned)batch, (unsigned)blocks), dim3(1024), 0, st, M, metric, strideM, p,
                        L_out, strideL);
     return hipGetLastError();

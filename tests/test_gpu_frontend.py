@@ -206,6 +206,25 @@ def test_mp_lengths_many_blocks(dev, oracle_mod, M):
         assert np.array_equal(L[b], oracle_mod.mp_lengths_fp32(g[b], tau, ladder))
 
 
+@pytest.mark.parametrize("batch,M", [(3, 40000), (2000, 2500)])
+def test_mp_lengths_over_the_metric(dev, oracle_mod, batch, M):
+    """Lengths written over the metrics they come from: every metric of an entry is read before the
+    entry's first length is written (also where an entry's blocks would not all run at once)."""
+    import torch
+    import paper_2609_32922_amd as scg
+    g = np.random.default_rng(M).gamma(2.0, 1.0, (batch, M)).astype(np.float32)
+    g[:, 0], g[:, -1] = 50.0, 0.0
+    tau, ladder = [0.5, 0.25, 0.1], [256, 128, 64, 32]
+    buf = _t(g, dev)
+    _note("mp lengths over the metric, %d x %d" % (batch, M))
+    rc = scg.sc_mp_lengths(batch, M, buf.data_ptr(), M, tau, ladder, buf.data_ptr(), M,
+                           int(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0
+    L = buf.cpu().numpy().view(np.int32)
+    for b in range(0, batch, 1 + batch // 100):
+        assert np.array_equal(L[b], oracle_mod.mp_lengths_fp32(g[b], tau, ladder))
+
+
 @pytest.mark.parametrize("shape", [(5, 48), (1, 5, 48), (3, 4, 16)])
 def test_binding_ranks_and_current_stream(dev, oracle_mod, shape):
     """Outputs have the rank of their input, own contiguous memory, and the launches go to the
