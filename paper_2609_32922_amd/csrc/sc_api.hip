@@ -340,9 +340,16 @@ static bool layout_with(const sc_gemm_desc &d, int cus, int spend, bool cbsg, La
             }
         }
         // (256 x 64 blocks: the last pair of each batch entry, if it holds at most half its rows, runs at
-        // most half its row blocks; a last round of such tiles alone stays whole.  The compensator,
-        // 16 x 8224 rows: 67.6 -> 64.6 us without parts and the launch that sums them)
-        if (l.F > 0 && l.narrow && d.M % 256 > 0 && d.M % 256 <= 128 && R <= (int64_t)d.batch * (l.NT / 2)) l.S = 1;
+        // most half its row blocks (a step then 9/16 of a full one, 5/16 with at most 32 rows).  A last round
+        // of such tiles alone stays whole while parts would save few steps: parts and the launch that
+        // sums them cost 10 to 20 us, less for the fewer tiles of more parts.  Measured, whole against parts
+        // (us): the compensator, 16 x 8224 rows, 3 steps saved, 65 and 68; 256 x 550 x 64 x 577 at L = 256,
+        // 21 of 2 parts, 289 and 306; and 128 x 1099 x 64 x 577, 40 of 4 parts, 323 and 310; 64 x 2115 x
+        // 64 x 256 at L = 512, 24 of 8 parts, 181 and 172)
+        const double saved = w.KC * w.gmean * (d.M % 256 <= 32 ? RW3_NARROW : RW2_NARROW) / RW1_NARROW * (1.0 - 1.0 / l.S);
+        if (l.F > 0 && l.narrow && d.M % 256 > 0 && d.M % 256 <= 128 && R <= (int64_t)d.batch * (l.NT / 2) &&
+            saved <= (l.S > 4 ? 12 : 24))
+            l.S = 1;
         if (l.S == 1) l.F = (int)tiles;
     } else if (tiles > 0 && kunits > 1) {
         // 128-row tiles: every tile split s ways.  Estimated time of split s: the busiest

@@ -1,0 +1,54 @@
+"""Which kernel, division and workspace a call gets (the host's choice; no GPU): the library's
+host code compiled on its own, asked for 256 compute units."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+HIPCC = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "bin", "hipcc")
+pytestmark = pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
+FIELDS = "total rgen tall narrow fused S F p16 vsplit sk_slots nplans".split()
+MIB, GIB = 1 << 20, 1 << 30
+
+
+@pytest.fixture(scope="module")
+def layout(tmp_path_factory):
+    import paper_2609_32922_amd._lib as L
+    out = str(tmp_path_factory.mktemp("layout") / "layout.so")
+    # (only the query is exported, so the entry points and the launches they call fall away)
+    r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+                        "-Xarch_host", "-ffunction-sections", "-Wl,--gc-sections", "-Xclang", "-target-feature",
+                        "-Xclang", "-packed-fp32-ops", os.path.join(HERE, "layout_query.hip"), "-o", out],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-4000:]
+    lib = ctypes.CDLL(out)
+    lib.layout_query.argtypes = [ctypes.POINTER(L.ScGemmDesc), ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_int64)]
+
+    def ask(batch, M, N, K, L_max, polarity=0, hint=0, rng=0, own_B=False, tables=False, **kw):
+        d = L.ScGemmDesc()
+        d.batch, d.M, d.N, d.K, d.lda, d.ldb, d.ldo = batch, M, N, K, K, K, N
+        d.strideA, d.strideB, d.strideO = M * K, N * K if own_B else 0, M * N
+        d.strideSA, d.strideSB, d.strideL = M, N if own_B else 0, M
+        d.L_max, d.polarity, d.rng, d.L_hint = L_max, polarity, rng, hint
+        for k, v in kw.items():
+            setattr(d, k, v)
+        o = (ctypes.c_int64 * len(FIELDS))()
+        rc = lib.layout_query(ctypes.byref(d), 256, int(tables), o)
+        return dict(zip(FIELDS, o)) if rc == 0 else rc
+
+    return ask
+
+
+@pytest.mark.parametrize("batch,M,K,L_max,polarity,parts", [
+    (16, 8224, 64, 256, 0, 1),       # the compensator: 32 rows, ten steps
+    (256, 550, 577, 256, 1, 1),
+    (16, 8320, 256, 256, 0, 8),      # 128 rows, 40 steps a tile
+    (128, 1152, 577, 256, 0, 4),
+    (64, 2115, 256, 512, 1, 8),
+])
+def test_ragged_last_round_of_narrow_tiles(layout, batch, M, K, L_max, polarity, parts):
+    # 256 x 64 blocks, one length: a last round of half-filled tiles stays whole only while it is short
+    lay = layout(batch, M, 64, K, L_max, polarity)
+    assert lay["narrow"] and lay["S"] == parts
