@@ -388,16 +388,22 @@ static bool layout_with(const sc_gemm_desc &d, int cus, int spend, bool cbsg, La
     l.off_units = off;
     int64_t pieces = quad ? (tiles - l.F) * (int64_t)l.S : tiles * (int64_t)l.S;
     if (l.vsplit) {
-        // (k_rprep weighs a step at most w1 and at least w2 and adds at most 7 w1 per tile for
-        // its decode and a minimum step: W <= w1 wmax.  A range of cost T = ceil(W / sl) <=
-        // w1 wmax / sl + 1 holds at most T / w2 + 1 steps, which must stay below RSTEP_EXACT;
-        // the 256 x 64 blocks' ranges hold up to twice T.)
-        const int64_t w1 = l.narrow ? RW1_NARROW : RW1_WIDE, w2 = l.narrow ? RW3_NARROW : RW2_WIDE;   // (w2: the lightest step)
-        const int64_t wmax = tiles * ((int64_t)l.KC * (l.LBS / 32) + 7);
+        // Ranges so many that no unit, a run of one tile's steps within a range, passes RSTEP_EXACT: any
+        // number while a tile's own steps do not.  Longer tiles: k_rprep weighs a step at most w1 and at
+        // least w2 and adds at most 7 w1 per tile for its decode and a minimum step: W <= w1 wmax, a range
+        // costs T = ceil(W / sl) <= w1 wmax / sl + 1 (256 x 64 blocks: up to twice that) and holds at most
+        // T / w2 + 1 steps.  The 256 x 256 blocks run no half groups there, so that w2 = w1.  (Lighter steps
+        // in this rule, whatever the tile's length, grew the partial sums of long calls 1.6 times: 136 -> 217
+        // GB for 406072 x 87105 x 5304 at L = 1579; a half group saves at most 3/8 of one of 17 or more.)
+        const int64_t tsteps = (int64_t)l.KC * (l.LBS / 32), wmax = tiles * (tsteps + 7);
+        if (tsteps > RSTEP_EXACT) l.halves = 0;
+        const int64_t w1 = l.narrow ? RW1_NARROW : RW1_WIDE, w2 = l.narrow ? RW3_NARROW : w1;   // (w2: the lightest step)
         const int64_t den = (w2 * (RSTEP_EXACT - 2) - 1) / (l.narrow ? 2 : 1);
         int64_t sl = l.q_slots;
-        if (w1 * wmax > sl * den) sl = (w1 * wmax + den - 1) / den;
-        if (sl > (1 << 20)) return false;
+        if (tsteps > RSTEP_EXACT && w1 * wmax > sl * den) sl = (w1 * wmax + den - 1) / den;
+        // (refused: a call that would fill 2^20 ranges, whether or not it needs as many)
+        const int64_t refused = l.narrow ? w1 * wmax - den * (1 << 20) : wmax - (RSTEP_EXACT - 3) * (1 << 20);
+        if (refused > 0) return false;
         l.sk_slots = (int)sl;
         l.F = 0;
         l.S = 1;

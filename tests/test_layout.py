@@ -52,3 +52,31 @@ def test_ragged_last_round_of_narrow_tiles(layout, batch, M, K, L_max, polarity,
     # 256 x 64 blocks, one length: a last round of half-filled tiles stays whole only while it is short
     lay = layout(batch, M, 64, K, L_max, polarity)
     assert lay["narrow"] and lay["S"] == parts
+
+
+@pytest.mark.parametrize("batch,M,N,K,L_max,hint,own_B,most", [
+    (1, 406072, 87105, 5304, 1579, 700, False, 137 * GIB),      # (217 with the lighter steps' ranges)
+    (1, 1060669, 42937, 342, 2277, 1000, False, 18 * GIB),      # (27)
+    (16, 17882, 29643, 22308, 2554, 851, False, 224 * GIB),     # tiles longer than one range may hold (353)
+    (1, 1098945, 12731, 8310, 3703, 370, True, 202 * GIB),
+])
+def test_workspace_of_long_range_divisions(layout, batch, M, N, K, L_max, hint, own_B, most):
+    lay = layout(batch, M, N, K, L_max, hint=hint, own_B=own_B)
+    assert lay["vsplit"] and lay["total"] <= most
+    # every range's steps stay exact where a tile alone has more
+    KC, G = (K + 31) // 32, (L_max + 31) // 32
+    tiles = batch * ((M + 255) // 256) * ((N + 255) // 256)
+    if KC * G > 1 << 14:
+        assert -(-tiles * (KC * G + 7) // lay["sk_slots"]) + 2 <= 1 << 14
+
+
+@pytest.mark.parametrize("batch,M,N,K,L_max,hint,own_B,accepted", [
+    (128, 5815, 50232, 27389, 1039, 103, False, True),
+    (1, 2966264, 7154, 26588, 1463, 146, False, True),
+    (13, 101552, 12575, 86011, 768, 76, True, True),
+    (1, 1 << 21, 1 << 21, 1 << 15, 4096, 100, False, False),
+])
+def test_range_division_limit(layout, batch, M, N, K, L_max, hint, own_B, accepted):
+    # 2^20 ranges of 2^14 steps, whatever a step weighs (no card holds these calls: only the answer matters)
+    lay = layout(batch, M, N, K, L_max, hint=hint, own_B=own_B)
+    assert isinstance(lay, dict) == accepted and (accepted or lay == -2)
