@@ -191,6 +191,7 @@ static bool layout_with(const sc_gemm_desc &d, int cus, int spend, bool cbsg, La
     l.rgen = l.mbm == 2 * BM && lfsr;
     l.tshift = tall ? 6 : 8;
     l.rtiles = tall ? (d.M + TROWS - 1) / TROWS : l.MT / 2;
+    const int bbits = chunk_bits_b(tallC, d.N);
     l.rslots = l.narrow || tall ? 0 : RSLOTS;
     l.halves = l.rgen && !l.narrow && !tall;
     l.KC = (d.K + 31) / 32;
@@ -244,7 +245,7 @@ static bool layout_with(const sc_gemm_desc &d, int cus, int spend, bool cbsg, La
     if (!mul_ok((size_t)l.MT * (size_t)l.words_per_L, (size_t)round_up(d.L_max, MSTEP) * 4, &sz))
         return false;
     if (l.fused) sz = 0;
-    if (l.rgen && !mul_ok(rowsA, (size_t)l.KC * 32, &sz)) return false;
+    if (l.rgen && !mul_ok((size_t)l.rtiles << l.tshift, (size_t)l.KC * 32, &sz)) return false;
     a = align256(a + sz);
     l.stride_batchA = a;
     const size_t baseA = off;
@@ -258,7 +259,7 @@ static bool layout_with(const sc_gemm_desc &d, int cus, int spend, bool cbsg, La
     l.off_Bp = bb;
     if (!mul_ok((size_t)l.NT * (size_t)l.words_per_L, (size_t)l.LBS * 4, &sz)) return false;
     if (l.fused) sz = 0;
-    if (l.rgen && !mul_ok(rowsB, (size_t)l.KC * 32, &sz)) return false;
+    if (l.rgen && !mul_ok(bbits < 8 ? (size_t)1 << bbits : rowsB, (size_t)l.KC * 32, &sz)) return false;
     bb = align256(bb + sz);
     l.stride_batchB = bb;
     const size_t baseB = off;

@@ -49,7 +49,8 @@
 // (the same comparator boundaries) and 0x80 (-128) marking an element >= K or a padding
 // row.  The GEMM builds the fp4 fragments from them.
 //
-// 64-row blocks (tall) read the same chunks, a row tile a quarter of a pair.
+// 64-row blocks (tall): A's chunks a row tile each, bytes [KC][64][32]; B's as above, or with N <= 64 or
+// 128 bytes [KC][64 or 128][32] (chunk_bits_b).
 //
 // N <= 128 with comparator streams and chunks that would not fit the array of sc_gemm_noalloc
 // (fused): no planes or chunks; the GEMM builds its fragments from the int8 rows themselves.
@@ -310,6 +311,11 @@ __host__ __device__ inline int plan_of(int L, int nplans, int pstep, int L_max) 
 __device__ __forceinline__ bool not_serving(const Layout &lay, uint8_t *ws) {
     return (lay.cbsg && ws_ptr<uint32_t>(ws, lay.off_status)[3] == 0u) ||
            (lay.off_skip != 0 && *ws_ptr<uint32_t>(ws, lay.off_skip) != 0u);
+}
+// rows of a block of B's chunks as a shift (A's: Layout::tshift).  A function, as every kernel takes the
+// layout as an argument: 8 bytes more of it (480 of arguments, not 472) cost a small call's launches 0.45 us
+__host__ __device__ inline int chunk_bits_b(int tall, int N) {
+    return !tall || N > 2 * TROWS ? 8 : N > TROWS ? 7 : 6;
 }
 // slots of a row of L cycles in a pair whose plan saves `save` slots and gives L_max `top` slots
 // (top counts whole groups: the slots past the last cycle are zero)

@@ -1650,7 +1650,7 @@ __device__ __forceinline__ uint32_t r_entry(const uint2 (&slots)[8], int side, i
 struct RChunkArgs {
     const int8_t *X[2];
     int64_t ld[2], strideX[2];
-    int rows[2], rows_pad[2], nb[2];
+    int rows[2], nb[2], rbits[2];
     size_t stride_batch[2], off_out[2];
     size_t off_perm;      // side 0 (A) takes its rows in the scheduler's order
     int K, KC;
@@ -1944,8 +1944,9 @@ __global__ __launch_bounds__(256) void k_rprep(RChunkArgs a, Layout lay, uint8_t
     const int nc = min(RC_CH, a.KC - c0);
     uint8_t *wsb = ws + (size_t)b * a.stride_batch[side];
     const int tid = threadIdx.x, hl = tid & 15;         // hl = 2 * chunk + half
-    u4 *out = reinterpret_cast<u4 *>(ws_ptr<uint8_t>(wsb, a.off_out[side])) + (size_t)(r0 >> 8) * a.KC * 512 +
-              (r0 & 255) * 2;
+    const int rb = a.rbits[side];
+    u4 *out = reinterpret_cast<u4 *>(ws_ptr<uint8_t>(wsb, a.off_out[side])) + ((size_t)(r0 >> rb) * a.KC << (rb + 1)) +
+              (r0 & ((1 << rb) - 1)) * 2;
     auto row_of = [&](int rl) {
         const int r = r0 + rl;
         return side == 0 ? ws_ptr<int32_t>(wsb, a.off_perm)[r] : (r < a.rows[side] ? r : -1);
@@ -1973,7 +1974,7 @@ __global__ __launch_bounds__(256) void k_rprep(RChunkArgs a, Layout lay, uint8_t
         __syncthreads();
         for (int k = tid; k < nc * RC_ROWS * 2; k += 256) {
             const int c = k / (RC_ROWS * 2), e = k % (RC_ROWS * 2);
-            out[(size_t)(c0 + c) * 512 + e] = sm[c * RC_CSTRIDE + e];
+            out[((size_t)(c0 + c) << (rb + 1)) + e] = sm[c * RC_CSTRIDE + e];
         }
         return;
     }
@@ -2011,7 +2012,7 @@ __global__ __launch_bounds__(256) void k_rprep(RChunkArgs a, Layout lay, uint8_t
         u4 x;
 #pragma unroll
         for (int j = 0; j < 4; ++j) x[j] = __builtin_amdgcn_alignbyte(t[j + 1], t[j], (uint32_t)at & 3u);
-        out[(size_t)(c0 + c) * 512 + e] = r_finish_half(x, src >= 0 ? a.K - ((c0 + c) * RCH + 16 * (e & 1)) : 0);
+        out[((size_t)(c0 + c) << (rb + 1)) + e] = r_finish_half(x, src >= 0 ? a.K - ((c0 + c) * RCH + 16 * (e & 1)) : 0);
     }
 }
 
@@ -2028,6 +2029,8 @@ hipError_t launch_rprep(const sc_gemm_desc &d, const Layout &lay, const int8_t *
     a.rows[1] = d.N;
     a.nb[0] = d.batch;
     a.nb[1] = lay.nbB;
+    a.rbits[0] = lay.tshift;
+    a.rbits[1] = chunk_bits_b(lay.tall, d.N);
     a.stride_batch[0] = lay.stride_batchA;
     a.stride_batch[1] = lay.stride_batchB;
     a.off_out[0] = lay.off_Ap;
@@ -2852,20 +2855,20 @@ struct TData {
 };
 template <int C>
 struct TSrc {
-    __amdgpu_buffer_rsrc_t a, b;   // the pair's A chunks; the B chunks from the wave's first pair on
+    __amdgpu_buffer_rsrc_t a, b;   // the tile's A chunks; the B chunks from the wave's first pair on
     int voff;                      // the lane's row and half within a 32-row block of a chunk
-    int aoff, boff[C];             // byte offsets of A's rows and the wave's column blocks
+    int bchunk, boff[C];           // bytes of a chunk of B's rows; byte offsets of the wave's column blocks
     uint32_t loA, loB;             // table columns (copy) of A and of B
     const char *lut;
     int KC;
 };
 template <int C>
 __device__ __forceinline__ void t_load(const TSrc<C> &q, int h, TData<C> &d) {
-    const int off = (h >> 1) * 256 * RCH + (h & 1) * 8;
+    const int oa = (h >> 1) * TROWS * RCH + (h & 1) * 8, ob = (h >> 1) * q.bchunk + (h & 1) * 8;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) d.a[i] = __builtin_amdgcn_raw_buffer_load_b64(q.a, q.voff, off + q.aoff + i * 32 * RCH, 0);
+    for (int i = 0; i < 2; ++i) d.a[i] = __builtin_amdgcn_raw_buffer_load_b64(q.a, q.voff, oa + i * 32 * RCH, 0);
 #pragma unroll
-    for (int c = 0; c < C; ++c) d.b[c] = __builtin_amdgcn_raw_buffer_load_b64(q.b, q.voff, off + q.boff[c], 0);
+    for (int c = 0; c < C; ++c) d.b[c] = __builtin_amdgcn_raw_buffer_load_b64(q.b, q.voff, ob + q.boff[c], 0);
 }
 // the table row of element e (0..7) of a lane's half chunk
 __device__ __forceinline__ u4 t_look(const char *lut, u2 v, int e, uint32_t lo) {
@@ -2966,11 +2969,12 @@ __global__ __launch_bounds__(256, 2) void k_tgemm(MGemmArgs g, Layout lay, uint8
     const int4 ps = ws_ptr<int4>(wsa, lay.off_pair)[rt];   // {groups, plan, slots saved, slots of L_max}
     const int32_t *perm = ws_ptr<int32_t>(wsa, lay.off_perm) + rt * TROWS;
     const int32_t *Ls = ws_ptr<int32_t>(wsa, lay.off_Ls) + rt * TROWS;
-    const size_t pairb = (size_t)g.KC * 256 * RCH;
+    const int bbits = chunk_bits_b(C, g.N);
+    const size_t tileb = (size_t)g.KC * TROWS * RCH, pairb = ((size_t)g.KC * RCH) << bbits;
     const int col0 = tw * W + 32 * C * w;                  // the wave's first column
     const bool act = col0 < g.N;                           // (else it only takes part in the table fills)
     TSrc<C> q;
-    q.a = __builtin_amdgcn_make_buffer_rsrc(ws_ptr<uint8_t>(wsa, lay.off_Ap) + (size_t)(rt >> 2) * pairb, 0, (int)pairb,
+    q.a = __builtin_amdgcn_make_buffer_rsrc(ws_ptr<uint8_t>(wsa, lay.off_Ap) + (size_t)rt * tileb, 0, (int)tileb,
                                             0x00020000);
     // (the wave's columns lie in its first 256-row pair of B or the next one; a block of columns past
     // the last pair reads the first block instead and goes unstored)
@@ -2978,7 +2982,7 @@ __global__ __launch_bounds__(256, 2) void k_tgemm(MGemmArgs g, Layout lay, uint8
     q.b = __builtin_amdgcn_make_buffer_rsrc(ws_ptr<uint8_t>(wsbB, lay.off_Bp) + (size_t)p0 * pairb, 0, (int)(np * pairb),
                                             0x00020000);
     q.voff = i32 * RCH + grp * 16;
-    q.aoff = (rt & 3) * TROWS * RCH;
+    q.bchunk = RCH << bbits;
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         const int col = act && col0 + 32 * c < g.N ? col0 + 32 * c : p0 * 256;

@@ -80,3 +80,15 @@ def test_range_division_limit(layout, batch, M, N, K, L_max, hint, own_B, accept
     # 2^20 ranges of 2^14 steps, whatever a step weighs (no card holds these calls: only the answer matters)
     lay = layout(batch, M, N, K, L_max, hint=hint, own_B=own_B)
     assert isinstance(lay, dict) == accepted and (accepted or lay == -2)
+
+
+@pytest.mark.parametrize("batch,M,N,K,own_B,most", [
+    (815, 1, 29, 7782, False, 520 * MIB),        # (1.6 GiB with A's chunks in whole pairs of 256 rows)
+    (815, 1, 29, 7782, True, 910 * MIB),         # (B's too: 3.1)
+    (128, 100, 100, 768, True, 25 * MIB),        # (48)
+    (1, 48, 3072, 768, False, 10 * MIB),
+])
+def test_workspace_of_few_rows_and_columns(layout, batch, M, N, K, own_B, most):
+    # chunks of the 64 (128) rows and columns that 64-row blocks read, and not of 256
+    lay = layout(batch, M, N, K, 64, own_B=own_B)
+    assert lay["tall"] and lay["total"] <= most
