@@ -85,7 +85,7 @@ def test_range_division_limit(layout, batch, M, N, K, L_max, hint, own_B, accept
 @pytest.mark.parametrize("batch,M,N,K,own_B,most", [
     (815, 1, 29, 7782, False, 520 * MIB),        # (1.6 GiB with A's chunks in whole pairs of 256 rows)
     (815, 1, 29, 7782, True, 910 * MIB),         # (B's too: 3.1)
-    (128, 100, 100, 768, True, 25 * MIB),        # (48)
+    (128, 100, 100, 768, True, 33 * MIB),         # (56)
     (1, 48, 3072, 768, False, 10 * MIB),
 ])
 def test_workspace_of_few_rows_and_columns(layout, batch, M, N, K, own_B, most):
