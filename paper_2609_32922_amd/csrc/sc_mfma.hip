@@ -1923,8 +1923,11 @@ constexpr int RC_RSTRIDE = RC_RAW * 4 + 1;       // dwords per row of them in LD
 constexpr int RC_LDS = RC_ROWS * (RC_RSTRIDE + 1) / 4;   // u4: those and a word per row
 static_assert(RC_LDS >= RC_CH * RC_CSTRIDE, "the aligned rows' chunks fit");
 __global__ __launch_bounds__(256) void k_rprep(RChunkArgs a, Layout lay, uint8_t *ws) {
-    // (a C-BSG call with other lengths, one batch entry: its chunks go unread)
-    if (lay.cbsg && a.batch == 1 && blockIdx.x != 0 && ws_ptr<int4>(ws, lay.off_pair)[lay.rtiles].z != a.L_max) return;
+    // (C-BSG: a batch entry with other lengths, whose chunks go unread, as all do then: 16 x 325 x 1091 x
+    // 2000 of mixed lengths 1275 us a call with them, 1263 so)
+    auto unread = [&](int b) {
+        return lay.cbsg && ws_ptr<int4>(ws + (size_t)b * lay.stride_batchA, lay.off_pair)[lay.rtiles].z != a.L_max;
+    };
     __shared__ u4 sm[RC_LDS];                 // (one region for the three kinds of block)
     static_assert(UNIT_PAIRS * sizeof(int4) <= sizeof(sm), "the prep block's pairs fit");
     if (blockIdx.x == 0) {
@@ -1932,6 +1935,7 @@ __global__ __launch_bounds__(256) void k_rprep(RChunkArgs a, Layout lay, uint8_t
         return;
     }
     if ((int)blockIdx.x <= a.nt) {
+        if (unread(0)) return;
         table_block((int)blockIdx.x - 1, a, lay, ws, reinterpret_cast<uint32_t *>(sm));
         return;
     }
@@ -1940,6 +1944,7 @@ __global__ __launch_bounds__(256) void k_rprep(RChunkArgs a, Layout lay, uint8_t
     if (side) u -= a.na;
     const int b = u / (a.gx[side] * a.gy);
     u -= b * a.gx[side] * a.gy;
+    if (unread(b)) return;
     const int r0 = (u % a.gx[side]) * RC_ROWS, c0 = (u / a.gx[side]) * RC_CH;
     const int nc = min(RC_CH, a.KC - c0);
     uint8_t *wsb = ws + (size_t)b * a.stride_batch[side];

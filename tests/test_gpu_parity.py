@@ -841,6 +841,7 @@ CBSG_TABLES = [
     (3, 2100, 2050, 300, 129, "short", 0, False, 811),
     (1, 4000, 3000, 288, 128, "random", 1, False, 813),
     (2, 3000, 2050, 300, 129, "below", 0, True, 815),
+    (3, 2100, 2050, 300, 129, "random", 1, False, 817),
 ]
 
 
