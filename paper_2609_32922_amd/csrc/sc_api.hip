@@ -477,13 +477,30 @@ bool make_cbsg_layout(const sc_gemm_desc &d, int cus, const Layout &planes, Layo
         return false;
     if (round_up(d.K, 32) * round_up(d.L_max, 32) >= MFMA_EXACT || !layout_with(d, cus, LAY_FULL, true, lay) || !lay->rgen)
         return false;
-    const size_t base = planes.total;
-    if (lay->total > MOST_EXTRA || lay->total > SIZE_MAX - base) return false;
-    for (size_t *o : {&lay->off_rA, &lay->off_rB, &lay->off_status, &lay->off_CA, &lay->off_plan, &lay->off_pslots,
-                      &lay->off_rtab, &lay->off_perm, &lay->off_Ls, &lay->off_tileL, &lay->off_tileOff, &lay->off_pair,
-                      &lay->off_Ap, &lay->off_Bp, &lay->off_part, &lay->off_units, &lay->off_tinfo, &lay->off_slot,
-                      &lay->total})
-        *o += base;
+    // The tables lie where the planes will if the tables do not serve: their rows and chunks of a batch entry
+    // in that entry's planes (16 bytes and more an element quad and octet of cycles, against 4 and 8 a row), their
+    // partial sums behind the last entry's, or in the planes path's; the rest, 100 KB at most, behind it all.
+    // (Beside each other they added up to 8 GiB to calls that nearly fill the card.)
+    Layout &t = *lay;
+    const size_t small = t.off_perm, parts = t.total - t.off_part, rows = t.off_perm;
+    const size_t roomA = planes.stride_batchA - (planes.off_Ap - planes.off_perm), roomB = planes.stride_batchB;
+    if (t.vsplit || t.total > MOST_EXTRA || t.stride_batchA > roomA || t.stride_batchB > roomB) return false;
+    for (size_t *o : {&t.off_perm, &t.off_Ls, &t.off_tileL, &t.off_tileOff, &t.off_pair, &t.off_Ap})
+        *o += planes.off_Ap - rows;
+    t.off_Bp = planes.off_Bp;
+    if (parts <= roomB - t.stride_batchB)
+        t.off_part = planes.off_Bp + (size_t)(planes.nbB - 1) * planes.stride_batchB + t.stride_batchB;
+    else if (parts <= roomA - t.stride_batchA)
+        t.off_part = planes.off_Ap + (size_t)(d.batch - 1) * planes.stride_batchA + t.stride_batchA;
+    else
+        t.off_part = planes.off_part;
+    t.stride_batchA = planes.stride_batchA;
+    t.stride_batchB = planes.stride_batchB;
+    if (parts + small > SIZE_MAX - planes.total) return false;
+    const size_t base = t.off_part + parts > planes.total ? t.off_part + parts : planes.total;
+    for (size_t *o : {&t.off_rA, &t.off_rB, &t.off_status, &t.off_CA, &t.off_plan, &t.off_pslots, &t.off_rtab}) *o += base;
+    t.off_units = t.off_tinfo = t.off_slot = base;      // (no range division)
+    t.total = base + small;
     // a call whose planes fit sc_gemm_noalloc's array keeps fitting it
     return planes.total > SC_NOALLOC_WORKSPACE_BYTES || lay->total <= SC_NOALLOC_WORKSPACE_BYTES;
 }

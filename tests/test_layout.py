@@ -92,3 +92,35 @@ def test_workspace_of_few_rows_and_columns(layout, batch, M, N, K, own_B, most):
     # chunks of the 64 (128) rows and columns that 64-row blocks read, and not of 256
     lay = layout(batch, M, N, K, 64, own_B=own_B)
     assert lay["tall"] and lay["total"] <= most
+
+
+@pytest.mark.parametrize("batch,M,N,K,L_max,polarity,own_B,grows", [
+    (1, 6304, 3072, 768, 128, 0, False, 1 * MIB),       # (34 MiB beside planes of 499)
+    (1, 381, 287391, 21327, 81, 1, False, 1 * MIB),     # (8 GiB beside planes of 275)
+    (1, 1645729, 679, 3987, 82, 0, False, 1 * MIB),     # (6 GiB beside 270)
+    (16, 325, 1091, 2000, 96, 1, True, 1 * MIB),
+    (24, 8224, 64, 130, 256, 0, True, 1 * MIB),
+    (1000, 129, 64, 500, 128, 0, True, 1 * MIB),
+])
+def test_workspace_of_cbsg_tables(layout, batch, M, N, K, L_max, polarity, own_B, grows):
+    # the tables lie where the planes will if they do not serve
+    planes = layout(batch, M, N, K, L_max, polarity, rng=1, own_B=own_B)
+    tables = layout(batch, M, N, K, L_max, polarity, rng=1, own_B=own_B, tables=True)
+    assert planes["total"] <= tables["total"] <= planes["total"] + grows
+
+
+def test_cbsg_tables_over_every_planes_layout(layout):
+    # each part of the tables inside the planes' part it lies on: over sizes where either is tightest
+    n = 0
+    for K in (1, 3, 16, 17, 33, 64, 97, 1000):
+        for L_max in (1, 7, 8, 9, 64, 255, 256):
+            for M, N in ((1, 1 << 20), (64, 70000), (100, 40000), (129, 60), (300, 300), (70000, 100), (1 << 20, 1)):
+                batch = max(1, int(4.1e11 // (M * N * K * L_max)) + 1)
+                if batch > 1 << 20:
+                    continue
+                lay = layout(batch, M, N, K, L_max, rng=1, own_B=True, tables=True)
+                if isinstance(lay, dict):
+                    n += 1
+                    planes = layout(batch, M, N, K, L_max, rng=1, own_B=True)
+                    assert lay["total"] <= planes["total"] * 1.01 + MIB, (batch, M, N, K, L_max)
+    assert n > 100
