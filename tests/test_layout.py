@@ -124,3 +124,17 @@ def test_cbsg_tables_over_every_planes_layout(layout):
                     planes = layout(batch, M, N, K, L_max, rng=1, own_B=True)
                     assert lay["total"] <= planes["total"] * 1.01 + MIB, (batch, M, N, K, L_max)
     assert n > 100
+
+
+@pytest.mark.parametrize("batch,M,N,K,L_max,hint,fused", [
+    (1, 24589, 116, 1983, 8, 0, True),
+    (8, 45067, 87, 3067, 8, 0, True),
+    (1, 40413, 118, 2959, 16, 5, True),
+    (1, 2196, 114, 71, 8, 2, False),
+    (8, 3811, 79, 1032, 16, 8, False),
+    (1, 24589, 116, 400, 64, 0, False),
+])
+def test_few_columns_and_short_streams(layout, batch, M, N, K, L_max, hint, fused):
+    # an octet of cycles costs 64-row blocks a whole group of 32 slots: k_fgemm where the call is large
+    lay = layout(batch, M, N, K, L_max, hint=hint)
+    assert bool(lay["fused"]) == fused and bool(lay["tall"]) != fused
