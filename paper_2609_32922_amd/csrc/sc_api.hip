@@ -108,12 +108,15 @@ static int device_cus() {
     return n;
 }
 
-// How much of the workspace a layout may spend: everything; no slot plans; int8 chunks only where
-// the 128-row kernels could not take their operands as they are
-enum { LAY_FULL, LAY_ONE_PLAN, LAY_LEAST };
+// How much of the workspace a layout may spend: everything; slot plans of no cycle and of all cycles
+// only; no slot plans; int8 chunks only where the 128-row kernels could not take their operands as they are
+enum { LAY_FULL, LAY_TWO_PLANS, LAY_ONE_PLAN, LAY_LEAST };
 
-// cbsg: of the tables of a C-BSG call (d's source is then taken as the LFSR)
-static bool layout_with(const sc_gemm_desc &d, int cus, int spend, bool cbsg, Layout *lay) {
+// cbsg: of the tables of a C-BSG call (d's source is then taken as the LFSR); parts: fewer than MAX_SPLIT,
+// 64-row blocks in at most so many parts (if exactness allows), or 256-row blocks (0); est: the estimated
+// time that the blocks were chosen by
+static bool layout_with(const sc_gemm_desc &d, int cus, int spend, bool cbsg, Layout *lay, int parts = MAX_SPLIT,
+                        double *est = nullptr) {
     Layout l{};
     l.cbsg = cbsg;
     l.cus = cus > 0 ? cus : DEFAULT_CUS;
@@ -166,9 +169,9 @@ static bool layout_with(const sc_gemm_desc &d, int cus, int spend, bool cbsg, La
     if (far && few && w.Smin < 2) w.Smin = 2;
     int tallC = 0, tallS = 1;
     if (lfsr && !l.narrow && !l.fused && (few || (spend != LAY_LEAST && !far))) {
-        double best = few ? 1e30 : est_wide(w);
+        double best = few || (parts > 0 && parts < MAX_SPLIT) ? 1e30 : est_wide(w);
         for (int c : {1, 2, 4, 5})
-            for (int S = w.Smin; S <= (c == 5 ? 1 : w.Smin > MAX_SPLIT ? w.Smin : MAX_SPLIT); ++S) {
+            for (int S = w.Smin; (few || parts > 0) && S <= (c == 5 ? 1 : w.Smin > parts ? w.Smin : parts); ++S) {
                 if (S > w.Smin && w.KC * w.gmean / S < TPART) break;
                 // (units are counted in 32 bits)
                 if (w.batch * ((d.M + TROWS - 1) / TROWS) * ceil(d.N / (128.0 * c)) * S > INT_MAX) break;
@@ -179,6 +182,14 @@ static bool layout_with(const sc_gemm_desc &d, int cus, int spend, bool cbsg, La
                     tallS = S;
                 }
             }
+        if (est != nullptr) {
+            // (without plans a slot is a cycle)
+            if (spend == LAY_ONE_PLAN || (spend == LAY_TWO_PLANS && !one_length)) {
+                w.gmean = ceil(Lmean / 32.0);
+                w.gmax = (d.L_max + 31) / 32;
+            }
+            *est = tallC > 0 ? est_tall(w, tallC, tallS) : est_wide(w);
+        }
     }
     const bool tall = tallC > 0;
     if (few && !tall && !l.fused) return false;
@@ -215,8 +226,8 @@ static bool layout_with(const sc_gemm_desc &d, int cus, int spend, bool cbsg, La
     // At most 32 plans past the first, and at most PLAN_GROUPS tables.
     l.nplans = 1;
     l.pstep = LCH;
-    if (spend == LAY_FULL && !cbsg && l.rgen && l.LBS > 32 && (int64_t)l.KC * 32 * l.LBS < MFMA_EXACT) {
-        const int n = PLAN_GROUPS / (l.LBS / 32) < 32 ? PLAN_GROUPS / (l.LBS / 32) : 32;
+    if (spend <= LAY_TWO_PLANS && !cbsg && l.rgen && l.LBS > 32 && (int64_t)l.KC * 32 * l.LBS < MFMA_EXACT) {
+        const int n = spend == LAY_TWO_PLANS ? 1 : PLAN_GROUPS / (l.LBS / 32) < 32 ? PLAN_GROUPS / (l.LBS / 32) : 32;
         l.pstep = (int)round_up((d.L_max + n - 1) / n, 8);
         l.nplans = 1 + (d.L_max + l.pstep - 1) / l.pstep;
     }
@@ -474,12 +485,36 @@ bool make_layout(const sc_gemm_desc &d, int cus, Layout *lay) {
         Layout least;
         if (layout_with(d, cus, LAY_LEAST, false, &least) && least.total < lay->total - MOST_EXTRA) *lay = least;
     }
-    // a call that fits sc_gemm_noalloc's array without the tables of the slot plans, or without
-    // chunks of its operands, keeps fitting it
-    for (int spend = LAY_ONE_PLAN; lay->total > SC_NOALLOC_WORKSPACE_BYTES && spend <= LAY_LEAST; ++spend) {
-        Layout less;
-        if (layout_with(d, cus, spend, false, &less) && less.total <= SC_NOALLOC_WORKSPACE_BYTES) *lay = less;
+    // A call that fits sc_gemm_noalloc's array in some layout keeps fitting it: the one estimated to take the
+    // least time of fewer parts, of fewer plans, of none, and of no chunks if none does not fit either.  (500
+    // calls of up to 9000 rows, with 64 to 220 MiB in full: 1.06 times the full layout's time in the middle,
+    // where going without plans at once took 1.68 times, as long as before there were any.  2200 x 1024 x
+    // 1024 at L = 256: 66.6 MiB in 7 parts, 57.8 in 6)
+    if (lay->total <= SC_NOALLOC_WORKSPACE_BYTES) return true;
+    Layout best, l;
+    double least_t = 1e30;
+    auto consider = [&](int spend, int parts) {
+        double t = 1e29;
+        if (!layout_with(d, cus, spend, false, &l, parts, &t) || l.total > SC_NOALLOC_WORKSPACE_BYTES) return false;
+        if (t < least_t) {
+            best = l;
+            least_t = t;
+        }
+        return true;
+    };
+    // (a call that fits neither without plans nor without chunks never did)
+    if (!consider(LAY_ONE_PLAN, MAX_SPLIT) && !consider(LAY_LEAST, MAX_SPLIT)) return true;
+    if (lay->off_part < SC_NOALLOC_WORKSPACE_BYTES) {
+        int S = MAX_SPLIT - 1;
+        if (lay->tall) {
+            const double part = (double)(lay->total - lay->off_part) / lay->S;
+            S = (int)fmin((SC_NOALLOC_WORKSPACE_BYTES - lay->off_part) / part, lay->S - 1);
+        }
+        while (S >= 1 && !consider(LAY_FULL, S)) --S;
     }
+    if (lay->tall) consider(LAY_FULL, 0);
+    if (!consider(LAY_TWO_PLANS, MAX_SPLIT)) consider(LAY_TWO_PLANS, 0);
+    *lay = best;
     return true;
 }
 

@@ -138,3 +138,30 @@ def test_few_columns_and_short_streams(layout, batch, M, N, K, L_max, hint, fuse
     # an octet of cycles costs 64-row blocks a whole group of 32 slots: k_fgemm where the call is large
     lay = layout(batch, M, N, K, L_max, hint=hint)
     assert bool(lay["fused"]) == fused and bool(lay["tall"]) != fused
+
+
+ARRAY = 64 * MIB      # sc_gemm_noalloc's
+
+
+@pytest.mark.parametrize("batch,M,N,K,L_max,polarity", [
+    (1, 2200, 1024, 1024, 256, 0),       # 66.6 MiB in 7 parts
+    (1, 577, 4096, 1024, 256, 0),
+    (1, 514, 4608, 1152, 192, 1),
+    (1, 1700, 1152, 4608, 192, 0),
+    (1, 2669, 3969, 748, 128, 0),        # 131.6
+    (1, 4815, 768, 768, 512, 0),         # 65 with the tables of all plans
+    (512, 256, 72, 256, 192, 0),
+])
+def test_calls_near_the_array_keep_their_plans(layout, batch, M, N, K, L_max, polarity):
+    lay = layout(batch, M, N, K, L_max, polarity)
+    assert lay["total"] <= ARRAY and lay["nplans"] > 1 and lay["rgen"]
+
+
+@pytest.mark.parametrize("N,K", [(768, 768), (3072, 768), (768, 3072), (1024, 1024), (4096, 1024), (1024, 4096),
+                                 (1152, 1152), (4608, 1152), (1152, 4608)])
+def test_no_row_count_loses_the_plans(layout, N, K):
+    # one row length: the array never costs a call its plans (it did for 7 % of these)
+    for L_max in (64, 128, 192, 256):
+        for M in range(150, 8192, 97):
+            lay = layout(1, M, N, K, L_max)
+            assert lay["nplans"] > 1, (M, L_max, lay)
