@@ -283,17 +283,26 @@ __device__ __forceinline__ void mplanes_block(const MPlaneArgs &a, uint8_t *ws, 
     }
 }
 
+// A launch of n blocks of 256 threads, numbered flat_block(): a grid dimension holds fewer than 2^32
+// threads, which 2^24 blocks pass (2^30 rows of 32 bytes in chunks).  (A row of the grid has a fixed
+// length: reading the grid's size would add arguments to the kernel.)
+constexpr int64_t GRID_ROW = 1 << 22;
+static dim3 flat_grid(int64_t n) {
+    return n <= GRID_ROW ? dim3((unsigned)n) : dim3((unsigned)GRID_ROW, (unsigned)((n + GRID_ROW - 1) / GRID_ROW));
+}
+__device__ __forceinline__ int flat_block() { return (int)(blockIdx.y * (unsigned)GRID_ROW + blockIdx.x); }
+
 // both sides in one launch: blocks [0, nA) are A's grid (gxA x gy x batch), the rest B's (gxB x gy
 // x nbB), so B's blocks fill A's last wave
 template <int POL>
 __global__ __launch_bounds__(256) void k_mplanes(MPlaneArgs a, MPlaneArgs bb, int gxA, int gxB, int gy, int nA,
-                                                 uint8_t *ws) {
+                                                 int nB, uint8_t *ws) {
     __shared__ MPlaneShared sh;
     if (a.off_skip != 0 && *ws_ptr<uint32_t>(ws, a.off_skip) != 0u) return;
-    const int bid = blockIdx.x;
+    const int bid = flat_block();
     if (bid < nA) {
         mplanes_block<POL, true>(a, ws, sh, bid % gxA, (bid / gxA) % gy, bid / (gxA * gy));
-    } else {
+    } else if (bid - nA < nB) {
         const int v = bid - nA;
         mplanes_block<POL, false>(bb, ws, sh, v % gxB, (v / gxB) % gy, v / (gxB * gy));
     }
@@ -339,13 +348,14 @@ hipError_t launch_mplanes(const sc_gemm_desc &d, const Layout &lay, const int8_t
     pb.off_r = lay.off_rB;
     pb.off_CA = 0;
     const dim3 gB((unsigned)(lay.NT * pb.nchunk), qgroups, (unsigned)lay.nbB);
-    const int nA = (int)(gA.x * gA.y * gA.z), nB = (int)(gB.x * gB.y * gB.z);
+    const int64_t nA = (int64_t)gA.x * gA.y * gA.z, nB = (int64_t)gB.x * gB.y * gB.z;
+    if (nA + nB > INT_MAX - GRID_ROW) return hipErrorInvalidValue;
     if (d.polarity == SC_BIPOLAR_XNOR)
-        hipLaunchKernelGGL((k_mplanes<SC_BIPOLAR_XNOR>), dim3((unsigned)(nA + nB)), dim3(256), 0, st, pa, pb,
-                           (int)gA.x, (int)gB.x, (int)qgroups, nA, ws);
+        hipLaunchKernelGGL((k_mplanes<SC_BIPOLAR_XNOR>), flat_grid(nA + nB), dim3(256), 0, st, pa, pb,
+                           (int)gA.x, (int)gB.x, (int)qgroups, (int)nA, (int)nB, ws);
     else
-        hipLaunchKernelGGL((k_mplanes<SC_UNIPOLAR_AND_SM>), dim3((unsigned)(nA + nB)), dim3(256), 0, st, pa, pb,
-                           (int)gA.x, (int)gB.x, (int)qgroups, nA, ws);
+        hipLaunchKernelGGL((k_mplanes<SC_UNIPOLAR_AND_SM>), flat_grid(nA + nB), dim3(256), 0, st, pa, pb,
+                           (int)gA.x, (int)gB.x, (int)qgroups, (int)nA, (int)nB, ws);
     return hipGetLastError();
 }
 
@@ -1930,21 +1940,22 @@ __global__ __launch_bounds__(256) void k_rprep(RChunkArgs a, Layout lay, uint8_t
     };
     __shared__ u4 sm[RC_LDS];                 // (one region for the three kinds of block)
     static_assert(UNIT_PAIRS * sizeof(int4) <= sizeof(sm), "the prep block's pairs fit");
-    if (blockIdx.x == 0) {
+    const int bid = flat_block();
+    if (bid == 0) {
         prep_block(a, lay, ws, reinterpret_cast<int4 *>(sm));
         return;
     }
-    if ((int)blockIdx.x <= a.nt) {
+    if (bid <= a.nt) {
         if (unread(0)) return;
-        table_block((int)blockIdx.x - 1, a, lay, ws, reinterpret_cast<uint32_t *>(sm));
+        table_block(bid - 1, a, lay, ws, reinterpret_cast<uint32_t *>(sm));
         return;
     }
-    int u = (int)blockIdx.x - 1 - a.nt;
+    int u = bid - 1 - a.nt;
     const int side = u >= a.na ? 1 : 0;
     if (side) u -= a.na;
     const int b = u / (a.gx[side] * a.gy);
     u -= b * a.gx[side] * a.gy;
-    if (unread(b)) return;
+    if (b >= a.nb[side] || unread(b)) return;      // (blocks past the last, of a grid in rows)
     const int r0 = (u % a.gx[side]) * RC_ROWS, c0 = (u / a.gx[side]) * RC_CH;
     const int nc = min(RC_CH, a.KC - c0);
     uint8_t *wsb = ws + (size_t)b * a.stride_batch[side];
@@ -2062,9 +2073,9 @@ hipError_t launch_rprep(const sc_gemm_desc &d, const Layout &lay, const int8_t *
     a.gx[1] = lay.narrow ? 1 : lay.tall ? (d.N + RC_ROWS - 1) / RC_ROWS : lay.NT * BN / RC_ROWS;
     a.gy = (lay.KC + RC_CH - 1) / RC_CH;
     const int64_t na = (int64_t)d.batch * a.gx[0] * a.gy, nb = (int64_t)lay.nbB * a.gx[1] * a.gy;
-    if (1 + a.nt + na + nb > INT_MAX) return hipErrorInvalidValue;
+    if (1 + a.nt + na + nb > INT_MAX - GRID_ROW) return hipErrorInvalidValue;
     a.na = (int)na;
-    hipLaunchKernelGGL(k_rprep, dim3((unsigned)(1 + a.nt + na + nb)), dim3(256), 0, st, a, lay, ws);
+    hipLaunchKernelGGL(k_rprep, flat_grid(1 + a.nt + na + nb), dim3(256), 0, st, a, lay, ws);
     return hipGetLastError();
 }
 

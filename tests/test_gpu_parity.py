@@ -896,3 +896,27 @@ def test_blocks_of_256(dev, oracle_mod, case):
         order = np.argsort(-g.L[b], kind="stable")
         rows = np.unique(np.concatenate([_sample(M, rng, 8), order[::max(1, M // 24)], order[:3], order[-3:]]))
         _compare(g, b, rows, np.arange(N), out, cnt, oracle_mod, "wide%s b%d" % (case, b))
+
+
+def test_more_blocks_than_a_grid_dimension(dev, oracle_mod):
+    # 60000 entries of 17920 rows: 16.8 million chunk blocks of 64 rows, more than 2^32 threads
+    import torch
+    import paper_2609_32922_amd as scg
+    batch, M, N, K, L_max = 60000, 17920, 1, 1, 8
+    if torch.cuda.mem_get_info(dev)[0] < 90 << 30:
+        pytest.skip("needs 60 GB of device memory")
+    gen = torch.Generator(device=dev).manual_seed(901)
+    _note("more chunk blocks than a grid dimension holds")
+    A = torch.randint(-127, 128, (batch, M, K), generator=gen, device=dev, dtype=torch.int8)
+    B = torch.randint(-127, 128, (1, N, K), generator=gen, device=dev, dtype=torch.int8)
+    sA = torch.full((batch, M), 0.5, device=dev)
+    sB = torch.full((1, N), 0.25, device=dev)
+    L = torch.full((batch, M), L_max, dtype=torch.int32, device=dev)
+    out, _ = scg.gemm(A, sA, B, sB, L, L_max=L_max, seed=901, check_status=True)
+    for b in (0, 1, 29999, 59998, 59999):
+        _, o_ref = oracle_mod.sc_gemm(A[b].cpu().numpy(), B[0].cpu().numpy(), sA[b].cpu().numpy(), sB[0].cpu().numpy(),
+                                      L[b].cpu().numpy(), L_max, 0, 901)
+        o = out[b].cpu().numpy().astype(np.float64)
+        assert np.all(np.abs(o - o_ref) <= REL_TOL * np.abs(o_ref)), b
+    del A, sA, L, out
+    torch.cuda.empty_cache()
