@@ -100,8 +100,7 @@ FUZZ = [
     (2, 140, 131, 65, 48, 0, 1, True, 19),
     (1, 64, 64, 1000, 24, 0, 1, False, 21),
     (1, 200, 150, 7, 512, 400, 0, False, 23),
-    # N <= 128: the MFMA engine builds its fp4 fragments from the int8 rows (unaligned rows,
-    # broadcast B, a split k-range with few tiles, the octet table changing every stage)
+    # N <= 128 (unaligned rows, broadcast B, a split k-range with few tiles)
     (1, 300, 100, 33, 70, 0, 0, False, 25),
     (2, 257, 128, 65, 300, 10, 1, True, 27),
     (3, 70, 64, 130, 64, 0, 0, False, 29),
@@ -351,8 +350,8 @@ def test_rgen_length_ladders(dev, oracle_mod, case, polarity):
 
 
 INT8_MIN_SHAPES = [
-    # M, N, K, rng: int8-chunk GEMM (rows copied bytewise, then 16 bytes at a time), 128-row
-    # planes GEMM (M <= 128), fragments from int8 rows (N <= 128), 256-row planes GEMM (C-BSG)
+    # M, N, K, rng: int8-chunk GEMM (rows copied bytewise, then 16 bytes at a time; few rows; few
+    # columns), 256-row planes GEMM (C-BSG)
     (290, 300, 70, 0), (290, 300, 96, 0), (100, 300, 70, 0), (290, 100, 70, 0), (290, 300, 70, 1),
 ]
 
@@ -656,14 +655,14 @@ def test_exact_at_the_bound(dev, oracle_mod, polarity):
 
 
 PAST_BOUND = [
-    # M, N, K, L_max, rng: every GEMM variant past K * L_max = 2^24: fragments
-    # from int8 rows (N <= 128), 128-row planes (M <= 128), int8 chunks in 256 x 256 and in
-    # 256 x 64 blocks, and with C-BSG the 256-row and 128-row planes GEMMs
+    # M, N, K, L_max, rng: GEMM variants past K * L_max = 2^24: 64-row blocks with few columns, few rows and
+    # neither, 256 x 64 and 256 x 256 blocks, and with C-BSG the 256-row and 128-row planes GEMMs
     # (the planes cases sit just past the bound: their planes take (M + N) K L / 2 bytes)
     (3, 5, 65536, 512, 0),
     (3, 129, 4128, 4096, 0),
     (300, 300, 16384, 2048, 0),
     (300, 17, 16384, 2048, 0),
+    (2600, 2600, 16416, 1024, 0),
     (200, 200, 65600, 256, 1),
     (3, 5, 65600, 256, 1),
 ]
@@ -747,12 +746,14 @@ TALL = [
     (1, 65, 130, 33, 70, "random", 0, False, 703),      # C = 1 whole
     (1, 96, 700, 512, 128, "uniform", 0, False, 705),   # C = 1 in 8 parts
     (1, 1, 3, 1000, 300, "uniform", 1, False, 707),
-    (20, 700, 600, 33, 96, "skew", 1, False, 709),      # C = 2
-    (1, 1025, 2000, 640, 128, "skew", 0, False, 711),   # C = 2 in parts
+    (20, 700, 600, 33, 96, "skew", 1, False, 709),      # C = 5
+    (1, 1025, 2000, 640, 128, "skew", 0, False, 711),   # C = 4 in 7 parts, int16
     (1, 900, 3000, 100, 64, "uniform", 1, False, 713),
-    (1, 900, 3000, 900, 64, "uniform", 0, False, 715),  # C = 4 in parts
+    (1, 900, 3000, 900, 64, "uniform", 0, False, 715),  # C = 4 in 5 parts, int16
     (60, 140, 620, 40, 64, "random", 0, True, 717),     # C = 5
-    (40, 129, 577, 64, 512, "skew", 0, False, 719),
+    (40, 129, 577, 64, 512, "skew", 0, False, 719),     # C = 2
+    (1, 197, 3072, 768, 128, "skew", 0, False, 725),    # C = 2 in 8 parts, int16 (one image)
+    (1, 257, 2657, 1192, 32, "random", 1, False, 727),
     (3, 130, 129, 0, 40, "random", 1, False, 721),      # K = 0
     (1, 100, 100, 40032, 3352, "uniform", 0, False, 723),   # 9 parts (exactness)
 ]
@@ -920,3 +921,124 @@ def test_more_blocks_than_a_grid_dimension(dev, oracle_mod):
         assert np.all(np.abs(o - o_ref) <= REL_TOL * np.abs(o_ref)), b
     del A, sA, L, out
     torch.cuda.empty_cache()
+
+
+# k_fgemm: few columns, fragments from the int8 rows themselves.  Taken for long A and streams of 8 cycles or
+# less, and where an operand's chunks would not fit the array of sc_gemm_noalloc.  Both polarities, mixed lengths
+# with rows of 0, several batch entries, shared and own B, rows at every byte alignment, whole tiles,
+# parts for balance and parts for exactness.
+FGEMM = [
+    # batch, M, N, K, L_max, lengths, polarity, broadcast_B, seed
+    (3, 15000, 101, 1001, 8, "random", 1, True, 921),
+    (2, 20000, 66, 4001, 7, "random", 0, False, 923),
+    (1, 30000, 100, 2400, 200, "random", 1, False, 925),        # 2 parts
+    (1, 1100, 99, 65536, 300, "random", 0, False, 927),         # 8 parts, past 2^24
+    (1, 1030, 70, 66001, 272, "uniform", 1, False, 929),
+    (1, 41000, 128, 1600, 1, "uniform", 0, False, 931),
+]
+
+
+@pytest.mark.parametrize("case", FGEMM, ids=[str(c) for c in FGEMM])
+def test_fragments_from_int8_rows(dev, oracle_mod, case):
+    batch, M, N, K, L_max, kind, pol, bcast, seed = case
+    rng = np.random.default_rng(seed)
+    g = W.random_gemm(rng, batch, M, N, K, L_max, pol, seed, broadcast_B=bcast,
+                      uniform_L=L_max if kind == "uniform" else None)
+    g.L[:, 5] = 0
+    g.A[:, 0] = 127
+    g.B[:, 0] = 127 if pol == 0 else -127
+    g.A[:, 7, ::3] = -128
+    _note("fragments from int8 rows %s" % (case,))
+    out, cnt = _run(g, dev)
+    for b in sorted({0, batch - 1}):
+        rows = np.union1d(_sample(M, rng, 8 if K > 10000 else 40), [0, 5, 7])
+        cols = np.arange(N) if K < 10000 else np.union1d([0, N - 1], rng.choice(N, 5))
+        _compare(g, b, rows, cols, out, cnt, oracle_mod, "fgemm%s b%d" % (case, b))
+
+
+@pytest.mark.parametrize("polarity", [0, 1])
+def test_fragments_from_int8_rows_strided(dev, oracle_mod, polarity):
+    """k_fgemm on odd bases and row strides, and a wider output."""
+    import torch
+    import paper_2609_32922_amd as scg
+    rng = np.random.default_rng(941 + polarity)
+    M, N, K, L_max, lda, ldb, ldo = 40000, 70, 1500, 8, 1507, 1503, 75
+    Abuf = rng.integers(-127, 128, M * lda + 3).astype(np.int8)
+    Bbuf = rng.integers(-127, 128, N * ldb + 1).astype(np.int8)
+    sa, sb = rng.uniform(0.001, 0.05, M).astype(np.float32), rng.uniform(0.001, 0.05, N).astype(np.float32)
+    L = rng.integers(0, L_max + 1, M).astype(np.int32)
+    d = scg.ScGemmDesc()
+    d.batch, d.M, d.N, d.K, d.lda, d.ldb, d.ldo = 1, M, N, K, lda, ldb, ldo
+    d.strideO = M * ldo
+    d.L_max, d.polarity, d.seed = L_max, polarity, 941
+    tA, tB, tsa, tsb, tL = (torch.from_numpy(a).to(dev) for a in (Abuf, Bbuf, sa, sb, L))
+    out = torch.zeros(M * ldo, dtype=torch.float32, device=dev)
+    cnt = torch.full((M * ldo,), -5, dtype=torch.int32, device=dev)
+    ws = scg.Workspace(scg.sc_gemm_workspace_size(d), dev)
+    _note("fragments from int8 rows, strided, polarity %d" % polarity)
+    sh = int(torch.cuda.current_stream().cuda_stream)
+    rc = scg.sc_gemm(d, tA.data_ptr() + 3, tsa.data_ptr(), tB.data_ptr() + 1, tsb.data_ptr(), tL.data_ptr(),
+                     out.data_ptr(), cnt.data_ptr(), ws.ptr, ws.nbytes, sh)
+    assert rc == 0 and scg.sc_gemm_status(ws.ptr, sh) == 0
+    c = cnt.cpu().numpy().reshape(M, ldo)
+    o = out.cpu().numpy().reshape(M, ldo)
+    rows = _sample(M, rng, 60)
+    A = np.stack([Abuf[3 + i * lda: 3 + i * lda + K] for i in rows])
+    B = np.stack([Bbuf[1 + j * ldb: 1 + j * ldb + K] for j in range(N)])
+    c_ref, o_ref = oracle_mod.sc_gemm(A, B, sa[rows], sb, L[rows], L_max, polarity, 941)
+    assert np.array_equal(c[rows][:, :N], c_ref)
+    assert np.all(np.abs(o[rows][:, :N] - o_ref) <= REL_TOL * np.abs(o_ref))
+    assert np.all(c[:, N:] == -5)
+
+
+# Outputs of 64-row blocks past 31-bit byte offsets (a wide row stride): decoded by the split sum with 64-bit
+# addresses, so such a call takes parts however small it is.
+@pytest.mark.parametrize("M,N,K,L_max,polarity", [(5, 70, 40, 64, 0), (3, 300, 100, 96, 1)])
+def test_outputs_past_31_bit_offsets(dev, oracle_mod, M, N, K, L_max, polarity):
+    import torch
+    import paper_2609_32922_amd as scg
+    ldo = (1 << 31) // 4 // (M - 2) + 9      # the last row starts past 2^31 bytes
+    rng = np.random.default_rng(951 + M)
+    g = W.random_gemm(rng, 1, M, N, K, L_max, polarity, 951)
+    A, sA, B, sB, L = _to_dev(g, dev)
+    d = scg.make_desc(A, B, L_max, polarity, 951)
+    d.ldo, d.strideO = ldo, M * ldo
+    out = torch.empty((M - 1) * ldo + N, dtype=torch.float32, device=dev)
+    cnt = torch.empty((M - 1) * ldo + N, dtype=torch.int32, device=dev)
+    ws = scg.Workspace(scg.sc_gemm_workspace_size(d), dev)
+    _note("output rows past 2^31 bytes, %d x %d" % (M, N))
+    rc = scg.sc_gemm(d, A.data_ptr(), sA.data_ptr(), B.data_ptr(), sB.data_ptr(), L.data_ptr(), out.data_ptr(),
+                     cnt.data_ptr(), ws.ptr, ws.nbytes, int(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0
+    c = np.stack([cnt[i * ldo: i * ldo + N].cpu().numpy() for i in range(M)])
+    o = np.stack([out[i * ldo: i * ldo + N].cpu().numpy() for i in range(M)])
+    _compare(g, 0, np.arange(M), np.arange(N), o[None], c[None], oracle_mod, "far rows")
+    del out, cnt
+    torch.cuda.empty_cache()
+
+
+# The range division at its bounds: ranges of more chunk steps than one accumulator sums (no tile has as many), and
+# tiles that have more, which every range cuts (one row length per pair at most is longer: skewed lengths).
+LONG_RANGES = [
+    # M, N, K, L_max, polarity, seed
+    (4400, 4400, 16000, 1024, 0, 961),       # 16000 steps a tile, 20250 a range
+    (1100, 900, 131200, 256, 1, 963),        # 32800 steps a tile
+    (2600, 2600, 16416, 1024, 0, 965),
+]
+
+
+@pytest.mark.parametrize("case", LONG_RANGES, ids=[str(c) for c in LONG_RANGES])
+def test_long_ranges(dev, oracle_mod, case):
+    M, N, K, L_max, pol, seed = case
+    rng = np.random.default_rng(seed)
+    g = W.random_gemm(rng, 1, M, N, K, L_max, pol, seed, uniform_L=L_max)
+    g.L[0, M // 2:] = (L_max * rng.random(M - M // 2) ** 2).astype(np.int32)
+    # saturated rows and columns: sums of +-1 products only, past 2^24 where the tile is
+    g.A[0, :2] = 127
+    g.B[0, 0] = 127
+    g.B[0, N - 1] = -127
+    _note("long ranges %s" % (case,))
+    out, cnt = _run(g, dev, L_hint=int(g.L.mean()))
+    rows = np.union1d([0, 1, M // 2, M - 1], rng.choice(M, 4))
+    cols = np.union1d([0, N - 1], rng.choice(N, 4))
+    _compare(g, 0, rows, cols, out, cnt, oracle_mod, "long ranges%s" % (case,))

@@ -165,3 +165,50 @@ def test_no_row_count_loses_the_plans(layout, N, K):
         for M in range(150, 8192, 97):
             lay = layout(1, M, N, K, L_max)
             assert lay["nplans"] > 1, (M, L_max, lay)
+
+
+def _cases(name):
+    import test_gpu_parity
+    return getattr(test_gpu_parity, name)
+
+
+# (columns of a wave / 32, parts, int16 counts) that each case of 64-row blocks takes, in order
+TALL_VARIANTS = [(1, 4, 1), (1, 1, 0), (1, 8, 1), (1, 8, 0), (5, 1, 0), (4, 7, 1), (1, 1, 0), (4, 5, 1), (5, 1, 0),
+                 (2, 1, 0), (2, 8, 1), (2, 8, 1), (1, 1, 0), (1, 9, 0)]
+
+
+def test_the_parity_cases_take_the_variants_they_name(layout):
+    """A case whose sizes come to take another kernel or division is to be replaced, not kept under its label."""
+    got = []
+    for batch, M, N, K, L_max, _, pol, bcast, _ in _cases("TALL"):
+        lay = layout(batch, M, N, K, L_max, pol, own_B=not bcast and batch > 1)
+        got.append((lay["tall"], lay["S"], lay["p16"]))
+    assert got == TALL_VARIANTS
+    got = []
+    for M, N, K, L_max, _, pol, _ in _cases("INT32_PARTS"):
+        lay = layout(1, M, N, K, L_max, pol)
+        got.append((lay["tall"], lay["S"], lay["p16"]))
+    assert got == [(2, 8, 0), (2, 8, 0), (4, 8, 0), (4, 8, 0)]
+    got = []
+    for batch, M, N, K, L_max, _, pol, bcast, _ in _cases("FGEMM"):
+        lay = layout(batch, M, N, K, L_max, pol, own_B=not bcast and batch > 1)
+        got.append((lay["fused"], lay["S"]))
+    assert got == [(1, 1), (1, 1), (1, 2), (1, 8), (1, 8), (1, 1)]
+    assert layout(1, 40000, 70, 1500, 8, lda=1507, ldb=1503, ldo=75)["fused"]
+    got = []
+    for M, N, K, L_max, rng in _cases("PAST_BOUND"):
+        lay = layout(1, M, N, K, L_max, rng=rng)
+        got.append((lay["rgen"], lay["tall"], lay["narrow"], lay["S"] >= 2))
+    assert got == [(1, 1, 0, True), (1, 1, 0, True), (1, 1, 0, True), (1, 0, 1, True), (1, 0, 0, True),
+                   (0, 0, 0, True), (0, 0, 0, True)]
+    for batch, M, N, K, L_max, kind, hint, pol, bcast, _ in _cases("WIDE"):
+        lay = layout(batch, M, N, K, L_max, pol, hint=hint, own_B=not bcast and batch > 1)
+        assert lay["rgen"] and not lay["tall"] and not lay["narrow"] and bool(lay["vsplit"]) == (hint > 0)
+    for M, N, K, L_max, pol, _ in _cases("LONG_RANGES"):
+        lay = layout(1, M, N, K, L_max, pol, hint=int(L_max * 0.66))
+        assert lay["vsplit"] and not lay["narrow"]
+
+
+def test_outputs_past_31_bit_offsets_take_parts(layout):
+    for M, N, K, L_max in ((5, 70, 40, 64), (3, 300, 100, 96)):
+        assert layout(1, M, N, K, L_max, ldo=(1 << 29) // (M - 2) + 9)["S"] >= 2
