@@ -519,10 +519,13 @@ bool make_layout(const sc_gemm_desc &d, int cus, Layout *lay) {
 }
 
 // Products of a C-BSG call from which the tables are tried: there the launches that may return at
-// once (two, about 5 us, beside the chunks' 7) are small against the planes' path (over 200 us)
+// once (two, about 5 us, beside the chunks' 7) are small against the planes' path (over 200 us).  And
+// with more than an octet of cycles: a group of 32 slots costs four of them, and 55 calls of 4, 7 and 8
+// cycles took up to 2.2 times as long from tables (13132 x 5516 x 768 four times at L = 4: 926 and 2034 us;
+// at L = 12 23 calls took 0.65 to 1.18 times as long)
 static constexpr double CBSG_TABLES = 4e11;
 bool make_cbsg_layout(const sc_gemm_desc &d, int cus, const Layout &planes, Layout *lay) {
-    if (d.rng != SC_RNG_SOBOL8_CBSG || d.batch < 1 || d.K < 1 || (d.L_hint > 0 && d.L_hint < d.L_max) ||
+    if (d.rng != SC_RNG_SOBOL8_CBSG || d.batch < 1 || d.K < 1 || d.L_max <= MSTEP || (d.L_hint > 0 && d.L_hint < d.L_max) ||
         (double)d.batch * d.M * d.N * d.K * d.L_max < CBSG_TABLES)
         return false;
     if (round_up(d.K, 32) * round_up(d.L_max, 32) >= MFMA_EXACT || !layout_with(d, cus, LAY_FULL, true, lay) || !lay->rgen)

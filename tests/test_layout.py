@@ -113,7 +113,7 @@ def test_cbsg_tables_over_every_planes_layout(layout):
     # each part of the tables inside the planes' part it lies on: over sizes where either is tightest
     n = 0
     for K in (1, 3, 16, 17, 33, 64, 97, 1000):
-        for L_max in (1, 7, 8, 9, 64, 255, 256):
+        for L_max in (9, 16, 17, 33, 64, 255, 256):
             for M, N in ((1, 1 << 20), (64, 70000), (100, 40000), (129, 60), (300, 300), (70000, 100), (1 << 20, 1)):
                 batch = max(1, int(4.1e11 // (M * N * K * L_max)) + 1)
                 if batch > 1 << 20:
@@ -165,6 +165,12 @@ def test_no_row_count_loses_the_plans(layout, N, K):
         for M in range(150, 8192, 97):
             lay = layout(1, M, N, K, L_max)
             assert lay["nplans"] > 1, (M, L_max, lay)
+
+
+@pytest.mark.parametrize("L_max,tables", [(1, False), (4, False), (8, False), (9, True), (128, True)])
+def test_cbsg_tables_from_an_octet_of_cycles_on(layout, L_max, tables):
+    # a group of 32 slots for less than that costs more than the planes
+    assert isinstance(layout(4, 13132, 5516, 768, L_max, 1, rng=1, tables=True), dict) == tables
 
 
 def _cases(name):
