@@ -626,7 +626,8 @@ static int enqueue(const sc_gemm_desc &d, const Layout &lay, const Layout &table
                        launch_rprep(d, tables, A, B, ws, st) != hipSuccess))
         return SC_ERR_HIP;
     if (!fuse && !try_tables) {
-        e = launch_draws(d.seed, d.rng, lay.LBS, rA, reinterpret_cast<uint32_t *>(ws + lay.off_rB), nullptr, -1,
+        // (the layout of an empty int8-chunk GEMM has no room for sequences: the status only)
+        e = launch_draws(d.seed, d.rng, lay.rgen ? 0 : lay.LBS, rA, reinterpret_cast<uint32_t *>(ws + lay.off_rB), nullptr, -1,
                          reinterpret_cast<uint32_t *>(ws + lay.off_status), st);
         if (e != hipSuccess) return SC_ERR_HIP;
     }

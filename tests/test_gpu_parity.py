@@ -828,6 +828,31 @@ def test_noalloc_keeps_long_narrow_calls(dev, oracle_mod):
     _compare(g, 0, rows, np.arange(N), out.cpu().numpy(), cnt.cpu().numpy(), oracle_mod, "noalloc long narrow")
 
 
+@pytest.mark.parametrize("batch,M,N,K", [(1, 0, 300, 64), (1, 300, 0, 64), (0, 300, 300, 64), (3, 0, 0, 64)])
+def test_empty_calls_write_the_status_alone(dev, batch, M, N, K):
+    """The layout of an empty call with comparator streams has no room for sequences of cycles."""
+    import torch
+    import paper_2609_32922_amd as scg
+    L = 1000
+    d = scg.make_desc(torch.empty((1, 1, K), dtype=torch.int8), torch.empty((1, 1, K), dtype=torch.int8), L, 0, 1)
+    d.batch, d.M, d.N, d.ldo, d.strideO = batch, M, N, max(N, 1), M * N
+    d.strideA, d.strideB, d.strideSA, d.strideSB, d.strideL = M * K, 0, M, 0, M
+    n = scg.sc_gemm_workspace_size(d)
+    ws = torch.full((n + 256,), 0x5A, dtype=torch.uint8, device=dev)
+    base = -ws.data_ptr() % 256
+    x = torch.zeros(max(M, N, 1) * K, dtype=torch.int8, device=dev)
+    f = torch.ones(max(M, N, 1), dtype=torch.float32, device=dev)
+    Lt = torch.full((max(M, 1),), L, dtype=torch.int32, device=dev)
+    sh = int(torch.cuda.current_stream().cuda_stream)
+    _note("empty call %d x (%d x %d x %d)" % (batch, M, N, K))
+    rc = scg.sc_gemm(d, x.data_ptr(), f.data_ptr(), x.data_ptr(), f.data_ptr(), Lt.data_ptr(), f.data_ptr(), 0,
+                     ws.data_ptr() + base, n, sh)
+    assert rc == 0 and scg.sc_gemm_status(ws.data_ptr() + base, sh) == 0
+    w = ws.cpu().numpy()[base:]
+    assert not w[:4].any() and (w[32:] == 0x5A).all()
+    assert (f == 1).all()
+
+
 # C-BSG calls of one row length from 4e11 products on: the tables of the int8-chunk GEMM (bipolar
 # counters k and L - 1 - k share a slot; unipolar slots from the plan) in place of the planes, and
 # the same sizes with other lengths, where the planes serve and the tables return at once.  Odd
