@@ -7,8 +7,11 @@ Prints ONE JSON line.  ``value`` is whole-call throughput in stream-bit-ops/s
 (N * K * sum_i L_i per step / seconds per step).  ``roofline`` is for the dominant kernel
 (the counting GEMM of the largest GEMM and, when its tiles are split, the pass that sums
 the splits), timed with HIP events that the library records around exactly those launches
-on the call's stream: one stream-bit-op is one fp4 product on the matrix cores (2 flops),
-against the dense fp4 MFMA peak.  ``valu_bitop_peak`` is the measured rate of the same
+on the call's stream: one stream-bit-op is one fp4 product (2 flops), against the dense fp4
+MFMA peak.  ``achieved`` and ``frac`` count the call's bit products, of which merged cycles
+share a multiply-add, so they are no utilisation and may pass the peak; ``issued`` and
+``issued_frac`` count the products that the MFMA instructions of one launch run (committed
+rocprofv3 counters, like ``traffic``) and cannot.  ``valu_bitop_peak`` is the measured rate of the same
 work done as packed words on the vector ALUs (AND + accumulating popcount, 2 instructions
 per 32 bit pairs: libscpeak), with the clock under that load; ``value`` is also given as a
 multiple of it.  ``cpu_baseline`` times the CPU oracle on a bounded row sample.
@@ -61,21 +64,22 @@ def parse():
 def kernel_source_digest():
     import hashlib
     h = hashlib.sha256()
-    for name in ("sc_internal.h", "sc_kernels.hip", "sc_mfma.hip"):
+    for name in ("sc_api.hip", "sc_internal.h", "sc_kernels.hip", "sc_mfma.hip"):
         with open(os.path.join(ROOT, "paper_2609_32922_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()
 
 
-def measured_traffic(workload):
-    """HBM bytes per GEMM launch from the committed rocprofv3 counter summary, or None
-    when the summary is missing or the kernel source changed since it was taken."""
+def counted(what, workload):
+    """A count per GEMM launch (HBM bytes, products of the MFMA instructions) from the committed
+    rocprofv3 counter summary of a workload, or None when the summary is missing or the sources
+    changed since it was taken."""
     import glob
     import re
     for path in glob.glob(os.path.join(ROOT, "profiles", "*counters*.md")):
         with open(path) as f:
             text = f.read()
-        m = re.search(r"^traffic_bytes_per_launch:\s*(\d+)\s+workload:\s*(\S+)\s+"
+        m = re.search(r"^" + what + r":\s*(\d+)\s+workload:\s*(\S+)\s+"
                       r"kernel_source_sha256:\s*([0-9a-f]+)", text, re.M)
         if m and m.group(2) == workload and m.group(3) == kernel_source_digest():
             return int(m.group(1))
@@ -167,15 +171,20 @@ def main():
     gemm_ms = float(np.mean([ev_pairs[s][kidx][0].elapsed_time(ev_pairs[s][kidx][1]) for s in timed]))
     g_dom = w.gemms[kidx]
     achieved = g_dom.bitops() / (gemm_ms * 1e-3)
-    traffic = measured_traffic("%s:%s" % (args.workload, args.rng))
+    traffic = counted("traffic_bytes_per_launch", "%s:%s" % (args.workload, args.rng))
     # one bit-pair product = one fp4 multiply-add = 2 flops on the matrix cores
+    issued = counted("issued_products_per_launch", "%s:%s" % (args.workload, args.rng))
+    issued = issued / (gemm_ms * 1e-3) if issued is not None else None
     roofline = {"bound": "mfma", "achieved": 2 * achieved / 1e12, "peak": PEAK_FP4_FLOPS / 1e12,
                 "unit": "TFLOP/s", "frac": 2 * achieved / PEAK_FP4_FLOPS, "traffic": traffic,
                 "kernel": "%s<%s>" % (gemm_kernel_name(g_dom, rng == scg.SC_RNG_LFSR32),
                                       "bipolar" if g_dom.polarity == 0 else "unipolar"),
                 "kernel_ms": gemm_ms, "kernel_ms_steps": len(timed), "kernel_stream_bit_ops_per_s": achieved,
-                "counts": "bit products of the call; cycles whose draws share a class share one "
-                          "multiply-add of the kernel, so frac is not bounded by 1"}
+                "issued": 2 * issued / 1e12 if issued is not None else None,
+                "issued_frac": 2 * issued / PEAK_FP4_FLOPS if issued is not None else None,
+                "counts": "achieved and frac: bit products of the call, of which cycles whose draws share "
+                          "a class share one multiply-add (no utilisation, not bounded by 1); issued and "
+                          "issued_frac: products of the MFMA instructions run"}
 
     valu = None
     if not args.no_valu_peak:
@@ -239,8 +248,8 @@ def settle_clock(step, stream, batch=10, min_s=0.1, max_s=3.0, tol=0.01):
 
 
 def gemm_kernel_name(g, comparator):
-    """The counting kernel the library takes for the workloads' shapes (its estimates decide; see
-    make_layout): blocks of 256 rows x 64 columns for N <= 64, of 64 rows for few rows or columns and
+    """The counting kernel the library takes for the workloads' shapes (its estimates decide, in
+    make_layout; a test holds these names to it for every workload): blocks of 256 rows x 64 columns for N <= 64, of 64 rows for few rows or columns and
     for short tiles with varying lengths, else of 256 x 256.  C-BSG calls run on the same kernels when
     every row has L_max cycles and the call is large, else on fp4 planes."""
     if not comparator and (g.L.min() < g.L_max or g.bitops() < 4e11):

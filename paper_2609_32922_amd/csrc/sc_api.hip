@@ -134,8 +134,7 @@ static bool layout_with(const sc_gemm_desc &d, int cus, int spend, bool cbsg, La
     // comparator streams with few rows or columns, or short tiles with varying lengths
     // (attention heads): the int8-chunk GEMM in blocks of 64 rows
     const bool few = lfsr && !l.narrow && (d.M <= BM || d.N <= BN);
-    // few columns and no room for chunks of a long A: k_fgemm takes the operands as they are
-    // (operand offsets must fit 31 bits)
+    // few columns and no chunks of A: k_fgemm takes the operands as they are (operand offsets must fit 31 bits)
     l.fused = few && spend == LAY_LEAST && d.N <= BN && fused_extent(d.M, d.lda, d.K) < INT_MAX - 4 &&
               fused_extent(d.N, d.ldb, d.K) < INT_MAX - 4;
     // Blocks of 64 rows x 128 C columns in S parts where that is estimated to take the least time:
@@ -223,7 +222,7 @@ static bool layout_with(const sc_gemm_desc &d, int cus, int spend, bool cbsg, La
     if (!lfsr) off = align256(off + (size_t)(d.L_max + 1) * CA_COLS * 2);
     // Slot plans: while a tile's products sum to less than 2^24 in magnitude whatever slots hold
     // them (K x L_max; so every part is exact), and more than one group of 32 cycles exists.
-    // At most 32 plans past the first, and at most PLAN_GROUPS tables.
+    // At most 32 plans past the first, and at most PLAN_GROUPS tables of theirs (past the first's).
     l.nplans = 1;
     l.pstep = LCH;
     if (spend <= LAY_TWO_PLANS && !cbsg && l.rgen && l.LBS > 32 && (int64_t)l.KC * 32 * l.LBS < MFMA_EXACT) {
@@ -485,11 +484,12 @@ bool make_layout(const sc_gemm_desc &d, int cus, Layout *lay) {
         Layout least;
         if (layout_with(d, cus, LAY_LEAST, false, &least) && least.total < lay->total - MOST_EXTRA) *lay = least;
     }
-    // A call that fits sc_gemm_noalloc's array in some layout keeps fitting it: the one estimated to take the
-    // least time of fewer parts, of fewer plans, of none, and of no chunks if none does not fit either.  (500
-    // calls of up to 9000 rows, with 64 to 220 MiB in full: 1.06 times the full layout's time in the middle,
-    // where going without plans at once took 1.68 times, as long as before there were any.  2200 x 1024 x
-    // 1024 at L = 256: 66.6 MiB in 7 parts, 57.8 in 6)
+    // A call that fits sc_gemm_noalloc's array in some layout keeps fitting it (sc_gemm_workspace_size reports
+    // what both entry points use, so sc_gemm pays for it too): of those that fit, the one with the least
+    // estimated time among fewer parts, fewer plans and no plans, or else the one without chunks.
+    // (500 calls of up to 9000 rows, with 64 to 220 MiB in full: 1.06 times the full layout's time in the
+    // middle, where going without plans at once took 1.68 times, as long as before there were any.  2200 x
+    // 1024 x 1024 at L = 256: 66.6 MiB in 7 parts, 57.8 in 6)
     if (lay->total <= SC_NOALLOC_WORKSPACE_BYTES) return true;
     Layout best, l;
     double least_t = 1e30;

@@ -6,8 +6,8 @@
 //              tile-pair cycle count of the call (256-row GEMM), then one uint32: nonzero
 //              when some 256-row pair holds more row lengths that end inside a slot group
 //              than the int8-chunk GEMM has masked tables (rslots; it then masks its
-//              fragments), then one uint32: nonzero when a C-BSG call's tables serve.  Cleared by k_draws (or k_schedule), or, int8-chunk GEMM, written
-//              by k_rprep
+//              fragments), then one uint32: nonzero when a C-BSG call's tables serve.  Cleared
+//              by k_draws (or k_schedule), or, int8-chunk GEMM, written by k_rprep
 //   draws      rA[LBS], rB[LBS]                   uint32, comparator sequences (not with rgen)
 //   CA         C-BSG only: CA[L][beta] = #{l < L : rA_l < beta}, uint16 [L_max+1][257]
 //   plan       int8-chunk GEMM only: slot plans (see below), int4 {prefix, merged slots,
@@ -52,8 +52,12 @@
 // 64-row blocks (tall): A's chunks a row tile each, bytes [KC][64][32]; B's as above, or with N <= 64 or
 // 128 bytes [KC][64 or 128][32] (chunk_bits_b).
 //
-// N <= 128 with comparator streams and chunks that would not fit the array of sc_gemm_noalloc
-// (fused): no planes or chunks; the GEMM builds its fragments from the int8 rows themselves.
+// N <= 128 with comparator streams (fused): no planes or chunks where streams are so short that laying
+// them out costs more than it saves, or where they would not fit sc_gemm_noalloc's array or would add
+// gigabytes (make_layout); the GEMM builds its fragments from the int8 rows themselves.
+//
+// A C-BSG call's tables (make_cbsg_layout): rows, chunks and partial sums of the int8-chunk GEMM in the
+// memory of the planes, which are only written if the tables do not serve; the rest behind it all.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -111,14 +115,15 @@ __host__ __device__ inline double quad_split_time(int64_t tiles, int s, double p
 // takes the plan with the largest prefix no longer than its shortest row, and a row of L >=
 // p_k cycles ends after S_k + L - p_k slots.  Prefixes: multiples of pstep, and L_max.
 //
-// C-BSG calls whose rows all have L = L_max cycles take the same GEMM: A's bit of counter k is
+// Large C-BSG calls whose rows all have L = L_max cycles take the same GEMM: A's bit of counter k is
 // [k < c(n)], c(n) = #{l < L : class(rA_l) <= n}, so it is [n >= the (k + 1)-th smallest class of A's
 // draws].  Bipolar: A holds sgn D_k = [k < c] - [k < L - c], the same at k and L - 1 - k, so the two
 // share a slot: half the cycles.  The host cannot see the lengths, so it enqueues this path (first)
 // and the planes path, and the one that does not serve returns at once.
 constexpr int SLOT_CYCLES = 4;
 constexpr int MAX_PLANS = 40;    // plans of a call (bits of the status words)
-constexpr int PLAN_GROUPS = 512; // most (plan, group) tables of a call, 8 KiB each
+constexpr int PLAN_GROUPS = 512; // most (merged plan, group) tables of a call, 8 KiB each (the
+                                 // plan of no cycle adds its L_max / 32: 640 in all at L_max = 4096)
 constexpr int UNIT_PLAN = 1 << 24;   // a unit's partial index (below 2^22) and plan in one word
 
 constexpr int TROWS = 64;        // rows of a block of k_tgemm

@@ -18,8 +18,8 @@
 //   k_mplanes     nibble planes of A (sorted rows, per-row lengths) or B (C-BSG), one block per
 //                 128-row tile x 64 cycles x 64 elements; element parameters and an
 //                 8-cycle lookup table in LDS, 16-byte stores, 1 KB per wave
-//   k_fgemm       N <= 128 with comparator streams where chunks of A would not fit the array of
-//                 sc_gemm_noalloc: 128x128 tile, the fp4 fragments of both operands built
+//   k_fgemm       N <= 128 with comparator streams, for long A with streams of about 8 cycles, and where
+//                 chunks of A would not fit sc_gemm_noalloc's array or would add gigabytes: 128x128 tile, the fp4 fragments of both operands built
 //                 in LDS from the int8 rows (an 8-cycle table per octet indexed by the int8
 //                 byte), so no planes or chunks are written or read
 //   k_rprep       int8 operands (A in the scheduler's row order) laid out in 32-element
@@ -2528,7 +2528,7 @@ __device__ __forceinline__ void rgemm_body(const MGemmArgs &g, const Layout &lay
     uint32_t *rems = sh.rems;
     DecodeLds &dl = sh.dl;
     const int NTW = lay.NT / 2;
-    // the block's units: one, or with vsplit its range of the work (k_units)
+    // the block's units: one, or with vsplit its range of the work (from k_rprep)
     int ub = blockIdx.x, ue = blockIdx.x + 1;
     if (lay.vsplit) {
         // The 256 x 64 blocks run two per CU; the dispatcher gives every CU one block before

@@ -6,6 +6,8 @@ import subprocess
 
 import pytest
 
+import workloads as W
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 HIPCC = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "bin", "hipcc")
 pytestmark = pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
@@ -218,3 +220,23 @@ def test_the_parity_cases_take_the_variants_they_name(layout):
 def test_outputs_past_31_bit_offsets_take_parts(layout):
     for M, N, K, L_max in ((5, 70, 40, 64), (3, 300, 100, 96)):
         assert layout(1, M, N, K, L_max, ldo=(1 << 29) // (M - 2) + 9)["S"] >= 2
+
+
+@pytest.mark.parametrize("name", sorted(W.WORKLOADS))
+def test_benchmark_names_the_kernel_that_runs(layout, name):
+    # the roofline's kernel name is worked out from the shape; the layout is what the call takes
+    import bench
+    for g in W.WORKLOADS[name]().gemms:
+        hint = int(round(float(g.L.mean())))
+        shape = dict(batch=g.batch, M=g.M, N=g.N, K=g.K, L_max=g.L_max, polarity=g.polarity, hint=hint,
+                     own_B=g.B.shape[0] > 1)
+        for rng in (0, 1):
+            if rng == 1 and g.L_max > 256:
+                continue
+            lay = layout(rng=rng, **shape)
+            if rng == 1 and g.L.min() == g.L_max:
+                tables = layout(rng=1, tables=True, **shape)
+                lay = tables if isinstance(tables, dict) else lay
+            want = ("k_tgemm" if lay["tall"] else "k_rgemm_n" if lay["narrow"] else "k_rgemm") if lay["rgen"] else \
+                   ("k_qgemm" if g.M > 128 and g.N > 128 else "k_mgemm")
+            assert bench.gemm_kernel_name(g, rng == 0) == want, (name, g.name, rng)
