@@ -129,6 +129,10 @@ def test_cbsg_tables_over_every_planes_layout(layout):
 
 
 @pytest.mark.parametrize("batch,M,N,K,L_max,hint,fused", [
+    (564, 79, 128, 378, 7, 0, True),         # few rows each: both operands' chunks, 67 us against 93
+    (49666, 16, 4, 268, 4, 1, True),
+    (51261, 8, 68, 266, 8, 2, True),         # 2.9 ms against 4.2
+    (209, 16, 128, 1441, 1, 0, False),       # 82 us against 67
     (1, 24589, 116, 1983, 8, 0, True),
     (8, 45067, 87, 3067, 8, 0, True),
     (1, 40413, 118, 2959, 16, 5, True),
@@ -138,7 +142,7 @@ def test_cbsg_tables_over_every_planes_layout(layout):
 ])
 def test_few_columns_and_short_streams(layout, batch, M, N, K, L_max, hint, fused):
     # an octet of cycles costs 64-row blocks a whole group of 32 slots: k_fgemm where the call is large
-    lay = layout(batch, M, N, K, L_max, hint=hint)
+    lay = layout(batch, M, N, K, L_max, hint=hint, own_B=batch > 100)
     assert bool(lay["fused"]) == fused and bool(lay["tall"]) != fused
 
 
