@@ -466,24 +466,30 @@ static constexpr size_t MOST_EXTRA = (size_t)8 << 30;
 bool make_layout(const sc_gemm_desc &d, int cus, Layout *lay) {
     if (!layout_with(d, cus, LAY_FULL, false, lay)) return layout_with(d, cus, LAY_LEAST, false, lay);
     // Few columns and lengths of 8 cycles or less on average: k_fgemm runs octets of cycles, a quarter of the
-    // 32-slot groups, and lays out no chunks, but at half the rate.  Streams of 8 cycles: taken where reading
-    // the operands (0.67 us a MB) and writing and reading A's chunks (0.39, padding rows too) and the fixed
-    // cost of 64-row blocks outweigh its stages (16 elements of an octet; two blocks a CU).  Fitted to 2500
-    // calls: 56 of them are 10 % slower than in k_fgemm and 8 than in 64-row blocks (A's chunks alone, which
-    // leaves out batches of few rows with operands of their own: over 240 and 1).  Longer streams: by A's chunks
-    // (1.1 us a MB).  (us, 64-row blocks against k_fgemm: 24589 x 116 x 1983 at L = 8 148 and 105;
-    // 8 x 45067 x 87 x 3067 1524 and 1015; 564 x 79 x 128 x 378, a B each, at L = 7 93 and 67; 2196 x 114 x 71 24 and 32;
-    // lengths up to 16 with a mean of 8, 40413 x 118 x 2959 262 and 182, 8 x 3811 x 79 x 1032 82 and 84.)
+    // 32-slot groups, and lays out no chunks, but at half the rate.  Taken where reading the operands (0.67 us a
+    // MB), writing and reading A's chunks (0.39, padding rows too) and the fixed cost of 64-row blocks outweigh
+    // its stages (16 elements of an octet; two blocks a CU), with a wider margin where lengths differ; or, many
+    // rows, by A's chunks alone (1.1 us a MB).  Fitted to 3400 calls: 108 of them are 10 % slower than in
+    // k_fgemm and 12 than in 64-row blocks (by A's chunks alone, which leaves out batches of few rows and of a
+    // B each: 325 and 6).  (us, 64-row blocks against k_fgemm: 24589 x 116 x 1983 at L = 8 148 and 105; 8 x 45067 x 87 x
+    // 3067 1524 and 1015; 564 x 79 x 128 x 378, a B each, at L = 7 93 and 67; 2196 x 114 x 71 24 and 32; lengths up
+    // to 16 with a mean of 8, 40413 x 118 x 2959 262 and 182, 8 x 3811 x 79 x 1032 82 and 84.)
     const int Lmean = d.L_hint > 0 ? d.L_hint : d.L_max;
     Layout taken;
-    if (lay->tall && d.N <= BN && Lmean <= MSTEP && layout_with(d, cus, LAY_LEAST, false, &taken) && taken.fused) {
-        const double rounds = (double)d.batch * taken.MT * taken.S / (MFMA_BLOCKS_PER_CU * taken.cus);
-        const double stages = (double)(taken.KQP / MSTAGE) / taken.S;
+    const bool few_short =
+        lay->tall && d.N <= BN && Lmean <= MSTEP && layout_with(d, cus, LAY_LEAST, false, &taken) && taken.fused;
+    double rounds = 0, octets = 0, chunks = 0, operands = 0;
+    if (few_short) {
+        rounds = (double)d.batch * taken.MT * taken.S / (MFMA_BLOCKS_PER_CU * taken.cus);
+        const double stages = (double)(taken.KQP / MSTAGE) / taken.S, longest = ceil((double)d.L_max / MSTEP);
         const double load = stages * (rounds <= 0.5 ? 1.0 : Lmean >= d.L_max ? ceil(rounds) : fmax(rounds, 1.0));
-        const double chunks = (double)d.batch * lay->rtiles * lay->KC * (TROWS * 32 / 1e6);
-        const double operands = ((double)d.batch * d.M + (double)lay->nbB * d.N) * d.K / 1e6;
-        if (d.L_max <= MSTEP ? 0.39 * chunks + 0.67 * operands + 2.5 * rounds > 0.41 * load + 5.2
-                             : 1.1 * chunks > 0.8 * load + 3 * rounds + 25)
+        octets = fmax(load * fmin(fmax((Lmean + 6.0) / MSTEP, 1.0), longest), stages * longest);
+        chunks = (double)d.batch * lay->rtiles * lay->KC * (TROWS * 32 / 1e6);
+        operands = ((double)d.batch * d.M + (double)lay->nbB * d.N) * d.K / 1e6;
+        const double saved = 0.39 * chunks + 0.67 * operands + 2.5 * rounds;
+        if (d.L_max <= MSTEP ? saved > 0.41 * octets + 5.2
+                             : (d.L_max <= 2 * MSTEP && saved > 0.6 * octets + 15) ||
+                                   (d.M > BM && 1.1 * chunks > 0.8 * load + 3 * rounds + 25))
             *lay = taken;
     }
     if (lay->total > MOST_EXTRA) {
@@ -520,6 +526,12 @@ bool make_layout(const sc_gemm_desc &d, int cus, Layout *lay) {
     }
     if (lay->tall) consider(LAY_FULL, 0);
     if (!consider(LAY_TWO_PLANS, MAX_SPLIT)) consider(LAY_TWO_PLANS, 0);
+    // (k_fgemm once more, beside what a smaller layout costs 64-row blocks of longer streams: estimated times
+    // of both calls; 64-row blocks are overestimated, 1.2 to 1.7 times, k_fgemm by 0.75 to 1.2.  18 x 637 x 100 x
+    // 4669 at L = 12 with a mean of 4: 175 us in the parts that fit and 103; 61 x 103 x 63 x 4915, L = 24: 116 and 140)
+    if (few_short && taken.total <= SC_NOALLOC_WORKSPACE_BYTES &&
+        0.68 * octets + 14.4 * rounds + 0.15 * operands + 22 < 0.62 * (least_t + 17 + 0.39 * chunks + 0.67 * operands))
+        best = taken;
     *lay = best;
     return true;
 }

@@ -133,6 +133,8 @@ def test_cbsg_tables_over_every_planes_layout(layout):
     (49666, 16, 4, 268, 4, 1, True),
     (51261, 8, 68, 266, 8, 2, True),         # 2.9 ms against 4.2
     (209, 16, 128, 1441, 1, 0, False),       # 82 us against 67
+    (830, 339, 100, 124, 9, 3, True),        # lengths of 9 and less: 109 us against 137
+    (616, 108, 32, 4609, 24, 8, False),      # 912 us against 640
     (1, 24589, 116, 1983, 8, 0, True),
     (8, 45067, 87, 3067, 8, 0, True),
     (1, 40413, 118, 2959, 16, 5, True),
@@ -147,6 +149,17 @@ def test_few_columns_and_short_streams(layout, batch, M, N, K, L_max, hint, fuse
 
 
 ARRAY = 64 * MIB      # sc_gemm_noalloc's
+
+
+@pytest.mark.parametrize("batch,M,N,K,L_max,hint,own_B,fused", [
+    (18, 637, 100, 4669, 12, 4, True, True),      # 103 us against 175 in the parts that fit
+    (2, 8521, 100, 3018, 16, 5, True, True),      # 115 against 135
+    (61, 103, 63, 4915, 24, 8, True, False),      # 140 against 116
+    (163, 97, 32, 1627, 12, 4, True, False),      # 117 against 81
+])
+def test_few_columns_past_the_array(layout, batch, M, N, K, L_max, hint, own_B, fused):
+    lay = layout(batch, M, N, K, L_max, hint=hint, own_B=own_B)
+    assert bool(lay["fused"]) == fused and lay["total"] <= ARRAY
 
 
 @pytest.mark.parametrize("batch,M,N,K,L_max,polarity", [
