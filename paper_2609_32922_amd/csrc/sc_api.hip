@@ -471,8 +471,8 @@ bool make_layout(const sc_gemm_desc &d, int cus, Layout *lay) {
     // its stages (16 elements of an octet; two blocks a CU), with a wider margin where lengths differ; or, many
     // rows, by A's chunks alone (1.1 us a MB).  Fitted to 3400 calls: 108 of them are 10 % slower than in
     // k_fgemm and 12 than in 64-row blocks (by A's chunks alone, which leaves out batches of few rows and of a
-    // B each: 325 and 6).  (us, 64-row blocks against k_fgemm: 24589 x 116 x 1983 at L = 8 148 and 105; 8 x 45067 x 87 x
-    // 3067 1524 and 1015; 564 x 79 x 128 x 378, a B each, at L = 7 93 and 67; 2196 x 114 x 71 24 and 32; lengths up
+    // B each: 325 and 6).  (us, 64-row blocks against k_fgemm: 24589 x 116 x 1983 at L = 8 148 and 105;
+    // 8 x 45067 x 87 x 3067 1524 and 1015; 564 x 79 x 128 x 378, a B each, at L = 7 93 and 67; 2196 x 114 x 71 24 and 32; lengths up
     // to 16 with a mean of 8, 40413 x 118 x 2959 262 and 182, 8 x 3811 x 79 x 1032 82 and 84.)
     const int Lmean = d.L_hint > 0 ? d.L_hint : d.L_max;
     Layout taken;

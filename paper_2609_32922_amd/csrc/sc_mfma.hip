@@ -18,10 +18,11 @@
 //   k_mplanes     nibble planes of A (sorted rows, per-row lengths) or B (C-BSG), one block per
 //                 128-row tile x 64 cycles x 64 elements; element parameters and an
 //                 8-cycle lookup table in LDS, 16-byte stores, 1 KB per wave
-//   k_fgemm       N <= 128 with comparator streams, for long A with streams of about 8 cycles, and where
-//                 chunks of A would not fit sc_gemm_noalloc's array or would add gigabytes: 128x128 tile, the fp4 fragments of both operands built
-//                 in LDS from the int8 rows (an 8-cycle table per octet indexed by the int8
-//                 byte), so no planes or chunks are written or read
+//   k_fgemm       N <= 128 with comparator streams, for large calls of about 8 cycles, and where
+//                 chunks of A would not fit sc_gemm_noalloc's array or would add gigabytes:
+//                 128x128 tile, the fp4 fragments of both operands built in LDS from the int8
+//                 rows (an 8-cycle table per octet indexed by the int8 byte), so no planes or
+//                 chunks are written or read
 //   k_rprep       int8 operands (A in the scheduler's row order) laid out in 32-element
 //                 chunks per 256-row pair through LDS (rows read along, chunks written
 //                 contiguous), the input of k_rgemm and k_tgemm; its first blocks divide the

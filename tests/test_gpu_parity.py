@@ -948,8 +948,8 @@ def test_more_blocks_than_a_grid_dimension(dev, oracle_mod):
     torch.cuda.empty_cache()
 
 
-# k_fgemm: few columns, fragments from the int8 rows themselves.  Taken for long A and streams of 8 cycles or
-# less, and where an operand's chunks would not fit the array of sc_gemm_noalloc.  Both polarities, mixed lengths
+# k_fgemm: few columns, fragments from the int8 rows themselves.  Taken for large calls of 8 cycles or less
+# on average, and where an operand's chunks would not fit the array of sc_gemm_noalloc.  Both polarities, mixed lengths
 # with rows of 0, several batch entries, shared and own B, rows at every byte alignment, whole tiles,
 # parts for balance and parts for exactness.
 FGEMM = [
